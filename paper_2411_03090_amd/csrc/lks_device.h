@@ -68,23 +68,44 @@ __host__ __device__ inline int xcd_blocks(int tiles) {
 //   zero-flux node with normal velocity u_n:
 //     kappa = -(sum_q (ga_q - u_n ge_q) g_q) / (A0 - 2 u_n A1 + u_n^2 A2)
 //     g_unk[a] = sum_q Lg0[a][q] g_q - kappa (hc[a] - u_n h1[a])
-// The kernels read a copy rounded to their arithmetic type (RingOpT<R>),
-// which is what they used to form from the double entries at every use.
-template <typename T>
-struct RingOpT {
-  T Lf[2][3][9];
-  T Ls[2][3];
-  T Lk[2][3];
-  T Ld[3][9];
-  T Lg0[3][9];
-  T ga[9], ge[9];
-  T A0, A1, A2;
-  T hc[3], h1[3];
-  T uw[3], ucx[3], ucy[3];  // weight and velocity of the unknown directions
+struct RingOp {
+  double Lf[2][3][9];
+  double Ls[2][3];
+  double Lk[2][3];
+  double Ld[3][9];
+  double Lg0[3][9];
+  double ga[9], ge[9];
+  double A0, A1, A2;
+  double hc[3], h1[3];
+  double uw[3];
   int unk[3];
-  int pad;
 };
-using RingOp = RingOpT<double>;
+
+// The operator in the form the kernels apply it, one for the four sides.
+// With known populations k = (rest, t, -t, -n, -n + t, -n - t) of a node in
+// its own frame, the even combinations e = (k0, k1 + k2, k3, k4 + k5) and the
+// odd ones d = (k1 - k2, k4 - k5), the weighted sums over the unknown
+// populations are
+//   Y = sum_u w_u f_u              = Y[v].e + Ys[v] s + Yk[v] kappa T
+//   Z = sum over n + t, n - t      = Z[v].e + Zs[v] s + Zk[v] kappa T
+//   X = their difference           = X[v].d
+// and for the temperature Y = Dy.e, X = Dx.d (temperature node) or
+// kappa = (u_n ke.e - ka.e) / (A0 - 2 u_n A1 + u_n^2 A2),
+// Y = Gy.e - kappa (Hc - u_n H1), X = Gx.d (zero-flux node). Entries are
+// formed in double and rounded once to the kernels' arithmetic type.
+template <typename T>
+struct RingFillT {
+  T Y[2][4], Z[2][4], X[2][2];
+  T Ys[2], Zs[2], Yk[2], Zk[2];
+  T Dy[4], Dx[2], Gy[4], Gx[2];
+  T ka[4], ke[4];
+  T A0, A1, A2, Hc, H1;
+};
+// bytes of the workspace the operators of a D2Q9 context are given; what the
+// operators leave of it holds RING_ACC objective accumulators
+constexpr size_t RING_OPS_BYTES = 4 * 1264;
+constexpr int RING_ACC = int((RING_OPS_BYTES - 512) / sizeof(double));
+static_assert(sizeof(RingFillT<double>) <= 512, "operators leave room for the accumulators");
 
 // element-wise conversion of operator tables (host)
 template <typename D, typename S>
@@ -94,12 +115,13 @@ inline void conv_op(D (&d)[N], const S (&s)[N]) {
   for (size_t i = 0; i < N; ++i) conv_op(d[i], s[i]);
 }
 template <typename R>
-inline RingOpT<R> ring_op_as(const RingOp& s) {
-  RingOpT<R> d{};
-  conv_op(d.Lf, s.Lf); conv_op(d.Ls, s.Ls); conv_op(d.Lk, s.Lk); conv_op(d.Ld, s.Ld);
-  conv_op(d.Lg0, s.Lg0); conv_op(d.ga, s.ga); conv_op(d.ge, s.ge); conv_op(d.A0, s.A0);
-  conv_op(d.A1, s.A1); conv_op(d.A2, s.A2); conv_op(d.hc, s.hc); conv_op(d.h1, s.h1);
-  conv_op(d.uw, s.uw); conv_op(d.ucx, s.ucx); conv_op(d.ucy, s.ucy); conv_op(d.unk, s.unk);
+inline RingFillT<R> ring_fill_as(const RingFillT<double>& s) {
+  RingFillT<R> d{};
+  conv_op(d.Y, s.Y); conv_op(d.Z, s.Z); conv_op(d.X, s.X); conv_op(d.Ys, s.Ys);
+  conv_op(d.Zs, s.Zs); conv_op(d.Yk, s.Yk); conv_op(d.Zk, s.Zk); conv_op(d.Dy, s.Dy);
+  conv_op(d.Dx, s.Dx); conv_op(d.Gy, s.Gy); conv_op(d.Gx, s.Gx); conv_op(d.ka, s.ka);
+  conv_op(d.ke, s.ke); conv_op(d.A0, s.A0); conv_op(d.A1, s.A1); conv_op(d.A2, s.A2);
+  conv_op(d.Hc, s.Hc); conv_op(d.H1, s.H1);
   return d;
 }
 
@@ -158,7 +180,7 @@ struct AdjArgs {
   R* vx1;
   R* vy1;
   R* th1;
-  const RingOpT<R>* ops;  // 4 ring orientations: -x, +x, -y, +y
+  const RingFillT<R>* ops;  // boundary completion
   double* sens;  // dJ/dgamma (double)
   int sens_mode; // 0 none, 1 accumulate, 2 overwrite
   int exact;     // 1: exact discrete adjoint of the Brinkman step
@@ -216,8 +238,8 @@ __host__ __device__ inline R* level_field(const BatchStore<R>& s, LevelRef r, in
   return ping;
 }
 
-// host: the four ring operators for a given A and fluid B
-void build_ring_ops(double A, double Bf, RingOp ops[4]);
+// host: the ring completion for a given A and fluid B
+void build_ring_fill(double A, double Bf, RingFillT<double>& fill);
 
 // ---------------------------------------------------------------------------
 // D3Q19 (three-dimensional extension)

@@ -440,19 +440,11 @@ struct FwdLds {
   double red[8];  // one per wave, up to 512 threads
 };
 
-// Stage A1 at one node (i, j): the post-collision values f'_i (and g_i)
-// from the raw fields in LDS (pitch PR, position pr), stored at position pf
-// of the post-collision arrays f and gq (each direction SF values apart).
-template <typename R, bool TH, int PR, int SF, bool INT = false>
-__device__ inline void fwd_collide(const Geo& g, R A, const R* ld, const R* lu, const R* lv,
-                                   const R* lT, const R* lB, int pr, int i, int j, R* f, R* gq,
-                                   int pf) {
+// The nine post-collision values f'_i (and W of the temperature) of a node
+// from its state and the differences of its velocity and temperature.
+template <typename R>
+__device__ inline void fwd_post(R A, R d, R ux, R uy, R uxx, R uxy, R uyx, R uyy, R f[9]) {
 #pragma clang fp contract(on)
-  const R d = ld[pr], ux = lu[pr], uy = lv[pr];
-  const R uxx = lds_dx<INT>(lu, pr, 1, i, g.nx, g.periodic);
-  const R uxy = lds_dx<INT>(lu, pr, PR, j, g.ny, g.periodic);
-  const R uyx = lds_dx<INT>(lv, pr, 1, i, g.nx, g.periodic);
-  const R uyy = lds_dx<INT>(lv, pr, PR, j, g.ny, g.periodic);
   // f'_i = w_i [P + 3 c.u + cx^2 Xx + cy^2 Yy + cx cy Xy]
   const R P = d - R(1.5) * (ux * ux + uy * uy);
   const R Xx = R(4.5) * ux * ux + R(2) * A * uxx;
@@ -461,23 +453,41 @@ __device__ inline void fwd_collide(const Geo& g, R A, const R* ld, const R* lu, 
   const R u3x = R(3) * ux, u3y = R(3) * uy;
   const R w0 = R(4.0 / 9), w1 = R(1.0 / 9), w5 = R(1.0 / 36);
   const R diag = P + Xx + Yy;
-  f[0 * SF + pf] = w0 * P;
-  f[1 * SF + pf] = w1 * (P + u3x + Xx);
-  f[2 * SF + pf] = w1 * (P + u3y + Yy);
-  f[3 * SF + pf] = w1 * (P - u3x + Xx);
-  f[4 * SF + pf] = w1 * (P - u3y + Yy);
-  f[5 * SF + pf] = w5 * (diag + u3x + u3y + Xy);
-  f[6 * SF + pf] = w5 * (diag - u3x + u3y - Xy);
-  f[7 * SF + pf] = w5 * (diag - u3x - u3y + Xy);
-  f[8 * SF + pf] = w5 * (diag + u3x - u3y - Xy);
-  if constexpr (TH) {
-    const R T = lT[pr];
-    const R Bk = lB[pr];
-    const R Wx = R(3) * T * ux + Bk * lds_dx<INT>(lT, pr, 1, i, g.nx, g.periodic);
-    const R Wy = R(3) * T * uy + Bk * lds_dx<INT>(lT, pr, PR, j, g.ny, g.periodic);
-    gq[0 * SF + pf] = Wx;
-    gq[1 * SF + pf] = Wy;
-  }
+  f[0] = w0 * P;
+  f[1] = w1 * (P + u3x + Xx);
+  f[2] = w1 * (P + u3y + Yy);
+  f[3] = w1 * (P - u3x + Xx);
+  f[4] = w1 * (P - u3y + Yy);
+  f[5] = w5 * (diag + u3x + u3y + Xy);
+  f[6] = w5 * (diag - u3x + u3y - Xy);
+  f[7] = w5 * (diag - u3x - u3y + Xy);
+  f[8] = w5 * (diag + u3x - u3y - Xy);
+}
+template <typename R>
+__device__ inline void fwd_flux(R T, R B, R ux, R uy, R Tx, R Ty, R& Wx, R& Wy) {
+#pragma clang fp contract(on)
+  Wx = R(3) * T * ux + B * Tx;
+  Wy = R(3) * T * uy + B * Ty;
+}
+
+// Stage A1 at one node (i, j): the post-collision values f'_i (and g_i)
+// from the raw fields in LDS (pitch PR, position pr), stored at position pf
+// of the post-collision arrays f and gq (each direction SF values apart).
+template <typename R, bool TH, int PR, int SF, bool INT = false>
+__device__ inline void fwd_collide(const Geo& g, R A, const R* ld, const R* lu, const R* lv,
+                                   const R* lT, const R* lB, int pr, int i, int j, R* f, R* gq,
+                                   int pf) {
+  R fv[9];
+  const R ux = lu[pr], uy = lv[pr];
+  fwd_post(A, ld[pr], ux, uy, lds_dx<INT>(lu, pr, 1, i, g.nx, g.periodic),
+           lds_dx<INT>(lu, pr, PR, j, g.ny, g.periodic),
+           lds_dx<INT>(lv, pr, 1, i, g.nx, g.periodic),
+           lds_dx<INT>(lv, pr, PR, j, g.ny, g.periodic), fv);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) f[q * SF + pf] = fv[q];
+  if constexpr (TH)
+    fwd_flux(lT[pr], lB[pr], ux, uy, lds_dx<INT>(lT, pr, 1, i, g.nx, g.periodic),
+             lds_dx<INT>(lT, pr, PR, j, g.ny, g.periodic), gq[0 * SF + pf], gq[1 * SF + pf]);
 }
 
 // g_q = w_q [T + c_q.W] (eq:geq2) of the node whose temperature is T and
@@ -499,6 +509,71 @@ __device__ inline R g_eq(int q, R T, R Wx, R Wy) {
   }
 }
 
+// New state of an interior node from the pulled f'_i and g_i; s is its
+// 1 / (1 + alpha), src says whether b is the heat-source coefficient.
+template <typename R, bool TH>
+__device__ inline void fwd_interior(const Geo& g, const R f[9], const R gg[9], R s, bool src, R b,
+                                    R& dn, R& uxn, R& uyn, R& Tn) {
+#pragma clang fp contract(on)
+  dn = f[0] + f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8];
+  R Ux = f[1] - f[3] + f[5] - f[6] - f[7] + f[8];
+  R Uy = f[2] - f[4] + f[5] + f[6] - f[7] - f[8];
+  if constexpr (TH) {
+    Tn = gg[0] + gg[1] + gg[2] + gg[3] + gg[4] + gg[5] + gg[6] + gg[7] + gg[8];
+    // heat source Q = beta (1 - T) at the new level (eq:lbeg_ex,
+    // eq:heatsource): T (1 + beta) = T* + beta
+    if (src) Tn = (Tn + b) / (R(1) + b);
+    // Boussinesq force at the new level, u (1 + alpha) = U* + G
+    // (eq:lbef_ex, eq:boussinesqforce); zero when g beta is zero
+    const R dT = Tn - R(g.Tref);
+    Ux += R(g.gbx) * dT;
+    Uy += R(g.gby) * dT;
+  }
+  uxn = Ux * s;
+  uyn = Uy * s;
+}
+
+// New state of a ring node with outward normal (nx_, ny_) and class m from
+// the populations that arrive (those with c.n < 0 are not read): ubx, uby
+// the prescribed velocity, fac the level's inflow factor, Tb the prescribed
+// temperature or heat flux.
+template <typename R, bool TH>
+__device__ inline void fwd_ring(const Geo& g, const R f[9], const R gg[9], int nx_, int ny_, int m,
+                                R ubx, R uby, double fac, R Tb, R& dn, R& uxn, R& uyn, R& Tn) {
+#pragma clang fp contract(on)
+  R S0 = R(0), Sp = R(0), S0g = R(0), Spg = R(0);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const int cn = CX[q] * nx_ + CY[q] * ny_;
+    if (cn == 0) {
+      S0 += f[q];
+      if constexpr (TH) S0g += gg[q];
+    } else if (cn > 0) {
+      Sp += f[q];
+      if constexpr (TH) Spg += gg[q];
+    }
+  }
+  R un;
+  if ((m & 3) == FLOW_VELOCITY) {
+    uxn = R(double(ubx) * fac);
+    uyn = R(double(uby) * fac);
+    un = uxn * R(nx_) + uyn * R(ny_);
+    dn = S0 + R(2) * Sp - un;
+  } else {
+    const R dout = R(g.drho_out);
+    dn = dout;
+    un = S0 + R(2) * Sp - dout;
+    uxn = un * R(nx_);
+    uyn = un * R(ny_);
+  }
+  if constexpr (TH) {
+    // heat-flux node: -q.n = qbar with q = sum c_i g_i - u T (Sec. 2.4); Tb
+    // holds qbar there (0: adiabatic)
+    if (((m >> 2) & 3) == THERM_DIRICHLET) Tn = Tb;
+    else Tn = (S0g + R(2) * Spg + Tb) / (R(1) + un);
+  }
+}
+
 // Stage B at one node (i, j), not a corner: pull f'_i(x - c_i) from the
 // post-collision arrays (pitch PF, position pf) and form the new state;
 // ring nodes complete it from the moment balance. `level` is the new level
@@ -507,7 +582,6 @@ template <typename R, bool TH, int PF, int SF, int PR, bool INT = false>
 __device__ inline void fwd_pull(const Geo& g, const FwdArgs<R>& a, const R* lf, const R* lg,
                                 const R* lT, int pf, int pr, int i, int j, int k, int m, R s,
                                 int level, R& dn, R& uxn, R& uyn, R& Tn) {
-#pragma clang fp contract(on)
   const int fc = (INT || g.periodic) ? FLOW_INTERIOR : (m & 3);
   R f[9], gg[9];
 #pragma unroll
@@ -523,61 +597,15 @@ __device__ inline void fwd_pull(const Geo& g, const FwdArgs<R>& a, const R* lf, 
   }
   Tn = R(0);
   if (fc == FLOW_INTERIOR) {
-    dn = f[0] + f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8];
-    R Ux = f[1] - f[3] + f[5] - f[6] - f[7] + f[8];
-    R Uy = f[2] - f[4] + f[5] + f[6] - f[7] - f[8];
-    if constexpr (TH) {
-      Tn = gg[0] + gg[1] + gg[2] + gg[3] + gg[4] + gg[5] + gg[6] + gg[7] + gg[8];
-      // heat source Q = beta (1 - T) at the new level (eq:lbeg_ex,
-      // eq:heatsource): T (1 + beta) = T* + beta
-      if (a.beta) {
-        const R b = a.beta[k];
-        Tn = (Tn + b) / (R(1) + b);
-      }
-      // Boussinesq force at the new level, u (1 + alpha) = U* + G
-      // (eq:lbef_ex, eq:boussinesqforce); zero when g beta is zero
-      const R dT = Tn - R(g.Tref);
-      Ux += R(g.gbx) * dT;
-      Uy += R(g.gby) * dT;
-    }
-    uxn = Ux * s;
-    uyn = Uy * s;
+    fwd_interior<R, TH>(g, f, gg, s, TH && a.beta, TH && a.beta ? a.beta[k] : R(0), dn, uxn, uyn,
+                        Tn);
     return;
   }
   const int nx_ = (i == 0) ? -1 : (i == g.nx - 1 ? 1 : 0);
   const int ny_ = nx_ != 0 ? 0 : (j == 0 ? -1 : 1);
-  R S0 = R(0), Sp = R(0), S0g = R(0), Spg = R(0);
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const int cn = CX[q] * nx_ + CY[q] * ny_;
-    if (cn == 0) {
-      S0 += f[q];
-      if constexpr (TH) S0g += gg[q];
-    } else if (cn > 0) {
-      Sp += f[q];
-      if constexpr (TH) Spg += gg[q];
-    }
-  }
-  R un;
-  if (fc == FLOW_VELOCITY) {
-    const double fac = a.ufac[level];
-    uxn = R(double(a.ubx[k]) * fac);
-    uyn = R(double(a.uby[k]) * fac);
-    un = uxn * R(nx_) + uyn * R(ny_);
-    dn = S0 + R(2) * Sp - un;
-  } else {
-    const R dout = R(g.drho_out);
-    dn = dout;
-    un = S0 + R(2) * Sp - dout;
-    uxn = un * R(nx_);
-    uyn = un * R(ny_);
-  }
-  if constexpr (TH) {
-    // heat-flux node: -q.n = qbar with q = sum c_i g_i - u T (Sec. 2.4); Tb
-    // holds qbar there (0: adiabatic)
-    if (((m >> 2) & 3) == THERM_DIRICHLET) Tn = a.Tb[k];
-    else Tn = (S0g + R(2) * Spg + a.Tb[k]) / (R(1) + un);
-  }
+  const bool vel = fc == FLOW_VELOCITY;
+  fwd_ring<R, TH>(g, f, gg, nx_, ny_, m, vel ? a.ubx[k] : R(0), vel ? a.uby[k] : R(0),
+                  vel ? a.ufac[level] : 0.0, TH ? a.Tb[k] : R(0), dn, uxn, uyn, Tn);
 }
 
 // corners take density and temperature from their y-neighbour at the new
@@ -728,89 +756,81 @@ __global__ __launch_bounds__((NT1<R, TH, TY>)) void lks_step_kernel(Geo g, FwdAr
 // ---------------------------------------------------------------------------
 // ALKS step
 // ---------------------------------------------------------------------------
-// the completion of ring_moments with the operator op of orientation o and
-// flow type v (0 velocity, 1 pressure node)
-template <typename R, bool TH, typename OP>
-__device__ inline void ring_apply(OP op, int v, int o, const AdjArgs<R>& a, const R* sTn, int p2,
-                                  int k, int m, const R f[9], const R gq[9], R mom[9]) {
-  R kappa = R(0), gu[3] = {R(0), R(0), R(0)};
-  const int nx_ = o == 0 ? -1 : (o == 1 ? 1 : 0);
-  const int ny_ = o == 2 ? -1 : (o == 3 ? 1 : 0);
+// Least-squares completion of the adjoint populations at a ring node (see
+// RingFillT) and the raw moments rho~, U~, s~ (xx, xy, yy), T~, q~ of the
+// completed set. In the node's frame (outward normal n, tangent t) f holds
+// the known populations: rest, t, -t, -n, -n + t, -n - t. Bound by the length
+// of its chain (one wave of an edge tile runs it while the others wait): the
+// reflection t -> -t splits the fixed linear map of the known populations
+// into an even and an odd part, and the moments need only three sums over
+// the unknown ones, so the flow part takes 10 products instead of the 27 of
+// the full 3 x 9 map, and one operator serves the four sides.
+template <typename R, bool TH>
+__device__ inline void ring_fill(const AdjArgs<R>& a, int o, int m, R ux, R uy, R Tn,
+                                 const R f[6], const R gq[6], R mom[9]) {
+#pragma clang fp contract(on)
+  const R w0 = R(4.0 / 9), w1 = R(1.0 / 9), w5 = R(1.0 / 36);
+  const auto* op = as_scalar(a.ops);
+  const R sg = (o & 1) ? R(1) : R(-1);
+  const R un = sg * (o < 2 ? ux : uy);
+  const bool diri = ((m >> 2) & 3) == THERM_DIRICHLET;
+  R kappa = R(0), Tt = R(0), qn = R(0), qt = R(0);
   if constexpr (TH) {
-    if (((m >> 2) & 3) == THERM_DIRICHLET) {
-#pragma nounroll
-      for (int c = 0; c < 3; ++c) {
-        R t = R(0);
-#pragma unroll
-        for (int q = 0; q < 9; ++q) t += op->Ld[c][q] * gq[q];
-        gu[c] = t;
-      }
+    const R b1 = gq[1] + gq[2], b3 = gq[4] + gq[5], c1 = gq[1] - gq[2], c2 = gq[4] - gq[5];
+    const R q0 = w1 * gq[3] + w5 * b3;
+    R Y, X;
+    if (diri) {
+      Y = op->Dy[0] * gq[0] + op->Dy[1] * b1 + op->Dy[2] * gq[3] + op->Dy[3] * b3;
+      X = op->Dx[0] * c1 + op->Dx[1] * c2;
     } else {
-      const R un = a.ux[k] * R(nx_) + a.uy[k] * R(ny_);
       // zero-flux completion in Schur form (no row seed)
-      R num = R(0);
-#pragma unroll
-      for (int q = 0; q < 9; ++q) num += (op->ga[q] - un * op->ge[q]) * gq[q];
+      const R na = op->ka[0] * gq[0] + op->ka[1] * b1 + op->ka[2] * gq[3] + op->ka[3] * b3;
+      const R ne = op->ke[0] * gq[0] + op->ke[1] * b1 + op->ke[2] * gq[3] + op->ke[3] * b3;
       const R den = op->A0 - R(2) * un * op->A1 + un * un * op->A2;
-      kappa = -num / den;
-#pragma nounroll
-      for (int c = 0; c < 3; ++c) {
-        R t = R(0);
-#pragma unroll
-        for (int q = 0; q < 9; ++q) t += op->Lg0[c][q] * gq[q];
-        gu[c] = t - kappa * (op->hc[c] - un * op->h1[c]);
-      }
+      kappa = (un * ne - na) / den;
+      Y = op->Gy[0] * gq[0] + op->Gy[1] * b1 + op->Gy[2] * gq[3] + op->Gy[3] * b3;
+      Y = Y - kappa * (op->Hc - un * op->H1);
+      X = op->Gx[0] * c1 + op->Gx[1] * c2;
     }
+    Tt = w0 * gq[0] + w1 * b1 + q0 + Y;
+    qn = Y - q0;
+    qt = w1 * c1 + w5 * c2 + X;
   }
   // boundary seed of the pressure-drop objective: its derivative with
   // respect to the boundary pressure, the same in every row
   R s = R(0);
   if (m & TAG_J_INLET) s += R(a.seed_dp);
   if (m & TAG_J_OUTLET) s -= R(a.seed_dp);
-  const R kT = TH ? kappa * sTn[p2] : R(0);
-  R fu[3];
+  const R kT = TH ? kappa * Tn : R(0);
+  const R b1 = f[1] + f[2], b3 = f[4] + f[5], c1 = f[1] - f[2], c2 = f[4] - f[5];
+  // sums over the unknown populations: Y weighted, Z those with a tangential
+  // component, X their difference. A wave holds nodes of one type mostly;
+  // the operator of each type present is read through the scalar unit.
+  R Y = R(0), Z = R(0), X = R(0);
+  const int v = (m & 3) == FLOW_VELOCITY ? 0 : 1;
 #pragma nounroll
-  for (int c = 0; c < 3; ++c) {
-    R t = op->Ls[v][c] * s + op->Lk[v][c] * kT;
-#pragma unroll
-    for (int q = 0; q < 9; ++q) t += op->Lf[v][c][q] * f[q];
-    fu[c] = t;
+  for (int t = 0; t < 2; ++t) {
+    if (!__any(v == t)) continue;
+    const R y = op->Y[t][0] * f[0] + op->Y[t][1] * b1 + op->Y[t][2] * f[3] + op->Y[t][3] * b3 +
+                op->Ys[t] * s + op->Yk[t] * kT;
+    const R z = op->Z[t][0] * f[0] + op->Z[t][1] * b1 + op->Z[t][2] * f[3] + op->Z[t][3] * b3 +
+                op->Zs[t] * s + op->Zk[t] * kT;
+    const R x = op->X[t][0] * c1 + op->X[t][1] * c2;
+    Y = v == t ? y : Y;
+    Z = v == t ? z : Z;
+    X = v == t ? x : X;
   }
-  R r = R(0), Ux = R(0), Uy = R(0), sxx = R(0), sxy = R(0), syy = R(0);
-  R Tt = R(0), qx = R(0), qy = R(0);
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const R wf = R(WD[q]) * f[q];
-    r += wf;
-    if (CX[q]) Ux += R(CX[q]) * wf;
-    if (CY[q]) Uy += R(CY[q]) * wf;
-    if (CX[q]) sxx += wf;
-    if (CX[q] * CY[q]) sxy += R(CX[q] * CY[q]) * wf;
-    if (CY[q]) syy += wf;
-    if constexpr (TH) {
-      const R wg = R(WD[q]) * gq[q];
-      Tt += wg;
-      if (CX[q]) qx += R(CX[q]) * wg;
-      if (CY[q]) qy += R(CY[q]) * wg;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const R cx = op->ucx[c], cy = op->ucy[c];
-    const R wf = op->uw[c] * fu[c];
-    r += wf;
-    Ux += cx * wf;
-    Uy += cy * wf;
-    sxx += cx * cx * wf;
-    sxy += cx * cy * wf;
-    syy += cy * cy * wf;
-    if constexpr (TH) {
-      const R wg = op->uw[c] * gu[c];
-      Tt += wg;
-      qx += cx * wg;
-      qy += cy * wg;
-    }
-  }
+  const R in = w1 * f[3] + w5 * b3;
+  const R Un = Y - in, Ut = w1 * c1 + w5 * c2 + X;
+  const R snn = in + Y, stt = w1 * b1 + w5 * b3 + Z, snt = X - w5 * c2;
+  mom[0] = w0 * f[0] + w1 * b1 + in + Y;
+  const bool ax = o < 2;  // normal along x: n = (sg, 0), t = (0, sg); else n = (0, sg), t = (-sg, 0)
+  mom[1] = ax ? sg * Un : -sg * Ut;
+  mom[2] = ax ? sg * Ut : sg * Un;
+  mom[3] = ax ? snn : stt;
+  mom[4] = ax ? snt : -snt;
+  mom[5] = ax ? stt : snn;
+  R qx = ax ? sg * qn : -sg * qt, qy = ax ? sg * qt : sg * qn;
   if constexpr (TH) {
     // heat-sink objective: the heated node's temperature is the flux closure
     // T (1 + u.n) = S0 + 2 S+ + qbar of the arriving populations, so
@@ -818,58 +838,57 @@ __device__ inline void ring_apply(OP op, int v, int o, const AdjArgs<R>& a, cons
     // 0 inwards) leaves every completed adjoint population; its weighted
     // moments are -seed/(1 + u.n) on T~ and -seed/(1 + u.n) n/3 on q~
     if ((m & TAG_PROBE) && a.seed_bt != 0.0) {
-      const R sb = R(a.seed_bt) / (R(1) + a.ux[k] * R(nx_) + a.uy[k] * R(ny_));
+      const R sb = R(a.seed_bt) / (R(1) + un);
       Tt -= sb;
-      qx -= sb * R(nx_) / R(3);
-      qy -= sb * R(ny_) / R(3);
+      qx -= sb * (ax ? sg : R(0)) / R(3);
+      qy -= sb * (ax ? R(0) : sg) / R(3);
     }
     // exact mode: the temperature of a prescribed-temperature node does not
     // depend on the populations that arrive there, so their adjoint is zero
-    if (a.exact && ((m >> 2) & 3) == THERM_DIRICHLET) Tt = qx = qy = R(0);
+    if (a.exact && diri) Tt = qx = qy = R(0);
   }
-  mom[0] = r;
-  mom[1] = Ux;
-  mom[2] = Uy;
-  mom[3] = sxx;
-  mom[4] = sxy;
-  mom[5] = syy;
   mom[6] = Tt;
   mom[7] = qx;
   mom[8] = qy;
 }
 
-// Least-squares completion of the adjoint populations at a ring node (see
-// RingOp): the known populations f~_i = rho~ + c_i.V and g~_i = Theta at
-// x + c_i come from LDS (the unknown directions point outside the domain,
-// where LDS holds zeros); returns the raw moments rho~, U~, s~ (xx, xy, yy),
-// T~, q~ of the completed set.
+// lattice velocities of the known directions of ring_fill for orientation o
+__device__ inline void ring_dirs(int o, int cx[6], int cy[6]) {
+  const int sg = (o & 1) ? 1 : -1;
+  const int nx_ = o < 2 ? sg : 0, ny_ = o < 2 ? 0 : sg;
+  const int tx = -ny_, ty = nx_;
+  cx[0] = cy[0] = 0;
+  cx[1] = tx;
+  cy[1] = ty;
+  cx[2] = -tx;
+  cy[2] = -ty;
+  cx[3] = -nx_;
+  cy[3] = -ny_;
+  cx[4] = tx - nx_;
+  cy[4] = ty - ny_;
+  cx[5] = -tx - nx_;
+  cy[5] = -ty - ny_;
+}
+
+// ring_fill at node (i, j) with the known populations f~_i = rho~ + c_i.V
+// and g~_i = Theta at x + c_i read from the raw coefficients in LDS
 template <typename R, bool TH, int W2>
-__device__ void ring_moments(const Geo& g, const AdjArgs<R>& a, const R* sr, const R* svx,
-                             const R* svy, const R* sth, const R* sTn, int p2, int i, int j,
-                             int k, int m, R mom[9]) {
+__device__ inline void ring_moments(const Geo& g, const AdjArgs<R>& a, const R* sr, const R* svx,
+                                    const R* svy, const R* sth, const R* sTn, int p2, int i,
+                                    int j, int k, int m, R mom[9]) {
   const int o = (i == 0) ? 0 : (i == g.nx - 1 ? 1 : (j == 0 ? 2 : 3));
-  const int v = (m & 3) == FLOW_VELOCITY ? 0 : 1;
-  R f[9], gq[9];
+  int cx[6], cy[6];
+  ring_dirs(o, cx, cy);
+  R f[6], gq[6];
 #pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const int p = p2 + CX[q] + CY[q] * W2;
-    R e = sr[p];
-    if (CX[q] > 0) e += svx[p];
-    if (CX[q] < 0) e -= svx[p];
-    if (CY[q] > 0) e += svy[p];
-    if (CY[q] < 0) e -= svy[p];
-    f[q] = e;
-    if constexpr (TH) gq[q] = sth[p];
+  for (int d = 0; d < 6; ++d) {
+    const int p = p2 + cx[d] + cy[d] * W2;
+    const R e = sr[p] + R(cx[d]) * svx[p];
+    f[d] = e + R(cy[d]) * svy[p];
+    gq[d] = TH ? sth[p] : R(0);
   }
-  // a wave whose lanes share orientation and node type reads the operator
-  // through the scalar unit; mixed waves read it per lane
-  const int key = 2 * o + v;
-  const int uk = __builtin_amdgcn_readfirstlane(key);
-  if (__all(key == uk))
-    ring_apply<R, TH>(as_scalar(a.ops) + (uk >> 1), uk & 1, uk >> 1, a, sTn, p2, k, m, f, gq,
-                      mom);
-  else
-    ring_apply<R, TH>(a.ops + o, v, o, a, sTn, p2, k, m, f, gq, mom);
+  const R ux = TH ? a.ux[k] : R(0), uy = TH ? a.uy[k] : R(0);
+  ring_fill<R, TH>(a, o, m, ux, uy, TH ? sTn[p2] : R(0), f, gq, mom);
 }
 
 // One ALKS step, adjoint level n+1 -> n. The adjoint state is kept as the
@@ -898,48 +917,50 @@ struct AdjLds {
   R m[NM][TL::W1 * TL::H1];
 };
 
-// Stage A1 at an interior node: weighted pull of the level-n+1 equilibria
+// Moments rho~, U~, s~ (xx, xy, yy), T~, q~ of the pulled values f~_q, g~_q
+// of an interior node, summed by weight class.
+template <typename R, bool TH>
+__device__ inline void adj_mom(const R E[9], const R G[9], R mom[9]) {
+#pragma clang fp contract(on)
+  const R w0 = R(4.0 / 9), w1 = R(1.0 / 9), w5 = R(1.0 / 36);
+  const R sa = E[1] + E[3], sb = E[2] + E[4];
+  const R p = E[5] + E[7], q = E[6] + E[8], pm = E[5] - E[7], qm = E[8] - E[6];
+  const R ps = p + q;
+  mom[0] = w0 * E[0] + w1 * (sa + sb) + w5 * ps;
+  mom[1] = w1 * (E[1] - E[3]) + w5 * (pm + qm);
+  mom[2] = w1 * (E[2] - E[4]) + w5 * (pm - qm);
+  mom[3] = w1 * sa + w5 * ps;
+  mom[4] = w5 * (p - q);
+  mom[5] = w1 * sb + w5 * ps;
+  mom[6] = mom[7] = mom[8] = R(0);
+  if constexpr (TH) {
+    const R gm = G[5] - G[7], hm = G[8] - G[6];
+    const R gs = (G[5] + G[7]) + (G[6] + G[8]);
+    mom[6] = w0 * G[0] + w1 * ((G[1] + G[3]) + (G[2] + G[4])) + w5 * gs;
+    mom[7] = w1 * (G[1] - G[3]) + w5 * (gm + hm);
+    mom[8] = w1 * (G[2] - G[4]) + w5 * (gm - hm);
+  }
+}
+
+// Stage A1 at an interior node: pull of the level-n+1 equilibria
 // f~_i^eq = rho~ + c_i.V and g~_i^eq = Theta from x + c_i (raw coefficients
-// in LDS, pitch PR, position pr); returns the moments rho~, U~, s~ (xx, xy,
-// yy), T~, q~.
+// in LDS, pitch PR, position pr) and their moments.
 template <typename R, bool TH, int PR>
 __device__ inline void adj_pull(const R* lr, const R* lvx, const R* lvy, const R* lth, int pr,
                                 R mom[9]) {
-  R r = R(0), Ux = R(0), Uy = R(0), sxx = R(0), sxy = R(0), syy = R(0);
-  R Tt = R(0), qx = R(0), qy = R(0);
+  R E[9], G[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) {
     const int p = pr + CX[q] + CY[q] * PR;
-    // rho~ + c_i.V with the zero components left out (a product with a
-    // constant 0 is not folded away under IEEE rules)
-    R E = lr[p];
-    if (CX[q] > 0) E += lvx[p];
-    if (CX[q] < 0) E -= lvx[p];
-    if (CY[q] > 0) E += lvy[p];
-    if (CY[q] < 0) E -= lvy[p];
-    const R wE = R(WD[q]) * E;
-    r += wE;
-    if (CX[q]) Ux += R(CX[q]) * wE;
-    if (CY[q]) Uy += R(CY[q]) * wE;
-    if (CX[q]) sxx += wE;
-    if (CX[q] * CY[q]) sxy += R(CX[q] * CY[q]) * wE;
-    if (CY[q]) syy += wE;
-    if constexpr (TH) {
-      const R wT = R(WD[q]) * lth[p];
-      Tt += wT;
-      if (CX[q]) qx += R(CX[q]) * wT;
-      if (CY[q]) qy += R(CY[q]) * wT;
-    }
+    R e = lr[p];
+    if (CX[q] > 0) e += lvx[p];
+    if (CX[q] < 0) e -= lvx[p];
+    if (CY[q] > 0) e += lvy[p];
+    if (CY[q] < 0) e -= lvy[p];
+    E[q] = e;
+    G[q] = TH ? lth[p] : R(0);
   }
-  mom[0] = r;
-  mom[1] = Ux;
-  mom[2] = Uy;
-  mom[3] = sxx;
-  mom[4] = sxy;
-  mom[5] = syy;
-  mom[6] = Tt;
-  mom[7] = qx;
-  mom[8] = qy;
+  adj_mom<R, TH>(E, G, mom);
 }
 
 // Stage A1 at node (i, j) of the raw region: the moments of the pulled and,
@@ -980,109 +1001,159 @@ __device__ inline void adj_corners(const Geo& g, R* lm, int rx0, int ry0, int rw
   for (int f = 0; f < NM; ++f) lm[f * SM + pm] = lm[f * SM + pn];
 }
 
-// Stage B at node (i, j): the local terms of eq:albef_ex / eq:albeg_ex at
-// level n (seeds, 3 T q~ coupling, implicit Brinkman), then V and Theta of
-// the new level from the moments (pitch PM, position pm) and, when want_sens
-// is set, the sensitivity integrand 3 alpha' u.u~ - B' grad T . q~.
+// What the local terms of a node need beside its moments: 1 / (1 + alpha),
+// the velocity, and (thermal) T, u_x and the probe tag of the node whose
+// moments were taken (the y-neighbour for corners), B with its differences
+// (paper mode) and the heat-source coefficient.
+template <typename R>
+struct AdjNode {
+  R s, ux, uy;
+  R Tl, uxl, B, dBx, dBy, beta;
+  int ring, probe;
+};
+
+// The local terms of eq:albef_ex / eq:albeg_ex at level n (seeds, 3 T q~
+// coupling, implicit Brinkman), then V and Theta of the new level from the
+// node's moments, div s~ = (dsx, dsy) and dq = div q~ (paper) or div (B q~)
+// (exact). pair is the Brinkman pairing of the sensitivity, adj_T the T~ or
+// Theta that pairs with the heat source. Accessors dq() and the like are
+// only called where the term exists.
+template <typename R, bool TH>
+__device__ inline void adj_node(const Geo& g, const AdjArgs<R>& a, const AdjNode<R>& n,
+                                const R mom[9], R dsx, R dsy, R dq, R& r_out, R& Vx, R& Vy, R& Th,
+                                double& pair, double& adj_T) {
+#pragma clang fp contract(on)
+  const R A2 = R(2.0 * g.A);
+  const R r = mom[0], sxx = mom[3], sxy = mom[4], syy = mom[5];
+  R Ux = mom[1], Uy = mom[2], Tt = R(0), qx = R(0), qy = R(0);
+  if constexpr (TH) {
+    Tt = mom[6];
+    qx = mom[7];
+    qy = mom[8];
+    Ux += n.Tl * qx;
+    Uy += n.Tl * qy;
+    if (n.probe && a.seed_heat != 0.0) {
+      Ux -= R(a.seed_heat / 3.0) * n.Tl;
+      Tt -= R(a.seed_heat) * n.uxl;
+    }
+  }
+  // paper: u~ = U~ / (1 + alpha) here; exact: V is divided by 1 + alpha
+  // instead, after it is formed from the undivided u~
+  const R su = a.exact ? R(1) : n.s;
+  const R utx = Ux * su, uty = Uy * su;
+  if constexpr (TH) {
+    // paper: the Boussinesq coupling of eq:albeg_ex, 3 g beta . u~ on T~ at
+    // interior nodes (zero when g beta is zero)
+    if (!n.ring && !a.exact) Tt += R(3) * (R(g.gbx) * utx + R(g.gby) * uty);
+    // heat source (interior nodes; beta = 0 on the ring): the heat-exchange
+    // seed dJ/dg_i = seed_src beta, and in paper mode the implicit
+    // T~ (1 + beta) of eq:albeg_ex
+    if (a.beta && !n.ring) {
+      Tt -= R(a.seed_src) * n.beta;
+      if (!a.exact) Tt /= R(1) + n.beta;
+    }
+  }
+  r_out = r;
+  const R sux = sxx * n.ux + sxy * n.uy, suy = sxy * n.ux + syy * n.uy;
+  Vx = R(3) * utx + R(9) * sux - R(3) * r * n.ux - A2 * dsx;
+  Vy = R(3) * uty + R(9) * suy - R(3) * r * n.uy - A2 * dsy;
+  // the Brinkman pairing of the sensitivity: 3 alpha' u.u~ (paper) or
+  // alpha' u.V / (1 + alpha) with the undivided V (exact)
+  pair = a.exact ? double(n.s) / 3.0 * (double(n.ux) * double(Vx) + double(n.uy) * double(Vy))
+                 : double(n.ux) * double(utx) + double(n.uy) * double(uty);
+  if (a.exact) {
+    Vx *= n.s;
+    Vy *= n.s;
+  }
+  adj_T = 0.0;
+  if constexpr (TH) {
+    const R qu = qx * n.ux + qy * n.uy;
+    if (a.exact) {
+      // exact: the transpose of the forward B c.grad_h T, -div_h (B q~)
+      Th = Tt + R(3) * qu - dq;
+      // the propagated Theta carries the force's dependence on the new
+      // temperature, g beta . V / (1 + alpha), at interior nodes, and the
+      // division by 1 + beta acts on it
+      if (!n.ring) Th += R(g.gbx) * Vx + R(g.gby) * Vy;
+      if (a.beta && !n.ring) Th /= R(1) + n.beta;
+    } else {
+      const R bq = n.dBx * qx + n.dBy * qy;
+      Th = Tt + R(3) * qu - n.B * dq - bq;
+    }
+    adj_T = double(a.exact ? Th : Tt);
+  }
+}
+
+// the sensitivity integrand 3 alpha' u.u~ - B' grad T . q~ of an interior
+// node, with the heat source's beta' (T - 1)(w_J + T~) (the propagated Theta
+// in exact mode). Exact mode at level 0 keeps only the conductivity term:
+// alpha and beta act on the levels the steps produce, B on the equilibria used
+template <typename R, bool TH>
+__device__ inline double adj_sens(const AdjArgs<R>& a, double pair, double adj_T, R dA3, R dB,
+                                  R dbeta, R T, R dTx, R dTy, R qx, R qy) {
+#pragma clang fp contract(on)
+  double v = a.sens_b_only ? 0.0 : double(dA3) * pair;
+  if constexpr (TH) {
+    const double tq = double(dTx) * double(qx) + double(dTy) * double(qy);
+    v -= double(dB) * tq;
+    if (a.beta && !a.sens_b_only) v += double(dbeta) * (double(T) - 1.0) * (a.seed_src + adj_T);
+  }
+  return v;
+}
+
+// Stage B at node (i, j): adj_node on the moments in LDS (pitch PM, position
+// pm) and, when want_sens is set, the sensitivity integrand.
 template <typename R, bool TH, int PR, int PM, int SM, bool INT = false>
 __device__ inline void adj_local(const Geo& g, const AdjArgs<R>& a, const R* lm, int pm,
                                  const R* lTn, const R* lB, int pr, int i, int j, int k, R s,
                                  R ux, R uy, R& r_out, R& Vx, R& Vy, R& Th, bool want_sens,
                                  double& sens) {
-  const R A2 = R(2.0 * g.A);
   const bool ring = !INT && !g.periodic && (i == 0 || j == 0 || i == g.nx - 1 || j == g.ny - 1);
   const bool corner = ring && (i == 0 || i == g.nx - 1) && (j == 0 || j == g.ny - 1);
   // local terms are those of the node whose moments were taken
   const int kl = corner ? (j == 0 ? g.nx + i : (g.ny - 2) * g.nx + i) : k;
   const int pl = corner ? pr + (j == 0 ? PR : -PR) : pr;
-  const R r = lm[0 * SM + pm];
-  R Ux = lm[1 * SM + pm], Uy = lm[2 * SM + pm];
-  const R sxx = lm[3 * SM + pm], sxy = lm[4 * SM + pm], syy = lm[5 * SM + pm];
-  R Tt = R(0), qx = R(0), qy = R(0);
-  if constexpr (TH) {
-    Tt = lm[6 * SM + pm];
-    qx = lm[7 * SM + pm];
-    qy = lm[8 * SM + pm];
-    const R Tl = lTn[pl];
-    Ux += Tl * qx;
-    Uy += Tl * qy;
-    if (a.seed_heat != 0.0 && (a.mask[kl] & TAG_PROBE)) {
-      Ux -= R(a.seed_heat / 3.0) * Tl;
-      Tt -= R(a.seed_heat) * a.ux[kl];
-    }
-  }
-  // paper: u~ = U~ / (1 + alpha) here; exact: V is divided by 1 + alpha
-  // instead, after it is formed from the undivided u~
-  const R su = a.exact ? R(1) : s;
-  const R utx = Ux * su, uty = Uy * su;
-  // paper: the Boussinesq coupling of eq:albeg_ex, 3 g beta . u~ on T~ at
-  // interior nodes (zero when g beta is zero)
-  if constexpr (TH)
-    if (!ring && !a.exact) Tt += R(3) * (R(g.gbx) * utx + R(g.gby) * uty);
-  // heat source (interior nodes; beta = 0 on the ring): the heat-exchange
-  // seed dJ/dg_i = seed_src beta, and in paper mode the implicit
-  // T~ (1 + beta) of eq:albeg_ex
-  R bsrc = R(0);
-  if constexpr (TH) {
-    if (a.beta && !ring) {
-      bsrc = a.beta[k];
-      Tt -= R(a.seed_src) * bsrc;
-      if (!a.exact) Tt /= R(1) + bsrc;
-    }
-  }
+  constexpr int NM = TH ? 9 : 6;
+  R mom[9];
+#pragma unroll
+  for (int f = 0; f < NM; ++f) mom[f] = lm[f * SM + pm];
   auto ldx = [&](int f) { return lds_dx<INT>(lm + f * SM, pm, 1, i, g.nx, g.periodic); };
   auto ldy = [&](int f) { return lds_dx<INT>(lm + f * SM, pm, PM, j, g.ny, g.periodic); };
-  const R dsx = ldx(3) + ldy(4);
-  const R dsy = ldx(4) + ldy(5);
-  r_out = r;
-  Vx = R(3) * utx + R(9) * (sxx * ux + sxy * uy) - R(3) * r * ux - A2 * dsx;
-  Vy = R(3) * uty + R(9) * (sxy * ux + syy * uy) - R(3) * r * uy - A2 * dsy;
-  // the Brinkman pairing of the sensitivity: 3 alpha' u.u~ (paper) or
-  // alpha' u.V / (1 + alpha) with the undivided V (exact)
-  const double pair = a.exact ? double(s) / 3.0 * (double(ux) * double(Vx) + double(uy) * double(Vy))
-                              : double(ux) * double(utx) + double(uy) * double(uty);
-  if (a.exact) {
-    Vx *= s;
-    Vy *= s;
-  }
+  AdjNode<R> n;
+  n.s = s;
+  n.ux = ux;
+  n.uy = uy;
+  n.ring = ring;
+  R dq = R(0);
   if constexpr (TH) {
+    n.Tl = lTn[pl];
+    n.probe = a.seed_heat != 0.0 && (a.mask[kl] & TAG_PROBE);
+    n.uxl = n.probe ? a.ux[kl] : R(0);
+    n.beta = a.beta && !ring ? a.beta[k] : R(0);
     if (a.exact) {
-      // exact: the transpose of the forward B c.grad_h T, -div_h (B q~)
-      const R dbx = lds_dxp<INT>(lB, pr, 1, lm + 7 * SM, pm, 1, i, g.nx, g.periodic);
-      const R dby = lds_dxp<INT>(lB, pr, PR, lm + 8 * SM, pm, PM, j, g.ny, g.periodic);
-      Th = Tt + R(3) * (qx * ux + qy * uy) - (dbx + dby);
+      dq = lds_dxp<INT>(lB, pr, 1, lm + 7 * SM, pm, 1, i, g.nx, g.periodic) +
+           lds_dxp<INT>(lB, pr, PR, lm + 8 * SM, pm, PM, j, g.ny, g.periodic);
+      n.B = n.dBx = n.dBy = R(0);
     } else {
-      const R divq = ldx(7) + ldy(8);
-      const R Bk = lB[pr];
-      const R dBx = lds_dx<INT>(lB, pr, 1, i, g.nx, g.periodic);
-      const R dBy = lds_dx<INT>(lB, pr, PR, j, g.ny, g.periodic);
-      Th = Tt + R(3) * (qx * ux + qy * uy) - Bk * divq - (dBx * qx + dBy * qy);
+      dq = ldx(7) + ldy(8);
+      n.B = lB[pr];
+      n.dBx = lds_dx<INT>(lB, pr, 1, i, g.nx, g.periodic);
+      n.dBy = lds_dx<INT>(lB, pr, PR, j, g.ny, g.periodic);
     }
-    // exact: the propagated Theta carries the force's dependence on the new
-    // temperature, g beta . V / (1 + alpha), at interior nodes
-    if (!ring && a.exact) Th += R(g.gbx) * Vx + R(g.gby) * Vy;
-    // exact: the division by 1 + beta acts on the propagated Theta
-    if (a.exact && a.beta) Th /= R(1) + bsrc;
   }
+  double pair, adj_T;
+  adj_node<R, TH>(g, a, n, mom, ldx(3) + ldy(4), ldx(4) + ldy(5), dq, r_out, Vx, Vy, Th, pair,
+                  adj_T);
   sens = 0.0;
-  if (want_sens) {
-    double v = 0.0;
-    if (!ring) {
-      // exact mode at level 0 keeps only the conductivity term: alpha and
-      // beta act on the levels the steps produce, B on the equilibria used
-      v = a.sens_b_only ? 0.0 : double(a.dA3[k]) * pair;
-      if constexpr (TH) {
-        const double dTx = double(lds_dx<INT>(lTn, pr, 1, i, g.nx, g.periodic));
-        const double dTy = double(lds_dx<INT>(lTn, pr, PR, j, g.ny, g.periodic));
-        v -= double(a.dB[k]) * (dTx * double(qx) + dTy * double(qy));
-        // heat source and heat-exchange objective: beta' (T - 1)(w_J + T~),
-        // with the propagated Theta in exact mode
-        if (a.beta && !a.sens_b_only)
-          v += double(a.dbeta[k]) * (double(lTn[pr]) - 1.0) *
-               (a.seed_src + double(a.exact ? Th : Tt));
-      }
+  if (want_sens && !ring) {
+    R dTx = R(0), dTy = R(0);
+    if constexpr (TH) {
+      dTx = lds_dx<INT>(lTn, pr, 1, i, g.nx, g.periodic);
+      dTy = lds_dx<INT>(lTn, pr, PR, j, g.ny, g.periodic);
     }
-    sens = v;
+    sens = adj_sens<R, TH>(a, pair, adj_T, a.dA3[k], TH ? a.dB[k] : R(0),
+                           TH && a.beta ? a.dbeta[k] : R(0), TH ? lTn[pr] : R(0), dTx, dTy,
+                           TH ? mom[TH ? 7 : 0] : R(0), TH ? mom[TH ? 8 : 0] : R(0));
   }
 }
 

@@ -83,140 +83,180 @@ void pseudo_inverse(int rows, int n, const double* K, double* P) {
 
 }  // namespace
 
-void build_ring_ops(double A, double Bf, RingOp ops[4]) {
-  const int NRM[4][2] = {{-1, 0}, {1, 0}, {0, -1}, {0, 1}};
-  for (int o = 0; o < 4; ++o) {
-    RingOp& op = ops[o];
-    std::memset(&op, 0, sizeof op);
-    const int nx = NRM[o][0], ny = NRM[o][1];
-    const int tx = -ny, ty = nx;
-    int cn[9], nu = 0;
-    for (int q = 0; q < 9; ++q) {
-      cn[q] = HX[q] * nx + HY[q] * ny;
-      if (cn[q] > 0) op.unk[nu++] = q;
+namespace {
+// the operator of a node with outward normal +x
+void build_ring_op(double A, double Bf, RingOp& op) {
+  std::memset(&op, 0, sizeof op);
+  const int nx = 1, ny = 0;
+  const int tx = -ny, ty = nx;
+  int cn[9], nu = 0;
+  for (int q = 0; q < 9; ++q) {
+    cn[q] = HX[q] * nx + HY[q] * ny;
+    if (cn[q] > 0) op.unk[nu++] = q;
+  }
+  for (int a = 0; a < 3; ++a) op.uw[a] = HW[op.unk[a]];
+  // flow rows: coefficient of f~_q in row r
+  double M[9][9];
+  for (int r = 0; r < 9; ++r)
+    for (int q = 0; q < 9; ++q)
+      M[r][q] = (r == q ? cn[r] : 0.0) -
+                2.0 * A * HW[q] * cn[q] * double(HX[q] * HX[r] + HY[q] * HY[r]);
+  for (int v = 0; v < 2; ++v) {
+    double K[9 * 5], P[5 * 9];
+    for (int r = 0; r < 9; ++r) {
+      for (int a = 0; a < 3; ++a) K[r * 5 + a] = M[r][op.unk[a]];
+      K[r * 5 + 3] = v == 0 ? double(HX[r]) : 1.0;
+      K[r * 5 + 4] = v == 0 ? double(HY[r]) : double(HX[r] * tx + HY[r] * ty);
     }
+    pseudo_inverse(9, 5, K, P);
     for (int a = 0; a < 3; ++a) {
-      op.uw[a] = HW[op.unk[a]];
-      op.ucx[a] = HX[op.unk[a]];
-      op.ucy[a] = HY[op.unk[a]];
-    }
-    // flow rows: coefficient of f~_q in row r
-    double M[9][9];
-    for (int r = 0; r < 9; ++r)
-      for (int q = 0; q < 9; ++q)
-        M[r][q] = (r == q ? cn[r] : 0.0) -
-                  2.0 * A * HW[q] * cn[q] * double(HX[q] * HX[r] + HY[q] * HY[r]);
-    for (int v = 0; v < 2; ++v) {
-      double K[9 * 5], P[5 * 9];
+      double s = 0, k = 0;
       for (int r = 0; r < 9; ++r) {
-        for (int a = 0; a < 3; ++a) K[r * 5 + a] = M[r][op.unk[a]];
-        K[r * 5 + 3] = v == 0 ? double(HX[r]) : 1.0;
-        K[r * 5 + 4] = v == 0 ? double(HY[r]) : double(HX[r] * tx + HY[r] * ty);
+        s += P[a * 9 + r];
+        k += P[a * 9 + r] * cn[r];
       }
-      pseudo_inverse(9, 5, K, P);
-      for (int a = 0; a < 3; ++a) {
-        double s = 0, k = 0;
-        for (int r = 0; r < 9; ++r) {
-          s += P[a * 9 + r];
-          k += P[a * 9 + r] * cn[r];
-        }
-        op.Ls[v][a] = -s;
-        op.Lk[v][a] = k;
-        for (int q = 0; q < 9; ++q) {
-          double t = 0;
-          if (cn[q] <= 0)
-            for (int r = 0; r < 9; ++r) t += P[a * 9 + r] * M[r][q];
-          op.Lf[v][a][q] = -t;
-        }
-      }
-    }
-    // thermal rows: coefficient of g~_q in row r
-    double Mg[9][9];
-    for (int r = 0; r < 9; ++r)
-      for (int q = 0; q < 9; ++q) Mg[r][q] = (r == q ? cn[r] : 0.0) - Bf * HW[q] * cn[q];
-    {
-      double K[9 * 4], P[4 * 9];
-      for (int r = 0; r < 9; ++r) {
-        for (int a = 0; a < 3; ++a) K[r * 4 + a] = Mg[r][op.unk[a]];
-        K[r * 4 + 3] = 1.0;
-      }
-      pseudo_inverse(9, 4, K, P);
-      for (int a = 0; a < 3; ++a)
-        for (int q = 0; q < 9; ++q) {
-          double t = 0;
-          if (cn[q] <= 0)
-            for (int r = 0; r < 9; ++r) t += P[a * 9 + r] * Mg[r][q];
-          op.Ld[a][q] = -t;
-        }
-    }
-    {
-      double K0[9 * 3], G[9], H[9];
-      for (int r = 0; r < 9; ++r)
-        for (int a = 0; a < 3; ++a) K0[r * 3 + a] = Mg[r][op.unk[a]];
-      for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-          double s = 0;
-          for (int r = 0; r < 9; ++r) s += K0[r * 3 + a] * K0[r * 3 + b];
-          G[a * 3 + b] = s;
-        }
-      invert(3, G, H);
-      // HK = H K0^T (3 x 9); Q = I - K0 HK (9 x 9)
-      double HK[3 * 9], Q[9][9];
-      for (int a = 0; a < 3; ++a)
-        for (int r = 0; r < 9; ++r) {
-          double s = 0;
-          for (int b = 0; b < 3; ++b) s += H[a * 3 + b] * K0[r * 3 + b];
-          HK[a * 9 + r] = s;
-        }
-      for (int r = 0; r < 9; ++r)
-        for (int c = 0; c < 9; ++c) {
-          double s = 0;
-          for (int a = 0; a < 3; ++a) s += K0[r * 3 + a] * HK[a * 9 + c];
-          Q[r][c] = (r == c ? 1.0 : 0.0) - s;
-        }
-      double Qcn[9], Q1[9];
-      for (int r = 0; r < 9; ++r) {
-        double s = 0, t = 0;
-        for (int c = 0; c < 9; ++c) {
-          s += Q[r][c] * cn[c];
-          t += Q[r][c];
-        }
-        Qcn[r] = s;
-        Q1[r] = t;
-      }
-      op.A0 = op.A1 = op.A2 = 0;
-      for (int r = 0; r < 9; ++r) {
-        op.A0 += cn[r] * Qcn[r];
-        op.A1 += cn[r] * Q1[r];
-        op.A2 += Q1[r];
-      }
+      op.Ls[v][a] = -s;
+      op.Lk[v][a] = k;
       for (int q = 0; q < 9; ++q) {
-        double ga = 0, ge = 0;
+        double t = 0;
         if (cn[q] <= 0)
-          for (int r = 0; r < 9; ++r) {
-            ga += Qcn[r] * Mg[r][q];
-            ge += Q1[r] * Mg[r][q];
-          }
-        op.ga[q] = ga;
-        op.ge[q] = ge;
-      }
-      for (int a = 0; a < 3; ++a) {
-        double hc = 0, h1 = 0;
-        for (int r = 0; r < 9; ++r) {
-          hc += HK[a * 9 + r] * cn[r];
-          h1 += HK[a * 9 + r];
-        }
-        op.hc[a] = hc;
-        op.h1[a] = h1;
-        for (int q = 0; q < 9; ++q) {
-          double t = 0;
-          if (cn[q] <= 0)
-            for (int r = 0; r < 9; ++r) t += HK[a * 9 + r] * Mg[r][q];
-          op.Lg0[a][q] = -t;
-        }
+          for (int r = 0; r < 9; ++r) t += P[a * 9 + r] * M[r][q];
+        op.Lf[v][a][q] = -t;
       }
     }
   }
+  // thermal rows: coefficient of g~_q in row r
+  double Mg[9][9];
+  for (int r = 0; r < 9; ++r)
+    for (int q = 0; q < 9; ++q) Mg[r][q] = (r == q ? cn[r] : 0.0) - Bf * HW[q] * cn[q];
+  {
+    double K[9 * 4], P[4 * 9];
+    for (int r = 0; r < 9; ++r) {
+      for (int a = 0; a < 3; ++a) K[r * 4 + a] = Mg[r][op.unk[a]];
+      K[r * 4 + 3] = 1.0;
+    }
+    pseudo_inverse(9, 4, K, P);
+    for (int a = 0; a < 3; ++a)
+      for (int q = 0; q < 9; ++q) {
+        double t = 0;
+        if (cn[q] <= 0)
+          for (int r = 0; r < 9; ++r) t += P[a * 9 + r] * Mg[r][q];
+        op.Ld[a][q] = -t;
+      }
+  }
+  {
+    double K0[9 * 3], G[9], H[9];
+    for (int r = 0; r < 9; ++r)
+      for (int a = 0; a < 3; ++a) K0[r * 3 + a] = Mg[r][op.unk[a]];
+    for (int a = 0; a < 3; ++a)
+      for (int b = 0; b < 3; ++b) {
+        double s = 0;
+        for (int r = 0; r < 9; ++r) s += K0[r * 3 + a] * K0[r * 3 + b];
+        G[a * 3 + b] = s;
+      }
+    invert(3, G, H);
+    // HK = H K0^T (3 x 9); Q = I - K0 HK (9 x 9)
+    double HK[3 * 9], Q[9][9];
+    for (int a = 0; a < 3; ++a)
+      for (int r = 0; r < 9; ++r) {
+        double s = 0;
+        for (int b = 0; b < 3; ++b) s += H[a * 3 + b] * K0[r * 3 + b];
+        HK[a * 9 + r] = s;
+      }
+    for (int r = 0; r < 9; ++r)
+      for (int c = 0; c < 9; ++c) {
+        double s = 0;
+        for (int a = 0; a < 3; ++a) s += K0[r * 3 + a] * HK[a * 9 + c];
+        Q[r][c] = (r == c ? 1.0 : 0.0) - s;
+      }
+    double Qcn[9], Q1[9];
+    for (int r = 0; r < 9; ++r) {
+      double s = 0, t = 0;
+      for (int c = 0; c < 9; ++c) {
+        s += Q[r][c] * cn[c];
+        t += Q[r][c];
+      }
+      Qcn[r] = s;
+      Q1[r] = t;
+    }
+    op.A0 = op.A1 = op.A2 = 0;
+    for (int r = 0; r < 9; ++r) {
+      op.A0 += cn[r] * Qcn[r];
+      op.A1 += cn[r] * Q1[r];
+      op.A2 += Q1[r];
+    }
+    for (int q = 0; q < 9; ++q) {
+      double ga = 0, ge = 0;
+      if (cn[q] <= 0)
+        for (int r = 0; r < 9; ++r) {
+          ga += Qcn[r] * Mg[r][q];
+          ge += Q1[r] * Mg[r][q];
+        }
+      op.ga[q] = ga;
+      op.ge[q] = ge;
+    }
+    for (int a = 0; a < 3; ++a) {
+      double hc = 0, h1 = 0;
+      for (int r = 0; r < 9; ++r) {
+        hc += HK[a * 9 + r] * cn[r];
+        h1 += HK[a * 9 + r];
+      }
+      op.hc[a] = hc;
+      op.h1[a] = h1;
+      for (int q = 0; q < 9; ++q) {
+        double t = 0;
+        if (cn[q] <= 0)
+          for (int r = 0; r < 9; ++r) t += HK[a * 9 + r] * Mg[r][q];
+        op.Lg0[a][q] = -t;
+      }
+    }
+  }
+}
+}  // namespace
+
+// Reflection t -> -t of the +x operator: unknown directions in ascending order
+// are n, n + t, n - t (1, 5, 8); the known ones rest, t, -t, -n, -n + t,
+// -n - t are 0, 2, 4, 3, 6, 7. Entries equal by symmetry are averaged.
+void build_ring_fill(double A, double Bf, RingFillT<double>& F) {
+  RingOp op;
+  build_ring_op(A, Bf, op);
+  std::memset(&F, 0, sizeof F);
+  const double w = op.uw[0], wd = op.uw[1];
+  auto even = [](const double* row, double e[4]) {
+    e[0] = row[0];
+    e[1] = 0.5 * (row[2] + row[4]);
+    e[2] = row[3];
+    e[3] = 0.5 * (row[6] + row[7]);
+  };
+  // Y, Z (even) and X (odd) of a 3 x 9 map
+  auto split = [&](const double L[3][9], double Y[4], double Z[4], double X[2]) {
+    double y[9], z[9], x[9];
+    for (int q = 0; q < 9; ++q) {
+      z[q] = wd * (L[1][q] + L[2][q]);
+      y[q] = w * L[0][q] + z[q];
+      x[q] = wd * (L[1][q] - L[2][q]);
+    }
+    even(y, Y);
+    if (Z) even(z, Z);
+    X[0] = 0.5 * (x[2] - x[4]);
+    X[1] = 0.5 * (x[6] - x[7]);
+  };
+  for (int v = 0; v < 2; ++v) {
+    split(op.Lf[v], F.Y[v], F.Z[v], F.X[v]);
+    F.Zs[v] = wd * (op.Ls[v][1] + op.Ls[v][2]);
+    F.Ys[v] = w * op.Ls[v][0] + F.Zs[v];
+    F.Zk[v] = wd * (op.Lk[v][1] + op.Lk[v][2]);
+    F.Yk[v] = w * op.Lk[v][0] + F.Zk[v];
+  }
+  split(op.Ld, F.Dy, nullptr, F.Dx);
+  split(op.Lg0, F.Gy, nullptr, F.Gx);
+  even(op.ga, F.ka);
+  even(op.ge, F.ke);
+  F.A0 = op.A0;
+  F.A1 = op.A1;
+  F.A2 = op.A2;
+  F.Hc = w * op.hc[0] + wd * (op.hc[1] + op.hc[2]);
+  F.H1 = w * op.h1[0] + wd * (op.h1[1] + op.h1[2]);
 }
 
 // D3Q19 faces: the same least-squares completion over 19 rows, with the five

@@ -104,9 +104,9 @@ struct lks_ctx {
   void* P[2][5] = {};
   void* C = nullptr;     // checkpoints
   void* Seg = nullptr;   // replay segment
-  void* d_ops = nullptr;   // adjoint boundary operators (4 orientations), RingOpT<R>
-  lks::RingOp ops[4];
-  lks::RingOpT<float> ops_f[4];
+  void* d_ops = nullptr;   // adjoint boundary completion, RingFillT<R>
+  lks::RingFillT<double> ops;
+  lks::RingFillT<float> ops_f;
   void* d_ops3 = nullptr;  // D3Q19 face operators (6 orientations), FaceOpT<R>
   lks::FaceOp3 ops3[6];
   lks::FaceOpT<float> ops3_f[6];
@@ -208,7 +208,7 @@ size_t base_bytes(const lks_ctx* c) {
     b += align256(sizeof(int) * c->face3h.size());  // boundary nodes
     b += align256(size_t(moments3_fields(c)) * N * r);
   } else {
-    b += align256(4 * sizeof(lks::RingOp));   // ring operators
+    b += align256(lks::RING_OPS_BYTES);  // ring completion and accumulators
   }
   b += align256(sizeof(double) * 8);
   b += align256(sizeof(int) * 4);
@@ -947,7 +947,7 @@ struct Run {
     a.exact = c->adj_exact;
     a.seed_dp = sdp;
     a.seed_heat = sh;
-    a.ops = static_cast<const lks::RingOpT<R>*>(c->d_ops);
+    a.ops = static_cast<const lks::RingFillT<R>*>(c->d_ops);
     a.beta = rp<R>(c->beta);
     a.dbeta = rp<R>(c->dbeta);
     return a;
@@ -1173,7 +1173,7 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
   g.gbx = phys->gbeta[0];
   g.gby = phys->gbeta[1];
   g.Tref = phys->T_ref;
-  lks::build_ring_ops(g.A, g.Bf, c->ops);
+  lks::build_ring_fill(g.A, g.Bf, c->ops);
   if (d3) {
     lks::Geo3& g3 = c->geo3;
     g3.nx = grid->nx;
@@ -1285,7 +1285,7 @@ lks_status lks_bind_workspace(lks_ctx* c, void* dev_ptr, size_t bytes) {
     c->face3 = reinterpret_cast<int*>(take(sizeof(int) * c->face3h.size()));
     c->M3 = take(size_t(moments3_fields(c)) * N * r);
   } else {
-    c->d_ops = take(4 * sizeof(lks::RingOp));
+    c->d_ops = take(lks::RING_OPS_BYTES);
   }
   c->scal = reinterpret_cast<double*>(take(sizeof(double) * 8));
   c->flag = reinterpret_cast<int*>(take(sizeof(int) * 4));
@@ -1315,10 +1315,10 @@ lks_status lks_bind_workspace(lks_ctx* c, void* dev_ptr, size_t bytes) {
   // the operators in the arithmetic type of the kernels
   const bool f32 = c->rsz == 4;
   if (f32) {
-    for (int o = 0; o < 4; ++o) c->ops_f[o] = lks::ring_op_as<float>(c->ops[o]);
+    c->ops_f = lks::ring_fill_as<float>(c->ops);
     for (int o = 0; o < 6; ++o) c->ops3_f[o] = lks::face_op_as<float>(c->ops3[o]);
   }
-  const void* ops_src = f32 ? static_cast<const void*>(c->ops_f) : static_cast<const void*>(c->ops);
+  const void* ops_src = f32 ? static_cast<const void*>(&c->ops_f) : static_cast<const void*>(&c->ops);
   const size_t ops_bytes = f32 ? sizeof c->ops_f : sizeof c->ops;
   const void* ops3_src =
       f32 ? static_cast<const void*>(c->ops3_f) : static_cast<const void*>(c->ops3);
@@ -1978,7 +1978,7 @@ void build_batch_desc(lks_batch* b, double seed, int nf, std::vector<char>& fwd,
         a.vx1 = rp<R>(c->P[p ^ 1][1]);
         a.vy1 = rp<R>(c->P[p ^ 1][2]);
         a.th1 = rp<R>(c->P[p ^ 1][3]);
-        a.ops = static_cast<const lks::RingOpT<R>*>(c->d_ops);
+        a.ops = static_cast<const lks::RingFillT<R>*>(c->d_ops);
         a.sens = b->d_sens + size_t(d) * b->maxN;
         a.sens_mode = 0;
         a.exact = b->exact;
