@@ -193,6 +193,32 @@ struct AdjArgs {
   int sens_b_only = 0;       // exact mode, level 0: the conductivity term only
 };
 
+// Several steps per launch (small grids, lks_multi.hip): ntx x nty tiles of
+// about equal size, k steps.
+constexpr int MULTI_STEPS = 8;  // most steps of one launch
+struct MultiShape {
+  int ntx, nty, k;
+};
+// a sweep direction's launch shape; k = 0: the sweep takes the tile kernels
+struct MultiPlan {
+  int k = 0, ntx = 0, nty = 0, variant = 0;
+};
+// where the level after each step of a forward launch is kept (drho, ux, uy,
+// T; ux null: not kept, drho null: without density)
+template <typename R>
+struct MultiLevels {
+  R* f[MULTI_STEPS][4];
+};
+// the state each step of an adjoint launch uses (one when frozen); the step
+// `unseeded` (-1: none) is that of level 0, without objective seeds
+template <typename R>
+struct MultiStates {
+  const R* u[MULTI_STEPS];
+  const R* v[MULTI_STEPS];
+  const R* T[MULTI_STEPS];
+  int frozen, unseeded;
+};
+
 // one design of a batch: geometry and the arguments of both ping-pong parities
 template <typename R>
 struct BatchFwd {
@@ -382,6 +408,18 @@ void launch_lks_step2(const Geo& g, const FwdArgs<float>& a, hipStream_t s);
 // FP64 non-thermal forward, two steps per launch
 void launch_lks_step2(const Geo& g, const FwdArgs<double>& a, hipStream_t s);
 void launch_alks_step2(const Geo& g, const AdjArgs<float>& a, hipStream_t s);
+// several steps per launch: the launch shape for a grid (k = 0 where the tile
+// kernels are faster or max_tiles is too small), and `steps` <= k steps of
+// it. Forward: a.level_mid is the level of the first step written, a.level_out
+// the last entry of the inflow table; a.d1 ... are not used (lv). Adjoint:
+// a.ux, a.uy, a.T are not used (sv).
+MultiPlan multi_plan(const Geo& g, int rsz, bool adjoint, int max_tiles);
+template <typename R>
+void launch_lks_multi(const Geo& g, const MultiPlan& p, int steps, const FwdArgs<R>& a,
+                      const MultiLevels<R>& lv, hipStream_t s);
+template <typename R>
+void launch_alks_multi(const Geo& g, const MultiPlan& p, int steps, const AdjArgs<R>& a,
+                       const MultiStates<R>& sv, hipStream_t s);
 template <typename R>
 void launch_pressure_drop(const Geo& g, const uint8_t* mask, const R* d, double* out,
                           hipStream_t s);

@@ -77,6 +77,9 @@ struct lks_ctx {
   int dim = 2;         // 2: D2Q9, 3: D3Q19
   int spl_f = 1;       // steady sweeps: time steps per launch (1 or 2),
   int spl_a = 1;       // forward and adjoint
+  // several steps per launch on small D2Q9 grids, until a launch shape is set
+  // explicitly (k = 0: the tile kernels run the sweep)
+  lks::MultiPlan mf, ma;
   int N = 0;           // nodes
   Geo geo{};           // D2Q9 geometry
   lks::Geo3 geo3{};    // D3Q19 geometry
@@ -115,6 +118,8 @@ struct lks_ctx {
   void* M3 = nullptr;    // D3Q19 adjoint moments of one step
   std::vector<int> copy3h, face3h;
   double* acc = nullptr; // per-tile objective accumulators
+  double* acc_run = nullptr;  // ... those of the last unsteady forward sweep
+  int acc_n = 0;              // and their count
   double* scal = nullptr;
   int* flag = nullptr;
   // run state
@@ -624,6 +629,25 @@ struct Run {
     int pp = 0;  // the ping-pong buffers of the current level
     R* in[5];
     level(from, seg_base, in, pp);
+    if (c->mf.k) {
+      for (int n = from; n < to;) {
+        const int m = std::min(c->mf.k, to - n);
+        R* lv[lks::MULTI_STEPS][5];
+        for (int s = 0; s < m; ++s) {
+          level(n + 1 + s, seg_base, lv[s], pp ^ 1);
+          // of a level inside the launch the checkpoint or slot fields are kept
+          for (int f = 0; f < 5 && s < m - 1; ++f)
+            if (lv[s][f] && (lv[s][f] == rp<R>(c->S[0][f]) || lv[s][f] == rp<R>(c->S[1][f])))
+              lv[s][f] = nullptr;
+        }
+        multi_step(in, n, m, lv, acc);
+        for (int f = 0; f < 5; ++f) in[f] = lv[m - 1][f];
+        n += m;
+        pp ^= 1;
+      }
+      for (int f = 0; f < 5; ++f) last[f] = in[f];
+      return;
+    }
     for (int n = from; n < to;) {
       R* out[5];
       if (two && n + 2 <= to) {
@@ -650,6 +674,30 @@ struct Run {
       for (int f = 0; f < 5; ++f) in[f] = out[f];
     }
     for (int f = 0; f < 5; ++f) last[f] = in[f];
+  }
+
+  // `steps` <= mf.k LKS steps from level n held in `in` in one launch; lv[s]
+  // is where level n + 1 + s is kept (null pointers: it is not)
+  void multi_step(R* const in[5], int n, int steps, R* const (*lv)[5], double* acc) {
+    lks::FwdArgs<R> a = fwd_args(in, in, 0, acc);
+    a.level_mid = n + 1;
+    a.level_out = int(c->ufac.size()) - 1;
+    lks::MultiLevels<R> ml;
+    for (int s = 0; s < lks::MULTI_STEPS; ++s)
+      for (int f = 0; f < 4; ++f) ml.f[s][f] = s < steps ? lv[s][f] : nullptr;
+    lks::launch_lks_multi<R>(g, c->mf, steps, a, ml, c->stream);
+  }
+
+  // accumulators of an unsteady forward sweep, zeroed
+  void clear_acc() {
+    c->acc_n = c->mf.k ? c->mf.ntx * c->mf.nty : acc_count(c);
+    // (many small tiles can outnumber the tiles of the smallest tile height)
+    c->acc_run = c->acc_n <= acc_capacity(c)
+                     ? c->acc
+                     : reinterpret_cast<double*>(static_cast<char*>(c->d_ops) +
+                                                 lks::RING_OPS_BYTES -
+                                                 lks::RING_ACC * sizeof(double));
+    lks::launch_fill(c->acc_run, size_t(c->acc_n), 0.0, c->stream);
   }
 
   void step(R* const in[5], R* const out[5], int level_out, double* acc) {
@@ -757,15 +805,23 @@ struct Run {
     R* cur[5];
     for (int f = 0; f < 5; ++f) cur[f] = in[f];
     int p = 0;
-    for (int i = 0; i < steps; ++i) {
+    const int per = std::max(1, c->mf.k);
+    for (int i = 0; i < steps; i += per) {
+      const int m = std::min(per, steps - i);
       R* out[5];
-      if (last && i == steps - 1) {
+      if (last && i + m == steps) {
         for (int f = 0; f < 5; ++f) out[f] = last[f];
       } else {
         work(p, out);
         p ^= 1;
       }
-      step(cur, out, from + i + 1, acc);
+      if (c->mf.k) {
+        R* lv[lks::MULTI_STEPS][5] = {};
+        for (int f = 0; f < 5; ++f) lv[m - 1][f] = out[f];
+        multi_step(cur, from + i, m, lv, acc);
+      } else {
+        step(cur, out, from + i + 1, acc);
+      }
       for (int f = 0; f < 5; ++f) cur[f] = out[f];
     }
     for (int f = 0; f < 5; ++f) res[f] = cur[f];
@@ -783,10 +839,10 @@ struct Run {
       const Act& x = p.acts[size_t(i)];
       R* dst[5];
       snap(x.dst, dst);
-      bin_advance(cur, lvl, x.steps, dst, cur, c->acc);
+      bin_advance(cur, lvl, x.steps, dst, cur, c->acc_run);
       lvl += x.steps;
     }
-    bin_advance(cur, lvl, steps - lvl, nullptr, cur, c->acc);
+    bin_advance(cur, lvl, steps - lvl, nullptr, cur, c->acc_run);
     for (int f = 0; f < 5; ++f) c->lastv[f] = cur[f];
     lks::launch_finite_check<R>(cur[1], N, c->flag, c->stream);
     c->last_level = steps;
@@ -795,7 +851,7 @@ struct Run {
   void forward(const double* gamma, int steps) {
     coefficients(gamma);
     if (c->mode == LKS_UNSTEADY && c->plan.scheme == LKS_CKPT_BINOMIAL) {
-      lks::launch_fill(c->acc, size_t(acc_count(c)), 0.0, c->stream);
+      clear_acc();
       forward_binomial(steps);
       return;
     }
@@ -807,12 +863,12 @@ struct Run {
       advance(steps);
       return;
     }
-    lks::launch_fill(c->acc, size_t(acc_count(c)), 0.0, c->stream);
+    clear_acc();
     R* lv[5];
     level(0, c->plan.ls, lv);
     init(lv);
     R* last[5];
-    sweep(0, steps, c->plan.ls, c->acc, last);
+    sweep(0, steps, c->plan.ls, c->acc_run, last);
     for (int f = 0; f < 5; ++f) c->lastv[f] = last[f];
     lks::launch_finite_check<R>(last[1], N, c->flag, c->stream);
     c->last_level = steps;
@@ -820,6 +876,18 @@ struct Run {
 
   void advance(int steps) {
     int n = 0;
+    while (c->mf.k && n < steps) {
+      const int m = std::min(c->mf.k, steps - n);
+      R* in[5] = {};
+      R* lv[lks::MULTI_STEPS][5] = {};
+      for (int f = 0; f < nf; ++f) {
+        in[f] = rp<R>(c->S[c->cur][f]);
+        lv[m - 1][f] = rp<R>(c->S[c->cur ^ 1][f]);
+      }
+      multi_step(in, c->last_level + n, m, lv, nullptr);
+      c->cur ^= 1;
+      n += m;
+    }
     if (two_step_fwd(c->spl_f)) {
       for (; n + 2 <= steps; n += 2) {
         R* in[5] = {};
@@ -953,6 +1021,29 @@ struct Run {
     return a;
   }
 
+  // `steps` <= ma.k ALKS steps in one launch, the state of step s in st[s]
+  // (drho, u..., T; st[0] for every step when frozen); `unseeded` as in
+  // MultiStates
+  void multi_adj(R* const (*st)[5], int steps, bool frozen, int unseeded, double seed,
+                 double* sens, int mode) {
+    double sdp, sh, ss, sbt;
+    seeds(seed, &sdp, &sh, &ss, &sbt);
+    lks::AdjArgs<R> a = adj_args(st[0], sdp, sh, sens, mode);
+    a.seed_src = ss;
+    a.seed_bt = sbt;
+    lks::MultiStates<R> sv;
+    for (int s = 0; s < lks::MULTI_STEPS; ++s) {
+      R* const* x = st[s < steps && !frozen ? s : 0];
+      sv.u[s] = x[1];
+      sv.v[s] = x[2];
+      sv.T[s] = x[3];
+    }
+    sv.frozen = frozen ? 1 : 0;
+    sv.unseeded = unseeded;
+    lks::launch_alks_multi<R>(g, c->ma, steps, a, sv, c->stream);
+    c->acur ^= 1;
+  }
+
   void adjoint_steady(double seed, int steps, double* dJ, bool reset) {
     if (reset) {
       c->acur = 0;
@@ -964,8 +1055,13 @@ struct Run {
     for (int f = 0; f < nf; ++f) st[f] = cur_field(f);
     if (!c->phys.thermal) st[nf - 1] = nullptr;
     int n = 0;
+    while (c->ma.k && n < steps) {
+      const int m = std::min(c->ma.k, steps - n);
+      n += m;
+      multi_adj(&st, m, true, -1, seed, n == steps ? dJ : nullptr, 2);
+    }
     if constexpr (std::is_same<R, float>::value) {
-      if (two_step(c->spl_a) && steps >= 2) {
+      if (!c->ma.k && two_step(c->spl_a) && steps >= 2) {
         if (steps % 2) adj_step(st, sdp, sh, nullptr, 2, ss, sbt);
         for (n = steps % 2; n < steps; n += 2) {
           lks::AdjArgs<R> a = adj_args(st, sdp, sh, n + 2 == steps ? dJ : nullptr, 2);
@@ -1025,7 +1121,14 @@ struct Run {
         R* last[5];
         sweep(b, top, b, nullptr, last);
       }
-      for (int n = top; n >= b; --n) {
+      for (int n = top; c->ma.k && n >= b;) {
+        const int m = std::min(c->ma.k, n - b + 1);
+        R* lv[lks::MULTI_STEPS][5];
+        for (int s = 0; s < m; ++s) level(n - s, b, lv[s]);
+        multi_adj(lv, m, false, n - m + 1 == 0 ? m - 1 : -1, seed / Nst, dJ, 1);
+        n -= m;
+      }
+      for (int n = top; !c->ma.k && n >= b; --n) {
         R* lv[5];
         level(n, b, lv);
         double sdp, sh, ss, sbt;
@@ -1196,6 +1299,13 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
   c->stream = static_cast<hipStream_t>(hip_stream);
   c->budget = mem_budget_bytes;
   c->rsz = grid->precision == LKS_FP64 ? 8 : 4;
+  if (!d3) {
+    // (an unsteady forward sweep accumulates its objective per tile)
+    c->mf = lks::multi_plan(g, c->rsz, false, c->mode == LKS_UNSTEADY
+                                                  ? std::max(lks::RING_ACC, max_tiles(g))
+                                                  : 1 << 20);
+    c->ma = lks::multi_plan(g, c->rsz, true, 1 << 20);
+  }
   st = plan_memory(c);
   if (st != LKS_OK) {
     delete c;
@@ -1448,7 +1558,7 @@ lks_status lks_objective(lks_ctx* c, double* J) {
   lks_status st = LKS_OK;
   double sc[8];
   int flag[4];
-  if (c->mode == LKS_UNSTEADY) lks::launch_sum(c->acc, acc_count(c), c->scal, c->stream);
+  if (c->mode == LKS_UNSTEADY) lks::launch_sum(c->acc_run, c->acc_n, c->scal, c->stream);
   if (!hip_ok(c, hipMemcpyAsync(sc, c->scal, sizeof sc, hipMemcpyDeviceToHost, c->stream),
               "read objective", &st) ||
       !hip_ok(c, hipMemcpyAsync(flag, c->flag, sizeof flag, hipMemcpyDeviceToHost, c->stream),
@@ -1588,6 +1698,7 @@ lks_status lks_set_tile_rows(lks_ctx* c, int tile_rows) {
   for (int ty : TILE_ROWS)
     if (ty == tile_rows && tile_rows_ok(ty, c->rsz, c->phys.thermal)) {
       set_tile_rows(c->geo, ty);
+      c->mf = c->ma = lks::MultiPlan();
       c->have_forward = false;
       c->have_adjoint = false;
       return LKS_OK;
@@ -1617,6 +1728,7 @@ lks_status lks_set_steps_per_launch(lks_ctx* c, int forward_steps, int adjoint_s
                 "FP64 sweeps run two steps per launch for the non-thermal forward only");
   c->spl_f = forward_steps;
   c->spl_a = adjoint_steps;
+  c->mf = c->ma = lks::MultiPlan();
   return LKS_OK;
 }
 
@@ -1701,7 +1813,7 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
     if (!hip_ok(c, hipEventCreate(&ev), "event", &st)) return st;
   // per tile height, the forward and adjoint sweeps with one and (where
   // supported) two steps per launch, timed separately
-  float best = 0.0f;
+  float best = 0.0f, best_tf = 0.0f, best_ta = 0.0f;
   int best_ty = c->geo.ty, best_f = c->spl_f, best_a = c->spl_a;
   const int mode = c->mode;
   // two steps per launch exist for FP32 sweeps and the FP64 non-thermal
@@ -1709,6 +1821,31 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
   const bool fwd2 = c->rsz == 4 || !c->phys.thermal;
   const int nspl = fwd2 ? 2 : 1;
   c->mode = LKS_STEADY;  // time plain steps on the ping-pong buffers
+  auto time_sweeps = [&](float* tf, float* ta) {
+    for (int rep = 0; rep < 2 && st == LKS_OK; ++rep) {  // the first repetition warms up
+      hipEventRecord(e[0], c->stream);
+      if (c->rsz == 8) {
+        Run<double> r(c);
+        r.forward(gamma_dev, steps);
+        hipEventRecord(e[1], c->stream);
+        r.adjoint_steady(1.0, steps, nullptr, true);
+      } else {
+        Run<float> r(c);
+        r.forward(gamma_dev, steps);
+        hipEventRecord(e[1], c->stream);
+        r.adjoint_steady(1.0, steps, nullptr, true);
+      }
+      hipEventRecord(e[2], c->stream);
+      if (!hip_ok(c, hipEventSynchronize(e[2]), "autotune sync", &st)) break;
+      hipEventElapsedTime(tf, e[0], e[1]);
+      hipEventElapsedTime(ta, e[1], e[2]);
+    }
+  };
+  // the several-steps kernels of the grid's size, if any
+  const lks::MultiPlan mf = c->mf, ma = c->ma;
+  float tmf = 0.0f, tma = 0.0f;
+  if (mf.k || ma.k) time_sweeps(&tmf, &tma);
+  c->mf = c->ma = lks::MultiPlan();
   for (int ty : TILE_ROWS) {
     if (!tile_rows_ok(ty, c->rsz, c->phys.thermal)) continue;
     set_tile_rows(c->geo, ty);
@@ -1716,24 +1853,7 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
     const int nspl_ty = ty == 16 ? 1 : nspl;
     for (int spl = 1; spl <= nspl_ty && st == LKS_OK; ++spl) {
       c->spl_f = c->spl_a = spl;
-      for (int rep = 0; rep < 2; ++rep) {  // the first repetition warms up
-        hipEventRecord(e[0], c->stream);
-        if (c->rsz == 8) {
-          Run<double> r(c);
-          r.forward(gamma_dev, steps);
-          hipEventRecord(e[1], c->stream);
-          r.adjoint_steady(1.0, steps, nullptr, true);
-        } else {
-          Run<float> r(c);
-          r.forward(gamma_dev, steps);
-          hipEventRecord(e[1], c->stream);
-          r.adjoint_steady(1.0, steps, nullptr, true);
-        }
-        hipEventRecord(e[2], c->stream);
-        if (!hip_ok(c, hipEventSynchronize(e[2]), "autotune sync", &st)) break;
-        hipEventElapsedTime(&tf[spl - 1], e[0], e[1]);
-        hipEventElapsedTime(&ta[spl - 1], e[1], e[2]);
-      }
+      time_sweeps(&tf[spl - 1], &ta[spl - 1]);
     }
     if (st != LKS_OK) break;
     const int sf = (nspl_ty == 2 && tf[1] < tf[0]) ? 2 : 1;
@@ -1741,6 +1861,8 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
     const float t = tf[sf - 1] + ta[sa - 1];
     if (best == 0.0f || t < best) {
       best = t;
+      best_tf = tf[sf - 1];
+      best_ta = ta[sa - 1];
       best_ty = ty;
       best_f = sf;
       best_a = sa;
@@ -1751,6 +1873,8 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
   set_tile_rows(c->geo, best_ty);
   c->spl_f = best_f;
   c->spl_a = best_a;
+  if (mf.k && tmf <= best_tf) c->mf = mf;
+  if (ma.k && tma <= best_ta) c->ma = ma;
   c->have_forward = false;
   c->have_adjoint = false;
   c->last_level = 0;
