@@ -381,10 +381,12 @@ lks_status lks_checkpoint_info(const lks_ctx *ctx, int *scheme, int *count,
  *     adjoint sweep (two-level checkpointing with one interval K for every
  *     design, chosen by lks_batch_set_memory_budget), the sensitivity summed
  *     over levels as alks_backward does for one design.
- * Each step of all designs is one kernel launch, and the whole sequence is
- * captured once as a HIP graph and replayed (use_graph = 1) or launched
- * eagerly (use_graph = 0). Each design's results are bitwise those of its own
- * context at the same tile height. */
+ * Each launch runs one step of all designs, or, until a tile height is set
+ * (lks_batch_set_tile_rows), several steps where the designs' sizes allow it;
+ * the whole sequence is captured once as a HIP graph and replayed
+ * (use_graph = 1) or launched eagerly (use_graph = 0). Each design's fields and
+ * sensitivities are bitwise those of its own context; an unsteady objective
+ * too at the same tile height. */
 typedef struct lks_batch lks_batch;
 
 /* Validates every design as lks_create does. Makes no HIP call. grids/phys/bcs

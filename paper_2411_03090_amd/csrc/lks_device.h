@@ -414,6 +414,36 @@ void launch_alks_step2(const Geo& g, const AdjArgs<float>& a, hipStream_t s);
 // the last entry of the inflow table; a.d1 ... are not used (lv). Adjoint:
 // a.ux, a.uy, a.T are not used (sv).
 MultiPlan multi_plan(const Geo& g, int rsz, bool adjoint, int max_tiles);
+// batches: steps per launch kf, ka (0: the tile kernels run the batch) on tiles
+// of at most `tile` nodes along each axis, and the block variants
+struct BatchPlan {
+  int tile = 0, kf = 0, vf = 0, ka = 0, va = 0;
+};
+BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool thermal);
+void multi_batch_tiles(const Geo& g, int tile, int* ntx, int* nty);
+bool multi_fits(const Geo& g, int ntx, int nty, int rsz, bool adjoint, int variant, int steps);
+// steady batches: `steps` steps of every design (descriptors as for the tile
+// kernels, the geometry's tile counts those of the plan)
+template <typename R>
+void launch_lks_multi_batch(const BatchFwd<R>* d, const int* tmap, int total, bool thermal,
+                            int variant, int steps, int parity, hipStream_t s);
+template <typename R>
+void launch_alks_multi_batch(const BatchAdj<R>* d, const int* tmap, int total, bool thermal,
+                             int variant, int steps, int parity, int last, hipStream_t s);
+// unsteady batches: from the level at `in` through those at lv (the first of
+// which is level `level`); adjoint: the levels at lv, downwards, `unseeded` as
+// in MultiStates
+struct MultiRefs {
+  LevelRef r[MULTI_STEPS];
+};
+template <typename R>
+void launch_lks_multi_ubatch(const BatchFwd<R>* d, const BatchStore<R>* st, const int* tmap,
+                             int total, bool thermal, int variant, int steps, LevelRef in,
+                             const MultiRefs& lv, int level, int use_acc, hipStream_t s);
+template <typename R>
+void launch_alks_multi_ubatch(const BatchAdj<R>* d, const BatchStore<R>* st, const int* tmap,
+                              int total, bool thermal, int variant, int steps, int parity,
+                              const MultiRefs& lv, int unseeded, hipStream_t s);
 template <typename R>
 void launch_lks_multi(const Geo& g, const MultiPlan& p, int steps, const FwdArgs<R>& a,
                       const MultiLevels<R>& lv, hipStream_t s);

@@ -31,9 +31,8 @@ struct MultiTile {
   int tile;
 };
 
-__device__ inline bool multi_tile(const Geo& g, const MultiShape& ms, MultiTile& t) {
-  t.tile = xcd_tile(ms.ntx * ms.nty);
-  if (t.tile < 0) return false;
+__device__ inline void multi_tile(const Geo& g, const MultiShape& ms, int tile, MultiTile& t) {
+  t.tile = tile;
   const int bx = t.tile % ms.ntx, by = t.tile / ms.ntx;
   t.x0 = int((long long)bx * g.nx / ms.ntx);
   t.x1 = int((long long)(bx + 1) * g.nx / ms.ntx);
@@ -51,7 +50,6 @@ __device__ inline bool multi_tile(const Geo& g, const MultiShape& ms, MultiTile&
   }
   t.W = X1 - t.X0;
   t.H = Y1 - t.Y0;
-  return true;
 }
 
 // A register value the compiler takes as new here: what is derived from it (LDS
@@ -140,15 +138,16 @@ __device__ inline MultiNode multi_node(const Geo& g, const MultiTile& t, int e) 
 // wanted (the last one always); their objective terms are summed per wave and
 // level and added to the tile's accumulator in level order, so the sum does
 // not depend on how a sweep is cut into launches.
-template <typename R, bool TH, int NT, int NPT, int NMAX>
-__global__ __launch_bounds__(NT) void lks_multi_kernel(Geo g, FwdArgs<R> a, MultiShape ms,
-                                                       MultiLevels<R> lv) {
+// (lv(st, out) gives the pointers of step st)
+template <typename R, bool TH, int NT, int NPT, int NMAX, typename Out>
+__device__ __forceinline__ void multi_fwd(const Geo& g, const FwdArgs<R>& a, const MultiShape& ms,
+                                          int tile, Out&& lv) {
   constexpr int LU = 0, LV = 1, LT = 2, LF = TH ? 3 : 2, LG = LF + 8, NA = TH ? 19 : 10;
   __shared__ R L[NA][NMAX];
   __shared__ double red[MULTI_STEPS][NT / 64];
   __shared__ R cd[4];  // new density of the corners (by their y-neighbours)
   MultiTile t;
-  if (!multi_tile(g, ms, t)) return;
+  multi_tile(g, ms, tile, t);
   const int W = t.W, tid = int(threadIdx.x);
   const R A = R(g.A);
   MultiNode n[NPT];
@@ -189,6 +188,9 @@ __global__ __launch_bounds__(NT) void lks_multi_kernel(Geo g, FwdArgs<R> a, Mult
   for (int st = 0; st < ms.k; ++st) {
     const int reach = 2 * (ms.k - st) - 1;  // the post-collision values are needed this far out
     const int level = min(a.level_mid + st, a.level_out);
+    // (scalar loads share their wait with LDS reads: fetched before the stages)
+    R* out[4];
+    lv(st, out);
     lds_barrier();
 #pragma unroll
     for (int e = 0; e < NPT; ++e) {
@@ -222,7 +224,6 @@ __global__ __launch_bounds__(NT) void lks_multi_kernel(Geo g, FwdArgs<R> a, Mult
     }
     lds_barrier();
     double part = 0.0;
-    R* const* out = lv.f[st];
     const bool keep = out[1] != nullptr;
 #pragma unroll
     for (int e = 0; e < NPT; ++e) {
@@ -323,15 +324,16 @@ __device__ inline int dir_of(int cx, int cy) {
 // The state of step st is st.u[st] ...; a steady sweep gives one state
 // (frozen). The sensitivity of the tile's nodes is summed in registers over
 // the launch, in the order of single steps.
-template <typename R, bool TH, int NT, int NPT, int NMAX>
-__global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, MultiShape ms,
-                                                        MultiStates<R> sv) {
+// (sv(st, f) gives field f of the state of step st: 1, 2 velocity, 3 T)
+template <typename R, bool TH, int NT, int NPT, int NMAX, typename In>
+__device__ __forceinline__ void multi_adj(const Geo& g, const AdjArgs<R>& a0, const MultiShape& ms,
+                                          int tile, bool frozen, int unseeded, In&& sv) {
   constexpr int LE = 0, LS = 8, LQ = 11, LTH = 13, LT = 14, LBQ = 15, NA = TH ? 17 : 11;
   __shared__ R L[NA][NMAX];
   __shared__ R cm[4][4];  // r, U~, T~ of the corners (by their y-neighbours)
   MultiTile t;
-  if (!multi_tile(g, ms, t)) return;
-  const int W = t.W, tid = int(threadIdx.x);
+  multi_tile(g, ms, tile, t);
+  const int W = t.W;
   AdjArgs<R> a = a0;
   // corners take the moments of their y-neighbour and its local terms
   auto local_of = [&](const MultiNode& x) {
@@ -374,11 +376,11 @@ __global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, Mu
     R th = R(0);
     s[e] = a.inv1pa[k];
     m[e] = a.mask[kl];
-    ux[e] = sv.u[0][k];
-    uy[e] = sv.v[0][k];
+    ux[e] = sv(0, 1)[k];
+    uy[e] = sv(0, 2)[k];
     if constexpr (TH) {
       th = a.th0[k];
-      T[e] = sv.T[0][kl];
+      T[e] = sv(0, 3)[kl];
       B[e] = a.B[k];
       if (a.beta) be[e] = a.beta[k];
     }
@@ -411,7 +413,7 @@ __global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, Mu
   for (int st = 0; st < ms.k; ++st) {
     const int reach = 2 * (ms.k - st) - 1;  // moments are needed this far out
     const bool want = a0.sens_mode == 1 || (a0.sens_mode == 2 && st == ms.k - 1);
-    if (st == sv.unseeded) {  // level 0 carries no seed
+    if (st == unseeded) {  // level 0 carries no seed
       a.seed_dp = a.seed_heat = a.seed_src = a.seed_bt = 0.0;
       a.sens_b_only = a0.exact;
     }
@@ -421,7 +423,7 @@ __global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, Mu
       if (n[e].ext() > reach) continue;
       const int p = here<NT, NPT>(n[e].p);
       if constexpr (TH)
-        if (want && (st == 0 || !sv.frozen || a0.sens_mode == 2)) {
+        if (want && (st == 0 || !frozen || a0.sens_mode == 2)) {
           // (a corner's own T enters no gradient that is used)
           L[TH ? LT : 0][p] = T[e];
         }
@@ -471,15 +473,15 @@ __global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, Mu
     }
     // the next step's state, in flight during the second stage
     R nux[NPT], nuy[NPT], nT[NPT];
-    const bool next = !sv.frozen && st + 1 < ms.k;
+    const bool next = !frozen && st + 1 < ms.k;
 #pragma unroll
     for (int e = 0; e < NPT; ++e) {
       nux[e] = nuy[e] = nT[e] = R(0);
       if (!next || n[e].ext() > reach - 2) continue;
       const int k = here<NT, NPT>(n[e].k);
-      nux[e] = sv.u[st + 1][k];
-      nuy[e] = sv.v[st + 1][k];
-      if constexpr (TH) nT[e] = sv.T[st + 1][local_of(n[e])];
+      nux[e] = sv(st + 1, 1)[k];
+      nuy[e] = sv(st + 1, 2)[k];
+      if constexpr (TH) nT[e] = sv(st + 1, 3)[local_of(n[e])];
     }
     lds_barrier();
 #pragma unroll
@@ -514,7 +516,7 @@ __global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, Mu
           nd.Tl = T[e];
           nd.probe = a.seed_heat != 0.0 && (m[e] & TAG_PROBE);
           nd.uxl = ux[e];
-          if (RING && nd.probe && n[e].corner()) nd.uxl = sv.u[sv.frozen ? 0 : st][local_of(n[e])];
+          if (RING && nd.probe && n[e].corner()) nd.uxl = sv(frozen ? 0 : st, 1)[local_of(n[e])];
           nd.beta = be[e];
           nd.B = B[e];
           nd.dBx = dBx[e];
@@ -559,6 +561,117 @@ __global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a0, Mu
 }
 
 // ---------------------------------------------------------------------------
+// kernels: one design
+// ---------------------------------------------------------------------------
+template <typename R, bool TH, int NT, int NPT, int NMAX>
+__global__ __launch_bounds__(NT) void lks_multi_kernel(Geo g, FwdArgs<R> a, MultiShape ms,
+                                                       MultiLevels<R> lv) {
+  const int tile = xcd_tile(ms.ntx * ms.nty);
+  if (tile < 0) return;
+  multi_fwd<R, TH, NT, NPT, NMAX>(g, a, ms, tile, [&](int st, R* out[4]) {
+#pragma unroll
+    for (int f = 0; f < 4; ++f) out[f] = lv.f[st][f];
+  });
+}
+template <typename R, bool TH, int NT, int NPT, int NMAX>
+__global__ __launch_bounds__(NT) void alks_multi_kernel(Geo g, AdjArgs<R> a, MultiShape ms,
+                                                        MultiStates<R> sv) {
+  const int tile = xcd_tile(ms.ntx * ms.nty);
+  if (tile < 0) return;
+  multi_adj<R, TH, NT, NPT, NMAX>(g, a, ms, tile, sv.frozen, sv.unseeded,
+                                  [&](int st, int f) {
+                                    return f == 1 ? sv.u[st] : (f == 2 ? sv.v[st] : sv.T[st]);
+                                  });
+}
+
+// ---------------------------------------------------------------------------
+// kernels: batches
+// ---------------------------------------------------------------------------
+// The table tmap holds the design and the tile within it of every global
+// tile; a design's tile counts are those of its descriptor's geometry.
+template <typename R, bool TH, int NT, int NPT, int NMAX>
+__global__ __launch_bounds__(NT) void lks_multi_batch_kernel(const BatchFwd<R>* __restrict__ d,
+                                                             const int* __restrict__ tmap,
+                                                             int total, int k, int parity) {
+  const int t = xcd_tile(total);
+  if (t < 0) return;
+  const int di = tmap[2 * t];
+  const Geo g = d[di].g;
+  FwdArgs<R> a = d[di].a[parity];
+  a.level_mid = a.level_out;
+  multi_fwd<R, TH, NT, NPT, NMAX>(g, a, {g.ntx, g.nty, k}, tmap[2 * t + 1],
+                                  [&](int st, R* out[4]) {
+                                    const bool last = st == k - 1;
+                                    out[0] = last ? a.d1 : nullptr;
+                                    out[1] = last ? a.ux1 : nullptr;
+                                    out[2] = last ? a.uy1 : nullptr;
+                                    out[3] = last ? a.T1 : nullptr;
+                                  });
+}
+template <typename R, bool TH, int NT, int NPT, int NMAX>
+__global__ __launch_bounds__(NT) void alks_multi_batch_kernel(const BatchAdj<R>* __restrict__ d,
+                                                              const int* __restrict__ tmap,
+                                                              int total, int k, int parity,
+                                                              int last) {
+  const int t = xcd_tile(total);
+  if (t < 0) return;
+  const int di = tmap[2 * t];
+  const Geo g = d[di].g;
+  AdjArgs<R> a = d[di].a[parity];
+  a.sens_mode = last ? 2 : 0;
+  multi_adj<R, TH, NT, NPT, NMAX>(g, a, {g.ntx, g.nty, k}, tmap[2 * t + 1], true, -1,
+                                  [&](int, int f) {
+                                    return f == 1 ? a.ux : (f == 2 ? a.uy : a.T);
+                                  });
+}
+
+// unsteady batches: the levels of a launch resolved from the design's store
+template <typename R, bool TH, int NT, int NPT, int NMAX>
+__global__ __launch_bounds__(NT) void lks_multi_ubatch_kernel(
+    const BatchFwd<R>* __restrict__ d, const BatchStore<R>* __restrict__ st,
+    const int* __restrict__ tmap, int total, int k, LevelRef in, MultiRefs lv, int level,
+    int use_acc) {
+  const int t = xcd_tile(total);
+  if (t < 0) return;
+  const int di = tmap[2 * t];
+  const BatchStore<R> s = st[di];
+  const Geo g = d[di].g;
+  FwdArgs<R> a = d[di].a[0];
+  a.d0 = level_field(s, in, 0);
+  a.ux0 = level_field(s, in, 1);
+  a.uy0 = level_field(s, in, 2);
+  a.T0 = level_field(s, in, 3);
+  a.level_mid = level;
+  a.level_out = s.n_ufac - 1;
+  if (!use_acc) a.acc = nullptr;
+  multi_fwd<R, TH, NT, NPT, NMAX>(
+      g, a, {g.ntx, g.nty, k}, tmap[2 * t + 1], [&](int i, R* out[4]) {
+        // of a level inside the launch its checkpoint or slot is kept (a slot
+        // without density)
+        const LevelRef r = lv.r[i];
+        const bool last = i == k - 1, held = last || r.kind != LVL_PING;
+        out[0] = last || r.kind == LVL_CKPT ? level_field(s, r, 0) : nullptr;
+        out[1] = held ? level_field(s, r, 1) : nullptr;
+        out[2] = held ? level_field(s, r, 2) : nullptr;
+        out[3] = held ? level_field(s, r, 3) : nullptr;
+      });
+}
+template <typename R, bool TH, int NT, int NPT, int NMAX>
+__global__ __launch_bounds__(NT) void alks_multi_ubatch_kernel(
+    const BatchAdj<R>* __restrict__ d, const BatchStore<R>* __restrict__ st,
+    const int* __restrict__ tmap, int total, int k, int parity, MultiRefs lv, int unseeded) {
+  const int t = xcd_tile(total);
+  if (t < 0) return;
+  const int di = tmap[2 * t];
+  const BatchStore<R> s = st[di];
+  const Geo g = d[di].g;
+  AdjArgs<R> a = d[di].a[parity];
+  a.sens_mode = 1;
+  multi_adj<R, TH, NT, NPT, NMAX>(g, a, {g.ntx, g.nty, k}, tmap[2 * t + 1], false, unseeded,
+                                  [&](int i, int f) { return level_field(s, lv.r[i], f); });
+}
+
+// ---------------------------------------------------------------------------
 // launch shapes
 // ---------------------------------------------------------------------------
 constexpr int LDS_BYTES = 160 * 1024 - 2048;  // of a CU, less the small tables
@@ -573,6 +686,9 @@ constexpr int NODES2 =
 // thermal adjoint, whose node does not fit the 128 registers of 1024 threads
 template <typename R, bool TH, bool ADJ>
 constexpr int THREADS1 = TH && ADJ && sizeof(R) == 8 ? 512 : 1024;
+
+template <int N>
+using IntC = std::integral_constant<int, N>;
 
 struct Block {
   int threads, nodes, region;  // threads, node slots, LDS positions
@@ -624,18 +740,6 @@ void region_of(const Geo& g, int ntx, int nty, int k, int lead, int* nodes, int*
   *slots = ms;
 }
 
-template <typename R, bool TH, int NT, int NPT, int NMAX>
-void launch_fwd(const Geo& g, const FwdArgs<R>& a, const MultiShape& ms, const MultiLevels<R>& lv,
-                hipStream_t s) {
-  lks_multi_kernel<R, TH, NT, NPT, NMAX>
-      <<<unsigned(xcd_blocks(ms.ntx * ms.nty)), NT, 0, s>>>(g, a, ms, lv);
-}
-template <typename R, bool TH, int NT, int NPT, int NMAX>
-void launch_adj(const Geo& g, const AdjArgs<R>& a, const MultiShape& ms, const MultiStates<R>& sv,
-                hipStream_t s) {
-  alks_multi_kernel<R, TH, NT, NPT, NMAX>
-      <<<unsigned(xcd_blocks(ms.ntx * ms.nty)), NT, 0, s>>>(g, a, ms, sv);
-}
 }  // namespace
 
 // tile counts for at most `most` tiles: the ones whose tiles with a halo of 4
@@ -699,40 +803,141 @@ MultiPlan multi_plan(const Geo& g, int rsz, bool adj, int max_tiles) {
   return MultiPlan();
 }
 
+// tile counts of a design whose tiles are at most `tile` nodes wide and tall
+void multi_batch_tiles(const Geo& g, int tile, int* ntx, int* nty) {
+  *ntx = std::max(1, std::min((g.nx + tile - 1) / tile, g.nx / 2));
+  *nty = std::max(1, std::min((g.ny + tile - 1) / tile, g.ny / 2));
+}
+
+// Batches. While the tiles of all designs fit one round of blocks, the
+// smallest tiles that do, with the steps their region holds (8 designs of 64 to
+// 256 nodes a side, FP32: 28 x 28 tiles, 4 steps, 2.9 us per step of all; 36 x
+// 36, 2 steps, 4.2; the tile kernels 6.4). Over several rounds larger tiles with
+// fewer steps: 32 designs of 128 to 512, 3.26M nodes, FP32 36 x 36 and 2 steps
+// 37.3 forward and 38.4 us adjoint against 41.0 and 39.6 of the 64 x 8 tile
+// kernels, FP64 30 x 30 and 3 steps 46.9, 48.4 against 65.9, 79.3; 16 thermal
+// ones, 1.46M nodes, FP32 33.9, 38.0 against 39.5, 41.6, FP64 24 x 24 and 2 steps
+// 61.9, 71.5 against 82.8, 92.5.
+BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th) {
+  struct Cand {
+    int tile, k, variant;
+  };
+  static const Cand f32[] = {{8, 6, 1}, {12, 5, 1}, {16, 4, 1}, {20, 6, 2},
+                             {24, 5, 2}, {28, 4, 2}, {32, 3, 2}, {36, 2, 2}};
+  static const Cand f64[] = {{8, 6, 1}, {12, 5, 1}, {16, 4, 1}, {18, 6, 2},
+                             {22, 5, 2}, {26, 4, 2}, {30, 3, 2}};
+  static const Cand f64t[] = {{8, 6, 1}, {12, 5, 1}, {16, 4, 1}, {20, 3, 1}, {24, 2, 1}};
+  const Cand* c = rsz == 4 ? f32 : (th ? f64t : f64);
+  const int nc = rsz == 4 ? 8 : (th ? 5 : 7);
+  BatchPlan p;
+  for (int i = 0; i < nc; ++i) {
+    p.tile = c[i].tile;
+    p.kf = p.ka = c[i].k;
+    p.vf = p.va = c[i].variant;
+    long long tiles = 0;
+    for (int d = 0; d < n; ++d) {
+      int x, y;
+      multi_batch_tiles(*g[d], p.tile, &x, &y);
+      tiles += (long long)x * y;
+    }
+    if (tiles <= 256) break;
+  }
+  return p;
+}
+
+// whether `steps` steps of a design's tiles fit the block of a variant
+bool multi_fits(const Geo& g, int ntx, int nty, int rsz, bool adj, int variant, int steps) {
+  const Block b = block_of(variant, rsz, g.thermal, adj);
+  if (!b.region) return false;
+  int nodes, slots;
+  region_of(g, ntx, nty, steps, b.nodes - b.threads, &nodes, &slots);
+  return nodes <= b.region && slots <= b.nodes;
+}
+
+// f(TH, NT, NPT, NMAX) of the block a variant names (as integral constants)
+template <typename R, bool ADJ, typename F>
+void with_block(bool th, int variant, F&& f) {
+  auto go = [&](auto t) {
+    constexpr bool TH = decltype(t)::value;
+    constexpr int N2 = NODES2<R, TH, ADJ>, NT1K = THREADS1<R, TH, ADJ>;
+    if (variant == 0) f(t, IntC<512>(), IntC<1>(), IntC<512>());
+    else if (variant == 1) f(t, IntC<NT1K>(), IntC<1024 / NT1K>(), IntC<1024>());
+    else if constexpr (N2 > 1024) f(t, IntC<1024>(), IntC<2>(), IntC<N2>());
+  };
+  if (th) go(std::true_type());
+  else go(std::false_type());
+}
+
 template <typename R>
 void launch_lks_multi(const Geo& g, const MultiPlan& p, int steps, const FwdArgs<R>& a,
                       const MultiLevels<R>& lv, hipStream_t s) {
   const MultiShape ms{p.ntx, p.nty, steps};
-  auto go = [&](auto th) {
-    constexpr bool TH = decltype(th)::value;
-    constexpr int N2 = NODES2<R, TH, false>, NT1K = THREADS1<R, TH, false>;
-    if (p.variant == 0) launch_fwd<R, TH, 512, 1, 512>(g, a, ms, lv, s);
-    else if (p.variant == 1) launch_fwd<R, TH, NT1K, 1024 / NT1K, 1024>(g, a, ms, lv, s);
-    else if constexpr (N2 > 1024) launch_fwd<R, TH, 1024, 2, N2>(g, a, ms, lv, s);
-  };
-  if (g.thermal) go(std::true_type());
-  else go(std::false_type());
+  with_block<R, false>(g.thermal, p.variant, [&](auto th, auto nt, auto npt, auto nmax) {
+    lks_multi_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
+        <<<unsigned(xcd_blocks(ms.ntx * ms.nty)), nt.value, 0, s>>>(g, a, ms, lv);
+  });
 }
 template <typename R>
 void launch_alks_multi(const Geo& g, const MultiPlan& p, int steps, const AdjArgs<R>& a,
                        const MultiStates<R>& sv, hipStream_t s) {
   const MultiShape ms{p.ntx, p.nty, steps};
-  auto go = [&](auto th) {
-    constexpr bool TH = decltype(th)::value;
-    constexpr int N2 = NODES2<R, TH, true>, NT1K = THREADS1<R, TH, true>;
-    if (p.variant == 0) launch_adj<R, TH, 512, 1, 512>(g, a, ms, sv, s);
-    else if (p.variant == 1) launch_adj<R, TH, NT1K, 1024 / NT1K, 1024>(g, a, ms, sv, s);
-    else if constexpr (N2 > 1024) launch_adj<R, TH, 1024, 2, N2>(g, a, ms, sv, s);
-  };
-  if (g.thermal) go(std::true_type());
-  else go(std::false_type());
+  with_block<R, true>(g.thermal, p.variant, [&](auto th, auto nt, auto npt, auto nmax) {
+    alks_multi_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
+        <<<unsigned(xcd_blocks(ms.ntx * ms.nty)), nt.value, 0, s>>>(g, a, ms, sv);
+  });
+}
+template <typename R>
+void launch_lks_multi_batch(const BatchFwd<R>* d, const int* tmap, int total, bool thermal,
+                            int variant, int steps, int parity, hipStream_t s) {
+  with_block<R, false>(thermal, variant, [&](auto th, auto nt, auto npt, auto nmax) {
+    lks_multi_batch_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
+        <<<unsigned(xcd_blocks(total)), nt.value, 0, s>>>(d, tmap, total, steps, parity);
+  });
+}
+template <typename R>
+void launch_alks_multi_batch(const BatchAdj<R>* d, const int* tmap, int total, bool thermal,
+                             int variant, int steps, int parity, int last, hipStream_t s) {
+  with_block<R, true>(thermal, variant, [&](auto th, auto nt, auto npt, auto nmax) {
+    alks_multi_batch_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
+        <<<unsigned(xcd_blocks(total)), nt.value, 0, s>>>(d, tmap, total, steps, parity, last);
+  });
+}
+template <typename R>
+void launch_lks_multi_ubatch(const BatchFwd<R>* d, const BatchStore<R>* st, const int* tmap,
+                             int total, bool thermal, int variant, int steps, LevelRef in,
+                             const MultiRefs& lv, int level, int use_acc, hipStream_t s) {
+  with_block<R, false>(thermal, variant, [&](auto th, auto nt, auto npt, auto nmax) {
+    lks_multi_ubatch_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
+        <<<unsigned(xcd_blocks(total)), nt.value, 0, s>>>(d, st, tmap, total, steps, in, lv, level,
+                                                          use_acc);
+  });
+}
+template <typename R>
+void launch_alks_multi_ubatch(const BatchAdj<R>* d, const BatchStore<R>* st, const int* tmap,
+                              int total, bool thermal, int variant, int steps, int parity,
+                              const MultiRefs& lv, int unseeded, hipStream_t s) {
+  with_block<R, true>(thermal, variant, [&](auto th, auto nt, auto npt, auto nmax) {
+    alks_multi_ubatch_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
+        <<<unsigned(xcd_blocks(total)), nt.value, 0, s>>>(d, st, tmap, total, steps, parity, lv,
+                                                          unseeded);
+  });
 }
 
 #define LKS_MULTI_INSTANTIATE(R)                                                             \
   template void launch_lks_multi<R>(const Geo&, const MultiPlan&, int, const FwdArgs<R>&,    \
                                     const MultiLevels<R>&, hipStream_t);                     \
   template void launch_alks_multi<R>(const Geo&, const MultiPlan&, int, const AdjArgs<R>&,   \
-                                     const MultiStates<R>&, hipStream_t);
+                                     const MultiStates<R>&, hipStream_t);                    \
+  template void launch_lks_multi_batch<R>(const BatchFwd<R>*, const int*, int, bool, int, int, \
+                                          int, hipStream_t);                                 \
+  template void launch_alks_multi_batch<R>(const BatchAdj<R>*, const int*, int, bool, int, int, \
+                                           int, int, hipStream_t);                           \
+  template void launch_lks_multi_ubatch<R>(const BatchFwd<R>*, const BatchStore<R>*, const int*, \
+                                           int, bool, int, int, LevelRef, const MultiRefs&, int, \
+                                           int, hipStream_t);                                \
+  template void launch_alks_multi_ubatch<R>(const BatchAdj<R>*, const BatchStore<R>*,        \
+                                            const int*, int, bool, int, int, int,            \
+                                            const MultiRefs&, int, hipStream_t);
 LKS_MULTI_INSTANTIATE(float)
 LKS_MULTI_INSTANTIATE(double)
 

@@ -1938,6 +1938,10 @@ struct lks_batch {
   char* ws = nullptr;
   std::vector<int> tile0;
   int total_tiles = 0;
+  // several steps per launch, until a tile height is set (kf = 0: the tile
+  // kernels), and the designs' tile counts then
+  lks::BatchPlan multi;
+  std::vector<int> ntx, nty;
   int max_tiles = 0;        // tiles of all designs at the shortest tile height
   std::vector<int> tmap;    // (design, tile within the design) of every global tile
   // device
@@ -1978,12 +1982,49 @@ lks_status bfail(lks_batch* b, lks_status s, const std::string& msg) {
 void build_tile_map(lks_batch* b) {
   b->tmap.assign(2 * size_t(b->total_tiles), 0);
   for (int d = 0; d < b->n; ++d) {
-    const int nt = n_tiles(b->ctx[d]->geo);
+    const int nt = b->ntx[d] * b->nty[d];
     for (int t = 0; t < nt; ++t) {
       b->tmap[2 * size_t(b->tile0[d] + t)] = d;
       b->tmap[2 * size_t(b->tile0[d] + t) + 1] = t;
     }
   }
+}
+
+// tile counts of the designs, and their first global tile
+void batch_tiles(lks_batch* b) {
+  b->total_tiles = 0;
+  b->tile0.assign(size_t(b->n), 0);
+  b->ntx.assign(size_t(b->n), 0);
+  b->nty.assign(size_t(b->n), 0);
+  for (int d = 0; d < b->n; ++d) {
+    const Geo& g = b->ctx[d]->geo;
+    if (b->multi.kf) {
+      lks::multi_batch_tiles(g, b->multi.tile, &b->ntx[d], &b->nty[d]);
+    } else {
+      b->ntx[d] = g.ntx;
+      b->nty[d] = g.nty;
+    }
+    b->tile0[d] = b->total_tiles;
+    b->total_tiles += b->ntx[d] * b->nty[d];
+  }
+}
+
+// takes the several-steps plan where every design's tiles fit its blocks and
+// its accumulators
+void batch_multi(lks_batch* b) {
+  std::vector<const Geo*> geos;
+  for (const lks_ctx* c : b->ctx) geos.push_back(&c->geo);
+  b->multi = lks::multi_batch_plan(geos.data(), b->n, b->rsz, b->thermal);
+  if (b->multi.kf) batch_tiles(b);
+  for (int d = 0; d < b->n && b->multi.kf; ++d) {
+    const lks_ctx* c = b->ctx[d];
+    const int x = b->ntx[d], y = b->nty[d];
+    if (x * y > acc_capacity(c) ||
+        !lks::multi_fits(c->geo, x, y, b->rsz, false, b->multi.vf, b->multi.kf) ||
+        !lks::multi_fits(c->geo, x, y, b->rsz, true, b->multi.va, b->multi.ka))
+      b->multi = lks::BatchPlan();
+  }
+  batch_tiles(b);
 }
 
 // workspace slices of the designs, then the batch's own tables
@@ -2047,6 +2088,18 @@ lks::LevelRef level_ref(int n, int base, int K) {
   return {lks::LVL_PING, 0, n & 1};
 }
 
+// launches of n steps, k per launch (0: one)
+int launches(int n, int k) { return k > 1 ? (n + k - 1) / k : n; }
+
+// launches of the adjoint sweep of an unsteady batch
+int adjoint_launches(const lks_batch* b) {
+  const int N = b->n_steps, K = b->K, ls = (N / K) * K;
+  int n = 0;
+  for (int base = ls; base >= 0; base -= K)
+    n += launches((base == ls ? N : base + K - 1) - base + 1, b->multi.ka);
+  return n;
+}
+
 template <typename R>
 void build_batch_desc(lks_batch* b, double seed, int nf, std::vector<char>& fwd,
                       std::vector<char>& adj) {
@@ -2057,6 +2110,8 @@ void build_batch_desc(lks_batch* b, double seed, int nf, std::vector<char>& fwd,
   for (int d = 0; d < b->n; ++d) {
     lks_ctx* c = b->ctx[d];
     F[d].g = c->geo;
+    F[d].g.ntx = b->ntx[d];
+    F[d].g.nty = b->nty[d];
     for (int p = 0; p < 2; ++p) {
       lks::FwdArgs<R>& a = F[d].a[p];
       a.mask = c->d_mask;
@@ -2078,10 +2133,10 @@ void build_batch_desc(lks_batch* b, double seed, int nf, std::vector<char>& fwd,
       a.acc = b->unsteady ? c->acc : nullptr;
       a.objective = c->objective;
     }
-    const int fin = nf & 1;  // ping-pong index of the final forward level
+    const int fin = launches(nf, b->multi.kf) & 1;  // buffer of the final forward level
     for (int v = 0; v < 3; ++v) {
       lks::BatchAdj<R>& D = Aj[v * b->n + d];
-      D.g = c->geo;
+      D.g = F[d].g;
       for (int p = 0; p < 2; ++p) {
         lks::AdjArgs<R>& a = D.a[p];
         a.mask = c->d_mask;
@@ -2139,6 +2194,19 @@ template <typename R>
 void enqueue_batch_steps(lks_batch* b, int nf, int na, hipStream_t s) {
   auto* F = static_cast<const lks::BatchFwd<R>*>(b->d_fwd);
   auto* Aj = static_cast<const lks::BatchAdj<R>*>(b->d_adj);
+  if (b->multi.kf) {
+    const lks::BatchPlan& p = b->multi;
+    int i = 0;
+    for (int n = 0; n < nf; n += p.kf, ++i)
+      lks::launch_lks_multi_batch<R>(F, b->d_tmap, b->total_tiles, b->thermal, p.vf,
+                                     std::min(p.kf, nf - n), i & 1, s);
+    lks::launch_pressure_drop_batch<R>(F, b->n, i & 1, b->d_J, s);
+    i = 0;
+    for (int n = 0; n < na; n += p.ka, ++i)
+      lks::launch_alks_multi_batch<R>(i ? Aj : Aj + 2 * b->n, b->d_tmap, b->total_tiles, b->thermal,
+                                      p.va, std::min(p.ka, na - n), i & 1, n + p.ka >= na, s);
+    return;
+  }
   for (int k = 0; k < nf; ++k)
     lks::launch_lks_step_batch<R>(F, b->d_tmap, b->total_tiles, b->ty, b->thermal, k & 1, s);
   lks::launch_pressure_drop_batch<R>(F, b->n, nf & 1, b->d_J, s);
@@ -2161,8 +2229,29 @@ void enqueue_batch_unsteady(lks_batch* b, bool adjoint, hipStream_t s) {
   auto* St = static_cast<const lks::BatchStore<R>*>(b->d_store);
   const int N = b->n_steps, K = b->K, ls = (N / K) * K;
   const bool th = b->thermal;
+  // LKS steps of levels from + 1 .. to with the slots above `base`, several per
+  // launch; the ping-pong buffers change once per launch
+  auto multi_sweep = [&](int from, int to, int base, int use_acc) {
+    int pp = 0;
+    lks::LevelRef in = level_ref(from, base, K);
+    in.par = pp;
+    for (int n = from; n < to;) {
+      const int m = std::min(b->multi.kf, to - n);
+      lks::MultiRefs lv = {};
+      for (int i = 0; i < m; ++i) {
+        lv.r[i] = level_ref(n + 1 + i, base, K);
+        lv.r[i].par = pp ^ 1;
+      }
+      lks::launch_lks_multi_ubatch<R>(F, St, b->d_tmap, b->total_tiles, th, b->multi.vf, m, in, lv,
+                                      n + 1, use_acc, s);
+      in = lv.r[m - 1];
+      n += m;
+      pp ^= 1;
+    }
+  };
   lks::launch_acc_zero_batch<R>(F, b->n, s);
-  for (int n = 0; n < N; ++n)
+  if (b->multi.kf) multi_sweep(0, N, ls, 1);
+  for (int n = 0; n < N && !b->multi.kf; ++n)
     lks::launch_lks_step_ubatch<R>(F, St, b->d_tmap, b->total_tiles, b->ty, th,
                                    level_ref(n, ls, K), level_ref(n + 1, ls, K), n + 1, 1, s);
   lks::launch_acc_sum_batch<R>(F, b->n, b->d_J, s);
@@ -2171,6 +2260,20 @@ void enqueue_batch_unsteady(lks_batch* b, bool adjoint, hipStream_t s) {
   int par = 0;
   for (int base = ls; base >= 0; base -= K) {
     const int top = base == ls ? N : base + K - 1;
+    if (b->multi.kf) {
+      if (base != ls) multi_sweep(base, top, base, 0);
+      for (int n = top; n >= base;) {
+        const int m = std::min(b->multi.ka, n - base + 1);
+        lks::MultiRefs lv = {};
+        for (int i = 0; i < m; ++i) lv.r[i] = level_ref(n - i, base, K);
+        lks::launch_alks_multi_ubatch<R>((base == ls && n == top) ? Aj + 2 * b->n : Aj, St,
+                                         b->d_tmap, b->total_tiles, th, b->multi.va, m, par, lv,
+                                         n - m + 1 == 0 ? m - 1 : -1, s);
+        n -= m;
+        par ^= 1;
+      }
+      continue;
+    }
     if (base != ls)
       for (int n = base; n < top; ++n)
         lks::launch_lks_step_ubatch<R>(F, St, b->d_tmap, b->total_tiles, b->ty, th,
@@ -2198,7 +2301,7 @@ void enqueue_batch(lks_batch* b, int nf, int na, hipStream_t s) {
 
 }  // namespace
 
-static lks_status batch_set_tile_rows(lks_batch* b, int ty);
+static lks_status batch_set_tile_rows(lks_batch* b, int ty, const lks::BatchPlan& multi);
 
 extern "C" {
 
@@ -2242,17 +2345,16 @@ lks_status lks_batch_create(int n, const lks_grid* grids, const lks_phys* phys, 
       return bfail(nullptr, st, "design " + std::to_string(d) + ": " + g_create_error);
     }
     b->ctx.push_back(c);
-    b->tile0.push_back(b->total_tiles);
-    b->total_tiles += n_tiles(c->geo);
     b->max_tiles += max_tiles(c->geo);
     b->maxN = std::max(b->maxN, size_t(c->geo.N));
     b->ty = c->geo.ty;
   }
   b->rsz = b->ctx[0]->rsz;
   b->thermal = phys[0].thermal ? 1 : 0;
+  batch_multi(b);
   if (b->unsteady) {
     // tile heights of the unsteady step launches: 4 and 8
-    if (b->ty == 16) batch_set_tile_rows(b, 8);
+    if (b->ty == 16) batch_set_tile_rows(b, 8, b->multi);
     lks_status st = plan_batch(b);  // no budget yet: every level kept
     if (st != LKS_OK) {
       g_create_error = b->err;
@@ -2460,8 +2562,8 @@ lks_status lks_batch_run(lks_batch* b, const double* const* gamma_dev, int n_fwd
     const double sj = b->unsteady ? Js[d] / b->n_steps : Js[d];
     if (c->objective == LKS_OBJ_PRESSURE_DROP) J_host[d] = (sj + double(c->n_in - c->n_out)) / 3.0;
     else J_host[d] = sj;
-    c->cur = n_fwd & 1;
-    c->acur = b->unsteady ? (n_fwd + 1) & 1 : n_adj & 1;
+    c->cur = launches(n_fwd, b->multi.kf) & 1;
+    c->acur = (b->unsteady ? adjoint_launches(b) : launches(n_adj, b->multi.ka)) & 1;
     c->last_level = n_fwd;
     c->have_forward = true;
     c->have_adjoint = n_adj > 0;
@@ -2472,13 +2574,12 @@ lks_status lks_batch_run(lks_batch* b, const double* const* gamma_dev, int n_fwd
   return LKS_OK;
 }
 
-static lks_status batch_set_tile_rows(lks_batch* b, int ty) {
-  b->total_tiles = 0;
-  for (int d = 0; d < b->n; ++d) {
-    set_tile_rows(b->ctx[d]->geo, ty);
-    b->tile0[d] = b->total_tiles;
-    b->total_tiles += n_tiles(b->ctx[d]->geo);
-  }
+// the tile height of the tile kernels and, in their place when multi.kf > 0,
+// the several-steps plan
+static lks_status batch_set_tile_rows(lks_batch* b, int ty, const lks::BatchPlan& multi) {
+  for (int d = 0; d < b->n; ++d) set_tile_rows(b->ctx[d]->geo, ty);
+  b->multi = multi;
+  batch_tiles(b);
   b->ty = ty;
   if (b->exec) {
     hipGraphExecDestroy(b->exec);
@@ -2511,28 +2612,33 @@ lks_status lks_batch_autotune(lks_batch* b, const double* const* gamma_dev, int 
   if (!hip_ok(nullptr, hipEventCreate(&e0), "event", &st) ||
       !hip_ok(nullptr, hipEventCreate(&e1), "event", &st))
     return bfail(b, st, g_create_error);
-  for (int ty : TILE_ROWS) {
-    if (!tile_rows_ok(ty, b->rsz, b->thermal)) continue;
-    if ((st = batch_set_tile_rows(b, ty)) != LKS_OK) break;
+  // the several-steps plan first (where it is in use), then each tile height
+  const lks::BatchPlan plan = b->multi;
+  lks::BatchPlan best_plan;
+  auto time_shape = [&](int ty, const lks::BatchPlan& p) {
+    if ((st = batch_set_tile_rows(b, ty, p)) != LKS_OK) return;
     float t = 0.0f;
     for (int rep = 0; rep < 2; ++rep) {
       hipEventRecord(e0, b->user);
       st = lks_batch_run(b, gamma_dev, steps, steps, 1.0, scratch_dev, J.data(), 0);
       hipEventRecord(e1, b->user);
-      if (st != LKS_OK) break;
+      if (st != LKS_OK) return;
       hipEventSynchronize(e1);
       hipEventElapsedTime(&t, e0, e1);
     }
-    if (st != LKS_OK) break;
     if (best == 0.0f || t < best) {
       best = t;
       best_ty = ty;
+      best_plan = p;
     }
-  }
+  };
+  if (plan.kf) time_shape(b->ty, plan);
+  for (int ty : TILE_ROWS)
+    if (st == LKS_OK && tile_rows_ok(ty, b->rsz, b->thermal)) time_shape(ty, lks::BatchPlan());
   hipEventDestroy(e0);
   hipEventDestroy(e1);
   if (st != LKS_OK) return st;
-  if ((st = batch_set_tile_rows(b, best_ty)) != LKS_OK) return st;
+  if ((st = batch_set_tile_rows(b, best_ty, best_plan)) != LKS_OK) return st;
   if (tile_rows) *tile_rows = best_ty;
   b->have_run = false;
   return LKS_OK;
@@ -2545,7 +2651,7 @@ lks_status lks_batch_set_tile_rows(lks_batch* b, int tile_rows) {
   if (!known || !tile_rows_ok(tile_rows, b->rsz, b->thermal) || (b->unsteady && tile_rows == 16))
     return bfail(b, LKS_E_INVALID,
                  "tile height must be 4 or 8 (or 16 for FP32 non-thermal steady batches)");
-  lks_status st = batch_set_tile_rows(b, tile_rows);
+  lks_status st = batch_set_tile_rows(b, tile_rows, lks::BatchPlan());
   if (st == LKS_OK) b->have_run = false;
   return st;
 }

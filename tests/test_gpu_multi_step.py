@@ -93,3 +93,63 @@ def test_periodic_box(nx, ny, prec):
     wl.gbeta, wl.T_ref = (0.0, 1e-4), 0.5
     wl.mode, wl.n_fwd, wl.n_adj, wl.ufac = W.MODE_UNSTEADY, 19, 19, np.ones(20)
     _same(wl, prec)
+
+
+def _batch(wls, prec, rows, n, m, **kw):
+    b = lks.Batch(wls, precision=prec, device=DEV, **kw)
+    if rows:
+        b.set_tile_rows(rows)
+    gs = [T(w.gamma) for w in wls]
+    outs = [torch.full_like(g, float("nan")) for g in gs]
+    runs = []
+    for graph in (True, True, False):  # captured, replayed, eager
+        J = b.run(gs, outs, n, m, graph=graph)
+        names = ["adj_rho", "adj_vx", "adj_vy"] + (["adj_theta"] if wls[0].thermal else [])
+        if wls[0].mode == W.MODE_STEADY:
+            names += ["drho", "ux", "uy"]
+        fields = [b.read(d, f).cpu().numpy() for d in range(len(wls)) for f in names]
+        runs.append((J, [o.cpu().numpy() for o in outs] + fields))
+    for J, x in runs[1:]:
+        assert J == runs[0][0]
+        assert all(np.array_equal(p, q) for p, q in zip(x, runs[0][1]))
+    return runs[0]
+
+
+# the first batch fits one round of the smallest tiles, the second takes the
+# tiles of several rounds
+BATCHES = [[(31, 31), (5, 4), (64, 40)], [(150, 131), (512, 300), (700, 513)]]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("sizes", BATCHES)
+def test_steady_batch(sizes, prec):
+    wls = [W.steady_channel_uniform(x, y, Re=20.0, seed=d, n_fwd=11, n_adj=10)
+           for d, (x, y) in enumerate(sizes)]
+    print(f"[gpu] steady batch {sizes} {prec}", flush=True)
+    J0, a = _batch(wls, prec, 4, 11, 10)
+    J1, b = _batch(wls, prec, None, 11, 10)
+    assert J0 == J1
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("mode", ["paper", "exact"])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("sizes", BATCHES)
+def test_unsteady_batch(sizes, prec, mode):
+    n = 23
+    wls = []
+    for d, (x, y) in enumerate(sizes):
+        w = W.unsteady_thermal_channel(x, y, Re=60.0, sigma=3.0, seed=d, n_steps=n, period=9.0)
+        w.mask = W.channel_mask(x, y, thermal=True, probe_col=2)
+        wls.append(w)
+    full = lks.Batch(wls, precision=prec, bind=False)
+    r = 8 if prec == "fp64" else 4
+    # room for about half of the levels: checkpoints and replayed segments
+    budget = full.workspace_size() - int(0.5 * n * 3 * r * sum(w.n_nodes for w in wls))
+    print(f"[gpu] unsteady batch {sizes} {prec} {mode}", flush=True)
+    kw = dict(mem_budget=budget, adjoint_mode=mode)
+    J0, a = _batch(wls, prec, 4, n, n, **kw)
+    J1, b = _batch(wls, prec, None, n, n, **kw)
+    # the objective sums the same terms in another order
+    assert all(abs(x - y) <= 1e-13 * max(abs(x), 1e-3) for x, y in zip(J0, J1))
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
