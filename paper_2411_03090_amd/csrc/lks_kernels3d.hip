@@ -201,8 +201,6 @@ constexpr int SX = ZX + 4, NSR = SX * (ZY + 4);    // tile + 2-node halo
 constexpr int CXN = ZX + 2, NCR = CXN * (ZY + 2);  // tile + 1-node halo
 constexpr int SRL = (NSR + ZT - 1) / ZT;           // halo-region loads per thread
 static_assert(ZT == NT3, "one block size for the 3D kernels");
-// the directions with an x or y component: their values cross columns
-__device__ constexpr int LQ[16] = {1, 2, 3, 4, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18};
 
 __host__ __device__ inline int zchunks(const Geo3& g) {
   const int zc = g.zc < 2 ? 2 : g.zc;
@@ -327,26 +325,14 @@ __device__ inline void zregion(const Geo3& g, const ZTile& t, int off[SRL]) {
 
 // one plane of NF fields over the thread's region elements (zero where the
 // plane or the node does not exist)
-// (SEL: elements off the domain or of a missing plane load the field's first
-// node and keep zero, with no per-element branches; the LKS step gains by it,
-// the ALKS march, whose loads wait longer, does not)
-template <typename R, int NF, bool SEL = false>
+template <typename R, int NF>
 __device__ inline void zload(const R* const F[NF], bool exists, unsigned base, const int off[SRL],
                              R v[SRL][NF]) {
 #pragma unroll
   for (int r = 0; r < SRL; ++r) {
     const bool in = exists && off[r] >= 0;
-    if constexpr (SEL) {
-      const unsigned o = in ? base + unsigned(off[r]) : 0u;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const R x = F[f][o];
-        v[r][f] = in ? x : R(0);
-      }
-    } else {
-#pragma unroll
-      for (int f = 0; f < NF; ++f) v[r][f] = in ? F[f][base + unsigned(off[r])] : R(0);
-    }
+    for (int f = 0; f < NF; ++f) v[r][f] = in ? F[f][base + unsigned(off[r])] : R(0);
   }
 }
 template <typename R, int NF>
@@ -382,67 +368,49 @@ __device__ inline R d1p(const R* f, const R* h, int i, int st, int e) {
 // ---------------------------------------------------------------------------
 // Per plane s of the march, every column of the tile and its ring forms the
 // coefficients a0 = drho - 3/2 u.u, P = 9/2 u u + A (grad u + grad u^T),
-// G = 3 T u + B grad T and the 19 equilibria f'_q = w_q [a0 + 3 c.u + c.P.c],
-// g_q = w_q [T + c.G] of its node (eq:feq2, eq:geq2). The values with an x or
-// y component go through LDS to the column they stream to; every column adds
-// what it receives from plane s to the moments of planes s - 1, s, s + 1 that
-// it keeps in registers (the pull of f_i^eq(x - c_i)). Plane s - 1 is then
-// complete. A source off the domain sends zeros, so a face node's sums over
-// the directions it receives are rho + sg (c_n . f) with n its normal.
+// G = 3 T u + B grad T of its node (eq:feq2, eq:geq2), all times w = 1/36, and
+// leaves in LDS what its neighbours need of them. A column then forms the
+// values f'_q = w_q [a0 + 3 c.u + c.P.c], g_q = w_q [T + c.G] that reach it from
+// the nine columns x - c_q and adds them to the moments of the planes s - 1, s,
+// s + 1 that it keeps in registers (the pull of f_i^eq(x - c_i)). Plane s - 1 is
+// then complete. The three values that an in-plane neighbour e sends to the
+// planes s and s +- 1 are 2 b, E + O, E - O (units of w) with
+//   b = a0 + c.P.c + 3 c.u along e,  E = b + Pzz,  O = 3 uz + 2 c.P.ez,
+// so the sums of a plane need 2 b, E and O of four neighbours and one value of
+// each of the four diagonal ones; all that arrives from below has c_z = 1, so
+// its u_z sum is its density sum. A source off the domain leaves zeros, so a
+// face node's sums over the directions it receives are rho + sg (c_n . f) with
+// n its normal.
+// Bound by instructions. Forming all 19 values at the source and sending each
+// behind a test of its target, with a branch for each difference, took 135 us
+// on 256 x 128 x 128 in FP32 and 74 us on 97 x 61 x 53 in FP64; this way it is
+// 76 and 41 us (172 MB of FP32 traffic, 28 us at the rate of a copy).
+template <typename R>
+struct alignas(2 * sizeof(R)) V2 {
+  R x, y;
+};
+template <typename R>
+struct alignas(16) V4 {
+  R x, y, z, w;
+};
 template <typename R, bool TH>
 struct FwdZLds {
-  R st[2][TH ? 4 : 3][NSR];  // u (3), T of planes s and s + 1
-  R fq[16][ZT];              // f'_q arriving at each column
-  // T and G = 3 T u + B grad T of every column of the tile and its ring (1-node
-  // halo region): a column forms the g_q = w_q (T + c_q.G) it receives itself
-  R tg[TH ? 4 : 1][TH ? NCR : 1];
+  V4<R> st[2][NSR];  // u, T of planes s and s + 1
+  // coefficients of the columns of the tile and its ring (1-node halo region):
+  // 3 uz, Pzz, T, Gz; a0 + Pxx, 2 Pxz; a0 + Pyy, 2 Pyz; a0 + Pxx + Pyy, 2 Pxy;
+  // 3 ux, Gx; 3 uy, Gy
+  V4<R> z[NCR];
+  V2<R> fx[NCR], fy[NCR], fd[NCR], gx[NCR], gy[NCR];
   double red[ZT / 64];
 };
 
-// moments of three planes (s - 1, s, s + 1) of a column
+// moments of a column: planes s - 1 (complete but for what arrives from above)
+// and s; the part of U_z from below is a density sum
 template <typename R, bool TH>
 struct FwdAcc {
-  R r[3], U[3][3], T[3], Q[3][3];
+  R r0, r1, Ux0, Ux1, Uy0, Uy1, Uz0, Uz1;
+  R T0, T1, Qx0, Qx1, Qy0, Qy1, Qz0, Qz1;
 };
-
-template <typename R, bool TH>
-__device__ inline void facc_add(FwdAcc<R, TH>& A, int q, R f, R gv) {
-  const int sl = QZ[q] + 1;
-  A.r[sl] += f;
-  if (QX[q]) A.U[sl][0] += R(QX[q]) * f;
-  if (QY[q]) A.U[sl][1] += R(QY[q]) * f;
-  if (QZ[q]) A.U[sl][2] += R(QZ[q]) * f;
-  if constexpr (TH) {
-    A.T[sl] += gv;
-    if (QX[q]) A.Q[sl][0] += R(QX[q]) * gv;
-    if (QY[q]) A.Q[sl][1] += R(QY[q]) * gv;
-    if (QZ[q]) A.Q[sl][2] += R(QZ[q]) * gv;
-  }
-}
-
-template <typename R, bool TH>
-__device__ inline void facc_shift(FwdAcc<R, TH>& A) {
-  A.r[0] = A.r[1];
-  A.r[1] = A.r[2];
-  A.r[2] = R(0);
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    A.U[0][c] = A.U[1][c];
-    A.U[1][c] = A.U[2][c];
-    A.U[2][c] = R(0);
-  }
-  if constexpr (TH) {
-    A.T[0] = A.T[1];
-    A.T[1] = A.T[2];
-    A.T[2] = R(0);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      A.Q[0][c] = A.Q[1][c];
-      A.Q[1][c] = A.Q[2][c];
-      A.Q[2][c] = R(0);
-    }
-  }
-}
 
 // z difference of a field at plane s from its values at s - 1 (zp), s (fc)
 // and s + 1 (zn); z2 is plane 2 (low end) or nz - 3 (high end)
@@ -453,96 +421,156 @@ __device__ inline R dz3(int ez, R fc, R zp, R zn, R z2) {
   return R(0.5) * (zn - zp);
 }
 
-// equilibria of the node of column n at plane sw, sent to the columns they
-// stream to; the own column keeps its c = 0 and c = +-e_z values. zp holds
-// u and T of plane sw - 1 and is advanced to plane sw.
-template <typename R, bool TH, bool OWN>
+// the node of a uniform plane pointer at byte offset o
+template <typename T>
+__device__ inline T at_b(const T* p, unsigned o) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + o);
+}
+
+// x, formed anew by every loop iteration that uses it: without this the
+// compiler keeps an address per field and column across the march (24 registers
+// and then spills)
+__device__ inline unsigned anew(unsigned x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// values of a source column that stay with it
+template <typename R>
+struct FwdOwn {
+  R A, Pzz, Uz, T, Gz;
+};
+
+// coefficients of the node of column n at plane sw, left in LDS. zp holds u and
+// T of plane sw - 1 and is advanced to plane sw.
+template <typename R, bool TH>
 __device__ inline void fwd_src(const Geo3& g, const Fwd3Args<R>& a, FwdZLds<R, TH>& L,
-                               const ZTile& t, const ZNode& n, int cur, int nxt, bool hn, int sw,
-                               unsigned nxy, R dk, R Bk, R zp[4], FwdAcc<R, TH>& A) {
-  if (!n.on) return;
-  R fv[19], gv[19];
-  R tgv[4] = {R(0), R(0), R(0), R(0)};
-  if (n.off < 0) {
-#pragma unroll
-    for (int q = 0; q < 19; ++q) fv[q] = gv[q] = R(0);
-  } else {
-    const int i = n.lds;
-    const int ez = endof(sw, g.nz, g.periodic & 4);
-    R u[3], zn[4] = {R(0), R(0), R(0), R(0)}, z2[4] = {R(0), R(0), R(0), R(0)};
-    constexpr int NZ = TH ? 4 : 3;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) u[c] = L.st[cur][c][i];
-    const R T = TH ? L.st[cur][TH ? 3 : 0][i] : R(0);
-    if (hn)
-#pragma unroll
-      for (int c = 0; c < NZ; ++c) zn[c] = L.st[nxt][c][i];
-    if (ez) {
-      const unsigned b2 = unsigned(ez < 0 ? 2 : g.nz - 3) * nxy + unsigned(n.off);
-#pragma unroll
-      for (int c = 0; c < NZ; ++c) z2[c] = a.s0[1 + c][b2];
-    }
-    R G[3][3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      G[c][0] = d1(L.st[cur][c], i, 1, n.ex);
-      G[c][1] = d1(L.st[cur][c], i, SX, n.ey);
-      G[c][2] = dz3(ez, u[c], zp[c], zn[c], z2[c]);
-    }
-    const R A_ = R(g.A);
-    const R uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const R a0 = dk - R(1.5) * uu;
-    R P[6];
-#pragma unroll
-    for (int x = 0; x < 3; ++x)
-#pragma unroll
-      for (int y = x; y < 3; ++y) P[SI[x][y]] = R(4.5) * u[x] * u[y] + A_ * (G[x][y] + G[y][x]);
-    R Gt[3] = {R(0), R(0), R(0)};
-    if constexpr (TH) {
-      const R dT[3] = {d1(L.st[cur][TH ? 3 : 0], i, 1, n.ex), d1(L.st[cur][TH ? 3 : 0], i, SX, n.ey),
-                       dz3(ez, T, zp[3], zn[3], z2[3])};
-#pragma unroll
-      for (int c = 0; c < 3; ++c) Gt[c] = R(3) * T * u[c] + Bk * dT[c];
-      zp[3] = T;
-      tgv[0] = T;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) tgv[1 + c] = Gt[c];
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) zp[c] = u[c];
-#pragma unroll
-    for (int q = 0; q < 19; ++q) {
-      const int cq[3] = {QX[q], QY[q], QZ[q]};
-      R cu = R(0), cpc = R(0), cg = R(0);
-#pragma unroll
-      for (int x = 0; x < 3; ++x) {
-        if (!cq[x]) continue;
-        cu += R(cq[x]) * u[x];
-        cpc += P[SI[x][x]];
-#pragma unroll
-        for (int y = x + 1; y < 3; ++y)
-          if (cq[y]) cpc += R(2 * cq[x] * cq[y]) * P[SI[x][y]];
-        if constexpr (TH) cg += R(cq[x]) * Gt[x];
-      }
-      fv[q] = R(QW[q]) * (a0 + R(3) * cu + cpc);
-      gv[q] = TH ? R(QW[q]) * (T + cg) : R(0);
-    }
+                               const ZNode& n, int cur, int sw, size_t nxy, R dk, R Bk, V4<R>& zp,
+                               FwdOwn<R>& o) {
+  const int i = n.lds;
+  const int ez = endof(sw, g.nz, g.periodic & 4);
+  const V4<R> c = L.st[cur][i], zn = L.st[cur ^ 1][i];
+  const V4<R> xp = L.st[cur][i + 1], xm = L.st[cur][i - 1];
+  const V4<R> yp = L.st[cur][i + SX], ym = L.st[cur][i - SX];
+  auto cen = [](const V4<R>& p, const V4<R>& m) {
+    return V4<R>{R(0.5) * (p.x - m.x), R(0.5) * (p.y - m.y), R(0.5) * (p.z - m.z),
+                 TH ? R(0.5) * (p.w - m.w) : R(0)};
+  };
+  // second-order one-sided difference, f1 and f2 one and two steps inwards of
+  // the low (e < 0) or high end
+  auto one = [](int e, const V4<R>& f, const V4<R>& f1, const V4<R>& f2) {
+    const R h = e < 0 ? R(-0.5) : R(0.5);
+    return V4<R>{h * (R(3) * f.x - R(4) * f1.x + f2.x), h * (R(3) * f.y - R(4) * f1.y + f2.y),
+                 h * (R(3) * f.z - R(4) * f1.z + f2.z),
+                 TH ? h * (R(3) * f.w - R(4) * f1.w + f2.w) : R(0)};
+  };
+  V4<R> dx = cen(xp, xm), dy = cen(yp, ym), dz = cen(zn, zp);
+  if (n.ex) dx = one(n.ex, c, L.st[cur][i - n.ex], L.st[cur][i - 2 * n.ex]);
+  if (n.ey) dy = one(n.ey, c, L.st[cur][i - n.ey * SX], L.st[cur][i - 2 * n.ey * SX]);
+  if (ez) {
+    const size_t b2 = size_t(ez < 0 ? 2 : g.nz - 3) * nxy;
+    const unsigned ob = anew(unsigned(n.off)) * unsigned(sizeof(R));
+    const V4<R> z2{at_b(a.s0[1] + b2, ob), at_b(a.s0[2] + b2, ob), at_b(a.s0[3] + b2, ob),
+                   TH ? at_b(a.s0[4] + b2, ob) : R(0)};
+    dz = one(ez, c, ez < 0 ? zn : zp, z2);
   }
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int q = LQ[j];
-    const int px = n.dx + QX[q], py = n.dy + QY[q];
-    if (px >= 0 && px < t.w && py >= 0 && py < t.h) {
-      L.fq[j][py * ZX + px] = fv[q];
-    }
+  zp = c;
+  const R w = R(1.0 / 36), A2 = R(g.A / 18.0);
+  const R A = w * (dk - R(1.5) * (c.x * c.x + c.y * c.y + c.z * c.z));
+  const R h = R(0.125) * c.x;  // 9/2 w ux
+  const R hy = R(0.125) * c.y, hz = R(0.125) * c.z;
+  const R Pxx = h * c.x + A2 * dx.x, Pyy = hy * c.y + A2 * dy.y, Pzz = hz * c.z + A2 * dz.z;
+  const R Pxy = R(2) * h * c.y + A2 * (dx.y + dy.x);
+  const R Pxz = R(2) * h * c.z + A2 * (dx.z + dz.x);
+  const R Pyz = R(2) * hy * c.z + A2 * (dy.z + dz.y);
+  const R U = R(1.0 / 12);
+  o.A = A;
+  o.Pzz = Pzz;
+  o.Uz = U * c.z;
+  o.T = o.Gz = R(0);
+  R Gx = R(0), Gy = R(0);
+  if constexpr (TH) {
+    const R t = U * c.w, b = w * Bk;
+    o.T = w * c.w;
+    Gx = t * c.x + b * dx.w;
+    Gy = t * c.y + b * dy.w;
+    o.Gz = t * c.z + b * dz.w;
   }
-  if constexpr (TH)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) L.tg[c][n.ci] = tgv[c];
-  if constexpr (OWN) {
-    facc_add(A, 0, fv[0], gv[0]);
-    facc_add(A, 5, fv[5], gv[5]);
-    facc_add(A, 6, fv[6], gv[6]);
+  const R axx = A + Pxx;
+  const int ci = n.ci;
+  L.z[ci] = V4<R>{o.Uz, Pzz, o.T, o.Gz};
+  L.fx[ci] = V2<R>{axx, Pxz};
+  L.fy[ci] = V2<R>{A + Pyy, Pyz};
+  L.fd[ci] = V2<R>{axx + Pyy, Pxy};
+  L.gx[ci] = V2<R>{U * c.x, Gx};
+  L.gy[ci] = V2<R>{U * c.y, Gy};
+}
+
+// what column ci receives from plane s, added to its moments; the moments of
+// plane s - 1 are then complete in A.*0
+template <typename R, bool TH>
+__device__ inline void fwd_recv(const FwdZLds<R, TH>& L, int ci, const FwdOwn<R>& o,
+                                FwdAcc<R, TH>& A, R& r2, R& x2, R& y2, R& t2, R& qx2, R& qy2) {
+  // neighbours that send along +x, -x, +y, -y
+  const V4<R> zl = L.z[ci - 1], zr = L.z[ci + 1], zd = L.z[ci - CXN], zu = L.z[ci + CXN];
+  const V2<R> fl = L.fx[ci - 1], fr = L.fx[ci + 1], fd = L.fy[ci - CXN], fu = L.fy[ci + CXN];
+  const V2<R> gl = L.gx[ci - 1], gr = L.gx[ci + 1], gd = L.gy[ci - CXN], gu = L.gy[ci + CXN];
+  const R bl = fl.x + gl.x, br = fr.x - gr.x, bd = fd.x + gd.x, bu = fu.x - gu.x;
+  const R El = bl + zl.y, Er = br + zr.y, Ed = bd + zd.y, Eu = bu + zu.y;
+  const R Ol = zl.x + fl.y, Or = zr.x - fr.y, Od = zd.x + fd.y, Ou = zu.x - fu.y;
+  const R e = R(2) * (o.A + o.Pzz) + ((El + Er) + (Ed + Eu));
+  const R od = R(2) * o.Uz + ((Ol + Or) + (Od + Ou));
+  const R ex = El - Er, ey = Ed - Eu, ox = Ol - Or, oy = Od - Ou;
+  r2 = e + od;
+  x2 = ex + ox;
+  y2 = ey + oy;
+  const R rz = e - od;
+  A.r0 += rz;
+  A.Uz0 -= rz;
+  A.Ux0 += ex - ox;
+  A.Uy0 += ey - oy;
+  A.r1 += R(12) * o.A + R(2) * ((bl + br) + (bd + bu));
+  A.Ux1 += R(2) * (bl - br);
+  A.Uy1 += R(2) * (bd - bu);
+  if constexpr (TH) {
+    const R hl = zl.z + gl.y, hr = zr.z - gr.y, hd = zd.z + gd.y, hu = zu.z - gu.y;
+    const R hs = (hl + hr) + (hd + hu), hx = hl - hr, hy = hd - hu;
+    const R Z = R(2) * o.Gz + ((zl.w + zr.w) + (zd.w + zu.w)), S = R(2) * o.T + hs;
+    const R gx = zl.w - zr.w, gy = zd.w - zu.w;
+    t2 = S + Z;
+    qx2 = hx + gx;
+    qy2 = hy + gy;
+    const R tz = S - Z;
+    A.T0 += tz;
+    A.Qz0 -= tz;
+    A.Qx0 += hx - gx;
+    A.Qy0 += hy - gy;
+    A.T1 += R(12) * o.T + R(2) * hs;
+    A.Qx1 += R(2) * hx;
+    A.Qy1 += R(2) * hy;
+  }
+  // (the reads below wait: all of them at once cost a wave per SIMD)
+  __builtin_amdgcn_sched_barrier(0);
+  // diagonal neighbours that send along ++, --, +-, -+
+  const int c1 = ci - CXN - 1, c2 = ci + CXN + 1, c3 = ci + CXN - 1, c4 = ci - CXN + 1;
+  const V2<R> d1 = L.fd[c1], d2 = L.fd[c2], d3 = L.fd[c3], d4 = L.fd[c4];
+  const V2<R> x1 = L.gx[c1], x2_ = L.gx[c2], x3 = L.gx[c3], x4 = L.gx[c4];
+  const V2<R> y1 = L.gy[c1], y2_ = L.gy[c2], y3 = L.gy[c3], y4 = L.gy[c4];
+  {
+    const R F1 = (d1.x + d1.y) + (x1.x + y1.x), F2 = (d2.x + d2.y) - (x2_.x + y2_.x);
+    const R F3 = (d3.x - d3.y) + (x3.x - y3.x), F4 = (d4.x - d4.y) - (x4.x - y4.x);
+    const R p = F1 - F2, m = F3 - F4;
+    A.r1 += (F1 + F2) + (F3 + F4);
+    A.Ux1 += p + m;
+    A.Uy1 += p - m;
+  }
+  if constexpr (TH) {
+    const R F1 = L.z[c1].z + (x1.y + y1.y), F2 = L.z[c2].z - (x2_.y + y2_.y);
+    const R F3 = L.z[c3].z + (x3.y - y3.y), F4 = L.z[c4].z - (x4.y - y4.y);
+    const R p = F1 - F2, m = F3 - F4;
+    A.T1 += (F1 + F2) + (F3 + F4);
+    A.Qx1 += p + m;
+    A.Qy1 += p - m;
   }
 }
 
@@ -556,9 +584,10 @@ __device__ inline R pick3(int ax, R v0, R v1, R v2) {
 // division inside, the velocity / pressure closures and the temperature
 // closure on faces; edge and corner nodes are copied afterwards
 template <typename R, bool TH>
-__device__ inline void fwd3_out(const Geo3& g, const Fwd3Args<R>& a, unsigned k, int ex, int ey,
-                                int ez, int m, R s, R Tb, const R ubk[3], double fac, R rho,
-                                const R U[3], R Ts, const R Q[3], double& part) {
+__device__ inline void fwd3_out(const Geo3& g, const Fwd3Args<R>& a, size_t plane, unsigned off,
+                                int ex, int ey, int ez, int m, R s, R Tb, const R ubk[3],
+                                double fac, R rho, const R U[3], R Ts, const R Q[3],
+                                double& part) {
   const int ne = (ex != 0) + (ey != 0) + (ez != 0);
   if (ne >= 2) return;
   R d, u[3], T = R(0);
@@ -594,11 +623,15 @@ __device__ inline void fwd3_out(const Geo3& g, const Fwd3Args<R>& a, unsigned k,
       else T = (Ts + R(sg) * Qn + Tb) / (R(1) + un);
     }
   }
-  a.s1[0][k] = d;
-  a.s1[1][k] = u[0];
-  a.s1[2][k] = u[1];
-  a.s1[3][k] = u[2];
-  if constexpr (TH) a.s1[4][k] = T;
+  const unsigned ob = off * unsigned(sizeof(R));
+  auto put = [&](R* f, R x) {
+    *reinterpret_cast<R*>(reinterpret_cast<char*>(f + plane) + ob) = x;
+  };
+  put(a.s1[0], d);
+  put(a.s1[1], u[0]);
+  put(a.s1[2], u[1]);
+  put(a.s1[3], u[2]);
+  if constexpr (TH) put(a.s1[4], T);
   if (a.acc) {
     if (a.objective == 1) {
       if (m & TAG_PROBE3) part += double(u[0]) * double(T);
@@ -610,119 +643,158 @@ __device__ inline void fwd3_out(const Geo3& g, const Fwd3Args<R>& a, unsigned k,
 }
 
 template <typename R, bool TH>
-__global__ __launch_bounds__(ZT) void lks3z_kernel(Geo3 g, Fwd3Args<R> a) {
-  constexpr int NF = TH ? 4 : 3;  // u (3), T in the LDS ring
+__global__ __launch_bounds__(ZT, sizeof(R) == 4 ? 4 : 2) void lks3z_kernel(Geo3 g, Fwd3Args<R> a) {
   __shared__ FwdZLds<R, TH> L;
   ZTile t;
   if (!ztile(g, t)) return;
   const int tid = int(threadIdx.x), lx = tid % ZX, ly = tid / ZX;
   const int pz = g.periodic & 4;
-  const unsigned nxy = unsigned(g.nx) * unsigned(g.ny);
-  int roff[SRL];
-  zregion(g, t, roff);
-  const ZNode n0 = znode(g, t, lx, ly, lx < t.w && ly < t.h);
-  const ZNode n1 = zring(g, t);
+  const size_t nxy = size_t(g.nx) * size_t(g.ny);
+  // byte offsets in a plane of the thread's elements of the 2-node halo region;
+  // an element off the domain reads the plane's first node, which nothing uses
+  unsigned roff[SRL];
+  {
+    int off[SRL];
+    zregion(g, t, off);
+#pragma unroll
+    for (int r = 0; r < SRL; ++r)
+      roff[r] = off[r] < 0 ? 0u : unsigned(off[r]) * unsigned(sizeof(R));
+  }
+  ZNode n0 = znode(g, t, lx, ly, lx < t.w && ly < t.h);
+  ZNode n1 = zring(g, t);
+  n1.on = n1.on && n1.off >= 0;
   const bool own = n0.on && t.x0 + lx >= t.xo && t.y0 + ly >= t.yo;
+  unsigned ob0 = unsigned(n0.off) * unsigned(sizeof(R));
+  unsigned ob1 = unsigned(n1.off) * unsigned(sizeof(R));
+  // columns off the domain send nothing: their entries stay zero
+  for (int e = tid; e < NCR; e += ZT) {
+    L.z[e] = V4<R>{R(0), R(0), R(0), R(0)};
+    L.fx[e] = L.fy[e] = L.fd[e] = L.gx[e] = L.gy[e] = V2<R>{R(0), R(0)};
+  }
   // source planes: one beyond the output range on each side where it exists
   const int sb = (t.z0 == 0 && !pz) ? 0 : t.z0 - 1;
   const int se = (t.z1 == g.nz && !pz) ? g.nz - 1 : t.z1;
-  const R* F[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) F[f] = a.s0[1 + f];
-  R v[SRL][NF];
-  zload<R, NF, true>(F, true, unsigned(zwrap(sb, g.nz)) * nxy, roff, v);
-  zstore<R, NF>(L.st[0], v);
   auto has = [&](int s) { return pz || (s >= 0 && s < g.nz); };
-  if (has(sb + 1)) zload<R, NF, true>(F, true, unsigned(zwrap(sb + 1, g.nz)) * nxy, roff, v);
-  R zp0[4] = {R(0), R(0), R(0), R(0)}, zp1[4] = {R(0), R(0), R(0), R(0)};
-  if (has(sb - 1)) {
-    const unsigned b = unsigned(zwrap(sb - 1, g.nz)) * nxy;
+  auto plane = [&](int s) { return size_t(zwrap(s, g.nz)) * nxy; };
+  V4<R> v[SRL];
+  auto load = [&](int s) {
+    const size_t b = plane(s);
+    const R *F1 = a.s0[1] + b, *F2 = a.s0[2] + b, *F3 = a.s0[3] + b;
+    const R* F4 = TH ? a.s0[4] + b : F1;
 #pragma unroll
-    for (int c = 0; c < NF; ++c) {
-      if (n0.on && n0.off >= 0) zp0[c] = F[c][b + unsigned(n0.off)];
-      if (n1.on && n1.off >= 0) zp1[c] = F[c][b + unsigned(n1.off)];
-    }
+    for (int r = 0; r < SRL; ++r)
+      if ((r + 1) * ZT <= NSR || tid + r * ZT < NSR) {
+        v[r].x = at_b(F1, roff[r]);
+        v[r].y = at_b(F2, roff[r]);
+        v[r].z = at_b(F3, roff[r]);
+        v[r].w = TH ? at_b(F4, roff[r]) : R(0);
+      }
+  };
+  auto store = [&](int slot) {
+#pragma unroll
+    for (int r = 0; r < SRL; ++r)
+      if ((r + 1) * ZT <= NSR || tid + r * ZT < NSR) L.st[slot][tid + r * ZT] = v[r];
+  };
+  auto zload = [&](int s, unsigned ob) {
+    const size_t b = plane(s);
+    return V4<R>{at_b(a.s0[1] + b, ob), at_b(a.s0[2] + b, ob), at_b(a.s0[3] + b, ob),
+                 TH ? at_b(a.s0[4] + b, ob) : R(0)};
+  };
+  load(sb);
+  store(0);
+  if (has(sb + 1)) load(sb + 1);
+  V4<R> zp0{R(0), R(0), R(0), R(0)}, zp1 = zp0;
+  if (has(sb - 1)) {
+    if (n0.on) zp0 = zload(sb - 1, ob0);
+    if (n1.on) zp1 = zload(sb - 1, ob1);
   }
   // per-node inputs one iteration ahead: drho and B of the source nodes,
-  // class, Brinkman factor and prescribed temperature of the output node
-  // the prescribed velocity of a velocity face node is read with the rest,
-  // a plane ahead, and the level's inflow factor once
+  // class, Brinkman factor and prescribed temperature of the output node; the
+  // prescribed velocity of a velocity face node is read with the rest (not
+  // waiting for its class), and the level's inflow factor once
   const double fac = a.ufac[a.level_out];
-  auto node_in = [&](int s, R& d0, R& d1_, R& b0, R& b1, int& mk, R& ip, R& tb, R ub[3]) {
-    d0 = d1_ = b0 = b1 = ip = tb = R(0);
-    ub[0] = ub[1] = ub[2] = R(0);
-    mk = 0;
-    if (!has(s)) return;
-    const unsigned base = unsigned(zwrap(s, g.nz)) * nxy;
-    if (n0.on && n0.off >= 0) {
-      d0 = a.s0[0][base + unsigned(n0.off)];
-      if constexpr (TH) b0 = a.B[base + unsigned(n0.off)];
+  R dd0, dd1, b0 = R(0), b1 = R(0), ip, tb = R(0), ub[3];
+  int mk;
+  auto node_in = [&](int s) {
+    const size_t b = plane(s);
+    dd0 = dd1 = R(0);
+    if (n0.on) {
+      dd0 = at_b(a.s0[0] + b, ob0);
+      if constexpr (TH) b0 = at_b(a.B + b, ob0);
     }
-    if (n1.on && n1.off >= 0) {
-      d1_ = a.s0[0][base + unsigned(n1.off)];
-      if constexpr (TH) b1 = a.B[base + unsigned(n1.off)];
+    if (n1.on) {
+      dd1 = at_b(a.s0[0] + b, ob1);
+      if constexpr (TH) b1 = at_b(a.B + b, ob1);
     }
     const int p = s - 1;
-    if (own && p >= t.z0 && p < t.z1) {
-      const unsigned k = unsigned(p) * nxy + unsigned(n0.off);
-      mk = a.mask[k];
-      ip = a.inv1pa[k];
-      if constexpr (TH) tb = a.Tb[k];
-      if (n0.ex || n0.ey || endof(p, g.nz, pz))  // a face node (not waiting for its class)
+    mk = 0;
+    ip = ub[0] = ub[1] = ub[2] = R(0);
+    if (p >= t.z0 && own) {
+      const size_t q = size_t(p) * nxy;
+      mk = at_b(a.mask + q, unsigned(n0.off));
+      ip = at_b(a.inv1pa + q, ob0);
+      if constexpr (TH) tb = at_b(a.Tb + q, ob0);
+      if (n0.ex || n0.ey || endof(p, g.nz, pz))
 #pragma unroll
-        for (int x = 0; x < 3; ++x) ub[x] = a.ub[x][k];
+        for (int x = 0; x < 3; ++x) ub[x] = at_b(a.ub[x] + q, ob0);
     }
   };
-  R dd0, dd1, b0, b1, ip, tb, ub[3];
-  int mk;
-  node_in(sb, dd0, dd1, b0, b1, mk, ip, tb, ub);
+  node_in(sb);
   FwdAcc<R, TH> A = {};
   double part = 0.0;
   for (int s = sb; s <= se; ++s) {
-    const int it = s - sb, cur = it & 1, nxt = cur ^ 1;
-    const bool hn = has(s + 1);
-    if (hn) zstore<R, NF>(L.st[nxt], v);
+    const int cur = (s - sb) & 1;
+    ob0 = anew(ob0);
+    ob1 = anew(ob1);
+    n0.off = int(anew(unsigned(n0.off)));
+    n1.lds = int(anew(unsigned(n1.lds)));
+    n0.lds = int(anew(unsigned(n0.lds)));
+#pragma unroll
+    for (int r = 0; r < SRL; ++r) roff[r] = anew(roff[r]);
+    if (has(s + 1)) store(cur ^ 1);
     lds_barrier();
-    if (has(s + 2)) zload<R, NF, true>(F, true, unsigned(zwrap(s + 2, g.nz)) * nxy, roff, v);
+    if (has(s + 2)) load(s + 2);
     const R cd0 = dd0, cd1 = dd1, cb0 = b0, cb1 = b1, cip = ip, ctb = tb;
     const R cub[3] = {ub[0], ub[1], ub[2]};
     const int cmk = mk;
-    if (s + 1 <= se) node_in(s + 1, dd0, dd1, b0, b1, mk, ip, tb, ub);
+    if (s + 1 <= se) node_in(s + 1);
     const int sw = zwrap(s, g.nz);
-    fwd_src<R, TH, true>(g, a, L, t, n0, cur, nxt, hn, sw, nxy, cd0, cb0, zp0, A);
-    fwd_src<R, TH, false>(g, a, L, t, n1, cur, nxt, hn, sw, nxy, cd1, cb1, zp1, A);
+    FwdOwn<R> own_v, ring_v;
+    if (n1.on) fwd_src<R, TH>(g, a, L, n1, cur, sw, nxy, cd1, cb1, zp1, ring_v);
+    if (n0.on) fwd_src<R, TH>(g, a, L, n0, cur, sw, nxy, cd0, cb0, zp0, own_v);
     lds_barrier();
-    if (n0.on) {
-      const int me = ly * ZX + lx;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int q = LQ[j];
-        R gv = R(0);
-        if constexpr (TH) {
-          // g_q of the source column x - c_q, summed as at the source
-          const int src = (ly - QY[q] + 1) * CXN + (lx - QX[q] + 1);
-          const int cq[3] = {QX[q], QY[q], QZ[q]};
-          R cg = R(0);
-#pragma unroll
-          for (int x = 0; x < 3; ++x)
-            if (cq[x]) cg += R(cq[x]) * L.tg[1 + x][src];
-          gv = R(QW[q]) * (L.tg[0][src] + cg);
-        }
-        facc_add(A, q, L.fq[j][me], gv);
-      }
-    }
+    R r2 = R(0), x2 = R(0), y2 = R(0), t2 = R(0), qx2 = R(0), qy2 = R(0);
+    if (n0.on) fwd_recv<R, TH>(L, n0.ci, own_v, A, r2, x2, y2, t2, qx2, qy2);
     const int p = s - 1;
-    if (own && p >= t.z0 && p < t.z1)
-      fwd3_out<R, TH>(g, a, unsigned(p) * nxy + unsigned(n0.off), n0.ex, n0.ey,
-                      endof(p, g.nz, pz), cmk, cip, ctb, cub, fac, A.r[0], A.U[0], A.T[0],
-                      A.Q[0], part);
-    facc_shift(A);
+    if (own && p >= t.z0 && p < t.z1) {
+      const R U[3] = {A.Ux0, A.Uy0, A.Uz0}, Q[3] = {A.Qx0, A.Qy0, A.Qz0};
+      fwd3_out<R, TH>(g, a, size_t(p) * nxy, unsigned(n0.off), n0.ex, n0.ey, endof(p, g.nz, pz),
+                      cmk, cip, ctb, cub, fac, A.r0, U, A.T0, Q, part);
+    }
+    A.r0 = A.r1;
+    A.Ux0 = A.Ux1;
+    A.Uy0 = A.Uy1;
+    A.Uz0 = A.Uz1;
+    A.r1 = A.Uz1 = r2;
+    A.Ux1 = x2;
+    A.Uy1 = y2;
+    if constexpr (TH) {
+      A.T0 = A.T1;
+      A.Qx0 = A.Qx1;
+      A.Qy0 = A.Qy1;
+      A.Qz0 = A.Qz1;
+      A.T1 = A.Qz1 = t2;
+      A.Qx1 = qx2;
+      A.Qy1 = qy2;
+    }
   }
   if (!pz && se == g.nz - 1 && own) {
-    const unsigned k = unsigned(g.nz - 1) * nxy + unsigned(n0.off);
-    const R ubk[3] = {a.ub[0][k], a.ub[1][k], a.ub[2][k]};
-    fwd3_out<R, TH>(g, a, k, n0.ex, n0.ey, 1, a.mask[k], a.inv1pa[k], TH ? a.Tb[k] : R(0), ubk,
-                    fac, A.r[0], A.U[0], A.T[0], A.Q[0], part);
+    const size_t q = size_t(g.nz - 1) * nxy;
+    const R ubk[3] = {at_b(a.ub[0] + q, ob0), at_b(a.ub[1] + q, ob0), at_b(a.ub[2] + q, ob0)};
+    const R U[3] = {A.Ux0, A.Uy0, A.Uz0}, Q[3] = {A.Qx0, A.Qy0, A.Qz0};
+    fwd3_out<R, TH>(g, a, q, unsigned(n0.off), n0.ex, n0.ey, 1, at_b(a.mask + q, unsigned(n0.off)),
+                    at_b(a.inv1pa + q, ob0), TH ? at_b(a.Tb + q, ob0) : R(0), ubk, fac, A.r0, U,
+                    A.T0, Q, part);
   }
   if (a.acc) {
     const double s = block_sum3(part, L.red);
