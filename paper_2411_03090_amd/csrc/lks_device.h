@@ -287,33 +287,52 @@ struct Geo3 {
   double drho_out;  // prescribed outlet density minus 1
 };
 
-// Least-squares completion operators of a face orientation o = 2 axis +
-// (n = +e_axis), the D3Q19 counterpart of RingOp with five unknowns.
-template <typename T>
-struct FaceOpT {
-  T Lf[2][5][19];
-  T Ls[2][5];
-  T Lk[2][5];
-  T Ld[5][19];
-  T Lg0[5][19];
-  T ga[19], ge[19];
-  T A0, A1, A2;
-  T hc[5], h1[5];
-  T uw[5], uc[5][3];
+// Least-squares completion operator of a face node with outward normal +x, the
+// D3Q19 counterpart of RingOp with five unknowns.
+struct FaceOp3 {
+  double Lf[2][5][19];
+  double Ls[2][5];
+  double Lk[2][5];
+  double Ld[5][19];
+  double Lg0[5][19];
+  double ga[19], ge[19];
+  double A0, A1, A2;
+  double hc[5], h1[5];
   int unk[5];
-  int pad[3];
 };
-using FaceOp3 = FaceOpT<double>;
+// The operator in the form the kernels apply it, one for the six faces (the
+// symmetries of the square leave these products of the 5 x 14 map). With the
+// known populations of a node in its frame (face_fill), the even combinations
+// e = (rest, sum of the four +-t, of the four +-t1 +-t2, -n, sum of the four
+// -n +-t), the odd ones of a tangent o = (difference of +-t, of the diagonals, of
+// -n +-t), and the weighted sums over the unknown populations
+//   Y all                              = Y[v].e + Ys s + Yk kappa T
+//   Z1 + Z2 those with a tangent       = Zs[v].e + Zss s + Zsk kappa T
+//   Z1 - Z2 (Zi those along +-ti)      = Zd[v].(t1 - t2 sums, -n +-t1 - those of t2)
+//   Xi difference of those along +-ti  = X[v].o_i
+// and for the temperature as in RingFillT.
+template <typename T>
+struct FaceFillT {
+  T Y[2][5], Zs[2][5], Zd[2][2], X[2][3];
+  T Ys[2], Zss[2], Yk[2], Zsk[2];
+  T Dy[5], Dx[3], Gy[5], Gx[3];
+  T ka[5], ke[5];
+  T A0, A1, A2, Hc, H1;
+};
 template <typename R>
-inline FaceOpT<R> face_op_as(const FaceOp3& s) {
-  FaceOpT<R> d{};
-  conv_op(d.Lf, s.Lf); conv_op(d.Ls, s.Ls); conv_op(d.Lk, s.Lk); conv_op(d.Ld, s.Ld);
-  conv_op(d.Lg0, s.Lg0); conv_op(d.ga, s.ga); conv_op(d.ge, s.ge); conv_op(d.A0, s.A0);
-  conv_op(d.A1, s.A1); conv_op(d.A2, s.A2); conv_op(d.hc, s.hc); conv_op(d.h1, s.h1);
-  conv_op(d.uw, s.uw); conv_op(d.uc, s.uc); conv_op(d.unk, s.unk);
+inline FaceFillT<R> face_fill_as(const FaceFillT<double>& s) {
+  FaceFillT<R> d{};
+  conv_op(d.Y, s.Y); conv_op(d.Zs, s.Zs); conv_op(d.Zd, s.Zd); conv_op(d.X, s.X);
+  conv_op(d.Ys, s.Ys); conv_op(d.Zss, s.Zss); conv_op(d.Yk, s.Yk); conv_op(d.Zsk, s.Zsk);
+  conv_op(d.Dy, s.Dy); conv_op(d.Dx, s.Dx); conv_op(d.Gy, s.Gy); conv_op(d.Gx, s.Gx);
+  conv_op(d.ka, s.ka); conv_op(d.ke, s.ke); conv_op(d.A0, s.A0); conv_op(d.A1, s.A1);
+  conv_op(d.A2, s.A2); conv_op(d.Hc, s.Hc); conv_op(d.H1, s.H1);
   return d;
 }
-void build_face_ops3(double A, double Bf, FaceOp3 ops[6]);
+// bytes of the workspace the face operators of a D3Q19 context are given
+constexpr size_t FACE_OPS_BYTES = 6 * 4056;
+static_assert(sizeof(FaceFillT<double>) <= FACE_OPS_BYTES, "face operators fit their slice");
+void build_face_fill(double A, double Bf, FaceFillT<double>& fill);
 
 // fields of the forward state: drho, ux, uy, uz, T
 template <typename R>
@@ -346,7 +365,7 @@ struct Adj3Args {
   const R* p0[5];      // level n+1
   R* p1[5];            // level n
   R* m;                // moments: rho~, u~ (3), s~ (6), T~, q~ (3); 14 N (10 N without T)
-  const FaceOpT<R>* ops;  // -x, +x, -y, +y, -z, +z
+  const FaceFillT<R>* ops;  // boundary completion
   const int* face;     // boundary nodes: faces by orientation, then edges and corners
   int nface;
   double* sens;

@@ -873,82 +873,106 @@ __device__ inline void mom19(const R f[19], const R g[19], R M[14]) {
   }
 }
 
-// the fill of face_fill with the operator op of orientation o and flow type
-// v (0 velocity, 1 pressure node)
-template <typename R, bool TH, typename OP>
-__device__ inline void face_apply(OP op, int v, int o, const Adj3Args<R>& a, int k, int m, R Tn,
-                                  const R f[19], const R gq[19], R M[14]) {
-  const int ax = o >> 1, sg = (o & 1) ? 1 : -1;
-  R kappa = R(0), gu[5] = {R(0), R(0), R(0), R(0), R(0)};
+// Least-squares completion of a face node with orientation o (see FaceFillT)
+// and the moments of the completed set. In the node's frame (outward normal n
+// along axis o / 2, tangents t1, t2 along the next two axes) the known
+// populations are f[0] rest, f[1..4] t1, -t1, t2, -t2, f[5..8] t1 + t2, t1 - t2,
+// -t1 + t2, -t1 - t2, f[9] -n, f[10..13] -n + t1, -n - t1, -n + t2, -n - t2.
+// The symmetries of the square split the 5 x 14 map into sums of products
+// with 15 coefficients, one operator for the six faces.
+template <typename R, bool TH>
+__device__ inline void face_fill(const Adj3Args<R>& a, int o, int m, R un, R Tn, const R f[14],
+                                 const R gq[14], R M[14]) {
+#pragma clang fp contract(on)
+  const R w0 = R(1.0 / 3), w1 = R(1.0 / 18), w2 = R(1.0 / 36);
+  const auto* op = as_scalar(a.ops);
+  const bool diri = ((m >> 2) & 3) == THERM_DIRICHLET3;
+  R kappa = R(0), Tt = R(0), qn = R(0), q1 = R(0), q2 = R(0);
   if constexpr (TH) {
-    if (((m >> 2) & 3) == THERM_DIRICHLET3) {
-#pragma nounroll
-      for (int c = 0; c < 5; ++c) {
-        R t = R(0);
-#pragma unroll
-        for (int q = 0; q < 19; ++q) t += op->Ld[c][q] * gq[q];
-        gu[c] = t;
-      }
+    const R ea = (gq[1] + gq[2]) + (gq[3] + gq[4]), ed = (gq[5] + gq[8]) + (gq[6] + gq[7]);
+    const R eb = (gq[10] + gq[11]) + (gq[12] + gq[13]);
+    const R t1 = gq[1] - gq[2], t2 = gq[3] - gq[4], i1 = gq[10] - gq[11], i2 = gq[12] - gq[13];
+    const R d1 = (gq[5] - gq[8]) + (gq[6] - gq[7]), d2 = (gq[5] - gq[8]) - (gq[6] - gq[7]);
+    auto even = [&](const auto& c) {
+      return c[0] * gq[0] + c[1] * ea + c[2] * ed + c[3] * gq[9] + c[4] * eb;
+    };
+    auto odd = [&](const auto& c, R t, R d, R i) { return c[0] * t + c[1] * d + c[2] * i; };
+    R Y, X1, X2;
+    if (diri) {
+      Y = even(op->Dy);
+      X1 = odd(op->Dx, t1, d1, i1);
+      X2 = odd(op->Dx, t2, d2, i2);
     } else {
-      const R* un_src = ax == 0 ? a.u[0] : (ax == 1 ? a.u[1] : a.u[2]);
-      const R un = R(sg) * un_src[k];
-      R num = R(0);
-#pragma unroll
-      for (int q = 0; q < 19; ++q) num += (op->ga[q] - un * op->ge[q]) * gq[q];
+      const R na = even(op->ka), ne = even(op->ke);
       const R den = op->A0 - R(2) * un * op->A1 + un * un * op->A2;
-      kappa = -num / den;
-#pragma nounroll
-      for (int c = 0; c < 5; ++c) {
-        R t = R(0);
-#pragma unroll
-        for (int q = 0; q < 19; ++q) t += op->Lg0[c][q] * gq[q];
-        gu[c] = t - kappa * (op->hc[c] - un * op->h1[c]);
-      }
+      kappa = (un * ne - na) / den;
+      Y = even(op->Gy);
+      Y = Y - kappa * (op->Hc - un * op->H1);
+      X1 = odd(op->Gx, t1, d1, i1);
+      X2 = odd(op->Gx, t2, d2, i2);
     }
+    const R in = w1 * gq[9] + w2 * eb;
+    Tt = w0 * gq[0] + w1 * ea + w2 * ed + in + Y;
+    qn = Y - in;
+    q1 = w1 * t1 + w2 * (d1 + i1) + X1;
+    q2 = w1 * t2 + w2 * (d2 + i2) + X2;
   }
   // boundary seed of the pressure-drop objective per unit boundary pressure
   R s = R(0);
   if (m & TAG_J_INLET3) s += R(a.seed_dp);
   if (m & TAG_J_OUTLET3) s -= R(a.seed_dp);
   const R kT = kappa * Tn;
-#pragma nounroll
-  for (int c = 0; c < 5; ++c) {
-    R t = op->Ls[v][c] * s + op->Lk[v][c] * kT;
-#pragma unroll
-    for (int q = 0; q < 19; ++q) t += op->Lf[v][c][q] * f[q];
-    const R wf = op->uw[c] * t;
-    const R cx[3] = {op->uc[c][0], op->uc[c][1], op->uc[c][2]};
-    M[0] += wf;
-#pragma unroll
-    for (int x = 0; x < 3; ++x) {
-      M[1 + x] += cx[x] * wf;
-#pragma unroll
-      for (int y = x; y < 3; ++y) M[4 + SI[x][y]] += cx[x] * cx[y] * wf;
-    }
-    if constexpr (TH) {
-      const R wg = op->uw[c] * gu[c];
-      M[10] += wg;
-#pragma unroll
-      for (int x = 0; x < 3; ++x) M[11 + x] += cx[x] * wg;
-    }
-  }
-}
-
-// least-squares fill of a face node with orientation o: the moments of its
-// five missing directions from the 14 received ones (zero in f, g at the
-// missing directions), the J seed and the thermal closure. A wave whose
-// lanes share orientation and node type reads the operator through the
-// scalar unit; mixed waves read it per lane.
-template <typename R, bool TH>
-__device__ void face_fill(const Adj3Args<R>& a, int k, int m, int o, R Tn, const R f[19],
-                          const R gq[19], R M[14]) {
+  const R s1 = f[1] + f[2], s2 = f[3] + f[4], ea = s1 + s2;
+  const R dp = f[5] + f[8], dm = f[6] + f[7], ed = dp + dm;
+  const R b1 = f[10] + f[11], b2 = f[12] + f[13], eb = b1 + b2;
+  const R t1 = f[1] - f[2], t2 = f[3] - f[4], i1 = f[10] - f[11], i2 = f[12] - f[13];
+  const R d1 = (f[5] - f[8]) + (f[6] - f[7]), d2 = (f[5] - f[8]) - (f[6] - f[7]);
+  R Y = R(0), Zs = R(0), Zd = R(0), X1 = R(0), X2 = R(0);
   const int v = (m & 3) == FLOW_VELOCITY3 ? 0 : 1;
-  const int key = 2 * o + v;
-  const int uk = __builtin_amdgcn_readfirstlane(key);
-  if (__all(key == uk))
-    face_apply<R, TH>(as_scalar(a.ops) + (uk >> 1), uk & 1, uk >> 1, a, k, m, Tn, f, gq, M);
-  else
-    face_apply<R, TH>(a.ops + o, v, o, a, k, m, Tn, f, gq, M);
+#pragma nounroll
+  for (int t = 0; t < 2; ++t) {
+    if (!__any(v == t)) continue;
+    auto even = [&](const auto& c) {
+      return c[0] * f[0] + c[1] * ea + c[2] * ed + c[3] * f[9] + c[4] * eb;
+    };
+    auto odd = [&](R x, R d, R i) {
+      return op->X[t][0] * x + op->X[t][1] * d + op->X[t][2] * i;
+    };
+    const R y = even(op->Y[t]) + op->Ys[t] * s + op->Yk[t] * kT;
+    const R zs = even(op->Zs[t]) + op->Zss[t] * s + op->Zsk[t] * kT;
+    const R zd = op->Zd[t][0] * (s1 - s2) + op->Zd[t][1] * (b1 - b2);
+    const R x1 = odd(t1, d1, i1), x2 = odd(t2, d2, i2);
+    Y = v == t ? y : Y;
+    Zs = v == t ? zs : Zs;
+    Zd = v == t ? zd : Zd;
+    X1 = v == t ? x1 : X1;
+    X2 = v == t ? x2 : X2;
+  }
+  const R in = w1 * f[9] + w2 * eb;
+  const R r = w0 * f[0] + w1 * ea + w2 * ed + in + Y;
+  const R Un = Y - in, U1 = w1 * t1 + w2 * (d1 + i1) + X1, U2 = w1 * t2 + w2 * (d2 + i2) + X2;
+  const R snn = in + Y;
+  const R s11 = w1 * s1 + w2 * (ed + b1) + R(0.5) * (Zs + Zd);
+  const R s22 = w1 * s2 + w2 * (ed + b2) + R(0.5) * (Zs - Zd);
+  const R sn1 = X1 - w2 * i1, sn2 = X2 - w2 * i2, s12 = w2 * (dp - dm);
+  // back to x, y, z: t1 and t2 are the axes after the normal's
+  const int ax = o >> 1;
+  const R sg = (o & 1) ? R(1) : R(-1);
+  auto pick = [&](R x0, R x1, R x2) { return ax == 0 ? x0 : (ax == 1 ? x1 : x2); };
+  M[0] = r;
+  M[1] = pick(sg * Un, U2, U1);
+  M[2] = pick(U1, sg * Un, U2);
+  M[3] = pick(U2, U1, sg * Un);
+  M[4] = pick(snn, s22, s11);
+  M[5] = pick(sg * sn1, sg * sn2, s12);
+  M[6] = pick(sg * sn2, s12, sg * sn1);
+  M[7] = pick(s11, snn, s22);
+  M[8] = pick(s12, sg * sn1, sg * sn2);
+  M[9] = pick(s22, s11, snn);
+  M[10] = Tt;
+  M[11] = pick(sg * qn, q2, q1);
+  M[12] = pick(q1, sg * qn, q2);
+  M[13] = pick(q2, q1, sg * qn);
 }
 
 // local terms of the adjoint moments: the probe seed, the prescribed
@@ -973,38 +997,82 @@ __device__ inline void adj_local(const Adj3Args<R>& a, int k, int m, int ne, R T
   for (int x = 0; x < 3; ++x) M[1 + x] *= s;
 }
 
-// moments of the node p (not an edge or corner node) with orientation o if
-// it is a face node; FACE = false compiles the interior rule alone (ne = 0)
-template <typename R, bool TH, bool FACE = true>
-__device__ void alks3_node(const Geo3& g, const Adj3Args<R>& a, P3 p, int k, int ne, int o,
-                           R M[14]) {
-  if constexpr (!FACE) ne = 0;
-  const int ax = o >> 1, sg = (o & 1) ? 1 : -1;
+// moments of the interior node p
+template <typename R, bool TH>
+__device__ inline void alks3_node(const Geo3& g, const Adj3Args<R>& a, P3 p, int k, R M[14]) {
   R f[19], gq[19];
 #pragma unroll
   for (int q = 0; q < 19; ++q) {
     const int cq[3] = {QX[q], QY[q], QZ[q]};
-    int cn = 0;
-    if (FACE && ne) cn = sg * (ax == 0 ? cq[0] : (ax == 1 ? cq[1] : cq[2]));
-    f[q] = R(0);
-    gq[q] = R(0);
-    if (cn > 0) continue;
     const int z = nbr(g, p, cq[0], cq[1], cq[2]);
     R v = a.p0[0][z];
 #pragma unroll
     for (int x = 0; x < 3; ++x)
       if (cq[x]) v += R(cq[x]) * a.p0[1 + x][z];
     f[q] = v;
-    if constexpr (TH) gq[q] = a.p0[4][z];
+    gq[q] = TH ? a.p0[4][z] : R(0);
   }
   mom19<R, TH>(f, gq, M);
   const int m = a.mask[k];
   const R Tn = TH ? a.T[k] : R(0);
-  if constexpr (FACE)
-    if (ne) face_fill<R, TH>(a, k, m, o, Tn, f, gq, M);
   // exact mode: u~ stays undivided; the update pass divides V instead
   const bool probe = TH && (m & TAG_PROBE3) && a.seed_heat != 0.0;
-  adj_local<R, TH>(a, k, m, ne, Tn, a.exact ? R(1) : a.inv1pa[k], M, probe ? a.u[0][k] : R(0));
+  adj_local<R, TH>(a, k, m, 0, Tn, a.exact ? R(1) : a.inv1pa[k], M, probe ? a.u[0][k] : R(0));
+}
+
+// moments of the face node p with orientation o. Only the 14 known
+// populations are read, at offsets formed from the orientation, so that all
+// their loads are in flight together; read direction by direction behind a test
+// of c.n each one waited for the last (57.7 us on 256 x 128 x 128 in FP32 with a
+// 5 x 19 operator per orientation, now 47.5; 97 x 61 x 53 FP64 23.1, now 18.9).
+template <typename R, bool TH>
+__device__ inline void alks3_face_node(const Geo3& g, const Adj3Args<R>& a, P3 p, int k, int o,
+                                       R M[14]) {
+  const int ax = o >> 1, sg = (o & 1) ? 1 : -1;
+  // steps along the normal (inwards) and the tangents; a face node has
+  // neighbours along its tangents, wrapped on a periodic axis
+  const int c[3] = {p.i, p.j, p.l}, n3[3] = {g.nx, g.ny, g.nz};
+  const int st[3] = {1, g.nx, g.nx * g.ny};
+  auto at = [&](const int (&x)[3], int e) { return e == 0 ? x[0] : (e == 1 ? x[1] : x[2]); };
+  auto side = [&](int e, int d) {
+    const int x = at(c, e), n = at(n3, e), s = at(st, e);
+    return (x + d < 0 ? n - 1 : (x + d >= n ? 1 - n : d)) * s;
+  };
+  const int a1 = ax == 2 ? 0 : ax + 1, a2 = ax == 0 ? 2 : ax - 1;
+  const int in = -sg * at(st, ax);
+  const int p1 = side(a1, 1), m1 = side(a1, -1), p2 = side(a2, 1), m2 = side(a2, -1);
+  const int off[14] = {0,       p1,      m1,      p2, m2,      p1 + p2, p1 + m2,
+                       m1 + p2, m1 + m2, in, in + p1, in + m1, in + p2, in + m2};
+  constexpr int C1[14] = {0, 1, -1, 0, 0, 1, 1, -1, -1, 0, 1, -1, 0, 0};
+  constexpr int C2[14] = {0, 0, 0, 1, -1, 1, -1, 1, -1, 0, 0, 0, 1, -1};
+  const R* const V[3] = {a.p0[1], a.p0[2], a.p0[3]};
+  const R* Vn = ax == 0 ? V[0] : (ax == 1 ? V[1] : V[2]);
+  const R* V1 = a1 == 0 ? V[0] : (a1 == 1 ? V[1] : V[2]);
+  const R* V2 = a2 == 0 ? V[0] : (a2 == 1 ? V[1] : V[2]);
+  R f[14], gq[14], vn[5], v1[14], v2[14];
+#pragma unroll
+  for (int q = 0; q < 14; ++q) {
+    const int z = k + off[q];
+    f[q] = a.p0[0][z];
+    if (q >= 9) vn[q - 9] = Vn[z];
+    if (C1[q]) v1[q] = V1[z];
+    if (C2[q]) v2[q] = V2[z];
+    gq[q] = TH ? a.p0[4][z] : R(0);
+  }
+  const int m = a.mask[k];
+  const R Tn = TH ? a.T[k] : R(0);
+  const R* un_src = ax == 0 ? a.u[0] : (ax == 1 ? a.u[1] : a.u[2]);
+  const R un = TH ? R(sg) * un_src[k] : R(0);
+  const R ip = a.exact ? R(1) : a.inv1pa[k];
+#pragma unroll
+  for (int q = 0; q < 14; ++q) {
+    if (q >= 9) f[q] -= R(sg) * vn[q - 9];
+    if (C1[q]) f[q] += R(C1[q]) * v1[q];
+    if (C2[q]) f[q] += R(C2[q]) * v2[q];
+  }
+  face_fill<R, TH>(a, o, m, un, Tn, f, gq, M);
+  const bool probe = TH && (m & TAG_PROBE3) && a.seed_heat != 0.0;
+  adj_local<R, TH>(a, k, m, 1, Tn, ip, M, probe ? a.u[0][k] : R(0));
 }
 
 // ALKS pass 1 at the interior nodes; the boundary nodes are left to
@@ -1018,7 +1086,7 @@ __global__ __launch_bounds__(NT3) void alks3_pull_kernel(Geo3 g, Adj3Args<R> a) 
   int o;
   if (ends(g, p, &o)) return;
   R mom[14];
-  alks3_node<R, TH, false>(g, a, p, k, 0, -1, mom);
+  alks3_node<R, TH>(g, a, p, k, mom);
   const size_t N = size_t(g.N);
   constexpr int NM = TH ? 14 : 10;
 #pragma unroll
@@ -1037,14 +1105,11 @@ __global__ __launch_bounds__(NT3) void alks3_face_kernel(Geo3 g, Adj3Args<R> a) 
   int o;
   const int ne = ends(g, p, &o);
   R mom[14];
-  if (ne >= 2) {
-    const P3 s = copy_src(g, p);
-    int os;
-    const int nes = ends(g, s, &os);
-    alks3_node<R, TH>(g, a, s, (s.l * g.ny + s.j) * g.nx + s.i, nes, os, mom);
-  } else {
-    alks3_node<R, TH>(g, a, p, k, ne, o, mom);
-  }
+  // edges and corners take the moments of the node one step inwards
+  const P3 s = ne >= 2 ? copy_src(g, p) : p;
+  const int ks = (s.l * g.ny + s.j) * g.nx + s.i;
+  if (ends(g, s, &o)) alks3_face_node<R, TH>(g, a, s, ks, o, mom);
+  else alks3_node<R, TH>(g, a, s, ks, mom);
   const size_t N = size_t(g.N);
   constexpr int NM = TH ? 14 : 10;
 #pragma unroll

@@ -263,137 +263,215 @@ void build_ring_fill(double A, double Bf, RingFillT<double>& F) {
 // directions c_i.n > 0 unknown; the pressure face has the multipliers
 // lambda~ + mu~_1 (c_i.t1) + mu~_2 (c_i.t2) with t1, t2 the two coordinate
 // axes normal to n, the velocity face mu~.c_i.
-void build_face_ops3(double A, double Bf, FaceOp3 ops[6]) {
-  for (int o = 0; o < 6; ++o) {
-    FaceOp3& op = ops[o];
-    std::memset(&op, 0, sizeof op);
-    const int ax = o / 2, sg = (o & 1) ? 1 : -1;
-    const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
-    int cn[19], nu = 0;
+namespace {
+// the operator of a face node with outward normal +x
+void build_face_op(double A, double Bf, FaceOp3& op) {
+  std::memset(&op, 0, sizeof op);
+  const int ax = 0, sg = 1;
+  const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
+  int cn[19], nu = 0;
+  for (int q = 0; q < 19; ++q) {
+    cn[q] = sg * C19[q][ax];
+    if (cn[q] > 0) op.unk[nu++] = q;
+  }
+  double M[19][19];
+  for (int r = 0; r < 19; ++r)
     for (int q = 0; q < 19; ++q) {
-      cn[q] = sg * C19[q][ax];
-      if (cn[q] > 0) op.unk[nu++] = q;
+      const double cc = C19[q][0] * C19[r][0] + C19[q][1] * C19[r][1] + C19[q][2] * C19[r][2];
+      M[r][q] = (r == q ? cn[r] : 0.0) - 2.0 * A * W19[q] * cn[q] * cc;
+    }
+  for (int v = 0; v < 2; ++v) {
+    double K[19 * 8], P[8 * 19];
+    for (int r = 0; r < 19; ++r) {
+      for (int a = 0; a < 5; ++a) K[r * 8 + a] = M[r][op.unk[a]];
+      if (v == 0) {
+        for (int d = 0; d < 3; ++d) K[r * 8 + 5 + d] = C19[r][d];
+      } else {
+        K[r * 8 + 5] = 1.0;
+        K[r * 8 + 6] = C19[r][t1];
+        K[r * 8 + 7] = C19[r][t2];
+      }
+    }
+    pseudo_inverse(19, 8, K, P);
+    for (int a = 0; a < 5; ++a) {
+      double s = 0, k = 0;
+      for (int r = 0; r < 19; ++r) {
+        s += P[a * 19 + r];
+        k += P[a * 19 + r] * cn[r];
+      }
+      op.Ls[v][a] = -s;
+      op.Lk[v][a] = k;
+      for (int q = 0; q < 19; ++q) {
+        double t = 0;
+        if (cn[q] <= 0)
+          for (int r = 0; r < 19; ++r) t += P[a * 19 + r] * M[r][q];
+        op.Lf[v][a][q] = -t;
+      }
+    }
+  }
+  double Mg[19][19];
+  for (int r = 0; r < 19; ++r)
+    for (int q = 0; q < 19; ++q) Mg[r][q] = (r == q ? cn[r] : 0.0) - Bf * W19[q] * cn[q];
+  {
+    double K[19 * 6], P[6 * 19];
+    for (int r = 0; r < 19; ++r) {
+      for (int a = 0; a < 5; ++a) K[r * 6 + a] = Mg[r][op.unk[a]];
+      K[r * 6 + 5] = 1.0;
+    }
+    pseudo_inverse(19, 6, K, P);
+    for (int a = 0; a < 5; ++a)
+      for (int q = 0; q < 19; ++q) {
+        double t = 0;
+        if (cn[q] <= 0)
+          for (int r = 0; r < 19; ++r) t += P[a * 19 + r] * Mg[r][q];
+        op.Ld[a][q] = -t;
+      }
+  }
+  {
+    // zero-flux face: Schur form in the normal velocity u_n
+    double K0[19 * 5], G[25], H[25], HK[5 * 19];
+    for (int r = 0; r < 19; ++r)
+      for (int a = 0; a < 5; ++a) K0[r * 5 + a] = Mg[r][op.unk[a]];
+    for (int a = 0; a < 5; ++a)
+      for (int b = 0; b < 5; ++b) {
+        double s = 0;
+        for (int r = 0; r < 19; ++r) s += K0[r * 5 + a] * K0[r * 5 + b];
+        G[a * 5 + b] = s;
+      }
+    invert(5, G, H);
+    for (int a = 0; a < 5; ++a)
+      for (int r = 0; r < 19; ++r) {
+        double s = 0;
+        for (int b = 0; b < 5; ++b) s += H[a * 5 + b] * K0[r * 5 + b];
+        HK[a * 19 + r] = s;
+      }
+    double Qcn[19], Q1[19];
+    for (int r = 0; r < 19; ++r) {
+      double s = 0, t = 0;
+      for (int c = 0; c < 19; ++c) {
+        double kk = 0;
+        for (int a = 0; a < 5; ++a) kk += K0[r * 5 + a] * HK[a * 19 + c];
+        const double q = (r == c ? 1.0 : 0.0) - kk;
+        s += q * cn[c];
+        t += q;
+      }
+      Qcn[r] = s;
+      Q1[r] = t;
+    }
+    op.A0 = op.A1 = op.A2 = 0;
+    for (int r = 0; r < 19; ++r) {
+      op.A0 += cn[r] * Qcn[r];
+      op.A1 += cn[r] * Q1[r];
+      op.A2 += Q1[r];
+    }
+    for (int q = 0; q < 19; ++q) {
+      double ga = 0, ge = 0;
+      if (cn[q] <= 0)
+        for (int r = 0; r < 19; ++r) {
+          ga += Qcn[r] * Mg[r][q];
+          ge += Q1[r] * Mg[r][q];
+        }
+      op.ga[q] = ga;
+      op.ge[q] = ge;
     }
     for (int a = 0; a < 5; ++a) {
-      op.uw[a] = W19[op.unk[a]];
-      for (int d = 0; d < 3; ++d) op.uc[a][d] = C19[op.unk[a]][d];
-    }
-    double M[19][19];
-    for (int r = 0; r < 19; ++r)
+      double hc = 0, h1 = 0;
+      for (int r = 0; r < 19; ++r) {
+        hc += HK[a * 19 + r] * cn[r];
+        h1 += HK[a * 19 + r];
+      }
+      op.hc[a] = hc;
+      op.h1[a] = h1;
       for (int q = 0; q < 19; ++q) {
-        const double cc = C19[q][0] * C19[r][0] + C19[q][1] * C19[r][1] + C19[q][2] * C19[r][2];
-        M[r][q] = (r == q ? cn[r] : 0.0) - 2.0 * A * W19[q] * cn[q] * cc;
-      }
-    for (int v = 0; v < 2; ++v) {
-      double K[19 * 8], P[8 * 19];
-      for (int r = 0; r < 19; ++r) {
-        for (int a = 0; a < 5; ++a) K[r * 8 + a] = M[r][op.unk[a]];
-        if (v == 0) {
-          for (int d = 0; d < 3; ++d) K[r * 8 + 5 + d] = C19[r][d];
-        } else {
-          K[r * 8 + 5] = 1.0;
-          K[r * 8 + 6] = C19[r][t1];
-          K[r * 8 + 7] = C19[r][t2];
-        }
-      }
-      pseudo_inverse(19, 8, K, P);
-      for (int a = 0; a < 5; ++a) {
-        double s = 0, k = 0;
-        for (int r = 0; r < 19; ++r) {
-          s += P[a * 19 + r];
-          k += P[a * 19 + r] * cn[r];
-        }
-        op.Ls[v][a] = -s;
-        op.Lk[v][a] = k;
-        for (int q = 0; q < 19; ++q) {
-          double t = 0;
-          if (cn[q] <= 0)
-            for (int r = 0; r < 19; ++r) t += P[a * 19 + r] * M[r][q];
-          op.Lf[v][a][q] = -t;
-        }
-      }
-    }
-    double Mg[19][19];
-    for (int r = 0; r < 19; ++r)
-      for (int q = 0; q < 19; ++q) Mg[r][q] = (r == q ? cn[r] : 0.0) - Bf * W19[q] * cn[q];
-    {
-      double K[19 * 6], P[6 * 19];
-      for (int r = 0; r < 19; ++r) {
-        for (int a = 0; a < 5; ++a) K[r * 6 + a] = Mg[r][op.unk[a]];
-        K[r * 6 + 5] = 1.0;
-      }
-      pseudo_inverse(19, 6, K, P);
-      for (int a = 0; a < 5; ++a)
-        for (int q = 0; q < 19; ++q) {
-          double t = 0;
-          if (cn[q] <= 0)
-            for (int r = 0; r < 19; ++r) t += P[a * 19 + r] * Mg[r][q];
-          op.Ld[a][q] = -t;
-        }
-    }
-    {
-      // zero-flux face: Schur form in the normal velocity u_n
-      double K0[19 * 5], G[25], H[25], HK[5 * 19];
-      for (int r = 0; r < 19; ++r)
-        for (int a = 0; a < 5; ++a) K0[r * 5 + a] = Mg[r][op.unk[a]];
-      for (int a = 0; a < 5; ++a)
-        for (int b = 0; b < 5; ++b) {
-          double s = 0;
-          for (int r = 0; r < 19; ++r) s += K0[r * 5 + a] * K0[r * 5 + b];
-          G[a * 5 + b] = s;
-        }
-      invert(5, G, H);
-      for (int a = 0; a < 5; ++a)
-        for (int r = 0; r < 19; ++r) {
-          double s = 0;
-          for (int b = 0; b < 5; ++b) s += H[a * 5 + b] * K0[r * 5 + b];
-          HK[a * 19 + r] = s;
-        }
-      double Qcn[19], Q1[19];
-      for (int r = 0; r < 19; ++r) {
-        double s = 0, t = 0;
-        for (int c = 0; c < 19; ++c) {
-          double kk = 0;
-          for (int a = 0; a < 5; ++a) kk += K0[r * 5 + a] * HK[a * 19 + c];
-          const double q = (r == c ? 1.0 : 0.0) - kk;
-          s += q * cn[c];
-          t += q;
-        }
-        Qcn[r] = s;
-        Q1[r] = t;
-      }
-      op.A0 = op.A1 = op.A2 = 0;
-      for (int r = 0; r < 19; ++r) {
-        op.A0 += cn[r] * Qcn[r];
-        op.A1 += cn[r] * Q1[r];
-        op.A2 += Q1[r];
-      }
-      for (int q = 0; q < 19; ++q) {
-        double ga = 0, ge = 0;
+        double t = 0;
         if (cn[q] <= 0)
-          for (int r = 0; r < 19; ++r) {
-            ga += Qcn[r] * Mg[r][q];
-            ge += Q1[r] * Mg[r][q];
-          }
-        op.ga[q] = ga;
-        op.ge[q] = ge;
-      }
-      for (int a = 0; a < 5; ++a) {
-        double hc = 0, h1 = 0;
-        for (int r = 0; r < 19; ++r) {
-          hc += HK[a * 19 + r] * cn[r];
-          h1 += HK[a * 19 + r];
-        }
-        op.hc[a] = hc;
-        op.h1[a] = h1;
-        for (int q = 0; q < 19; ++q) {
-          double t = 0;
-          if (cn[q] <= 0)
-            for (int r = 0; r < 19; ++r) t += HK[a * 19 + r] * Mg[r][q];
-          op.Lg0[a][q] = -t;
-        }
+          for (int r = 0; r < 19; ++r) t += HK[a * 19 + r] * Mg[r][q];
+        op.Lg0[a][q] = -t;
       }
     }
+  }
+}
+
+// index of a lattice velocity
+int dir19(int x, int y, int z) {
+  for (int q = 0; q < 19; ++q)
+    if (C19[q][0] == x && C19[q][1] == y && C19[q][2] == z) return q;
+  return -1;
+}
+}  // namespace
+
+// The +x operator in the combinations that the symmetries of the face leave
+// (t1 = y, t2 = z); entries equal by symmetry are averaged.
+void build_face_fill(double A, double Bf, FaceFillT<double>& F) {
+  FaceOp3 op;
+  build_face_op(A, Bf, op);
+  std::memset(&F, 0, sizeof F);
+  const double w1 = 1.0 / 18, w2 = 1.0 / 36;
+  // positions of the unknown directions n, n +- t1, n +- t2
+  int u[5];
+  const int un[5][3] = {{1, 0, 0}, {1, 1, 0}, {1, -1, 0}, {1, 0, 1}, {1, 0, -1}};
+  for (int e = 0; e < 5; ++e)
+    for (int a = 0; a < 5; ++a)
+      if (op.unk[a] == dir19(un[e][0], un[e][1], un[e][2])) u[e] = a;
+  auto sum4 = [](const double* r, const int (&d)[4][3]) {
+    double s = 0;
+    for (const auto& v : d) s += r[dir19(v[0], v[1], v[2])];
+    return 0.25 * s;
+  };
+  const int tang[4][3] = {{0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1}};
+  const int diag[4][3] = {{0, 1, 1}, {0, 1, -1}, {0, -1, 1}, {0, -1, -1}};
+  const int inw[4][3] = {{-1, 1, 0}, {-1, -1, 0}, {-1, 0, 1}, {-1, 0, -1}};
+  auto even = [&](const double* r, double e[5]) {
+    e[0] = r[0];
+    e[1] = sum4(r, tang);
+    e[2] = sum4(r, diag);
+    e[3] = r[dir19(-1, 0, 0)];
+    e[4] = sum4(r, inw);
+  };
+  // Y, Z1 + Z2 (even), Z1 - Z2 and X1 (odd in t1) of a 5 x 19 map
+  auto split = [&](const double L[5][19], double Y[5], double* Zs, double* Zd, double X[3]) {
+    double y[19], zs[19], zd[19], x[19];
+    for (int q = 0; q < 19; ++q) {
+      const double z1 = w2 * (L[u[1]][q] + L[u[2]][q]), z2 = w2 * (L[u[3]][q] + L[u[4]][q]);
+      zs[q] = z1 + z2;
+      zd[q] = z1 - z2;
+      y[q] = w1 * L[u[0]][q] + z1 + z2;
+      x[q] = w2 * (L[u[1]][q] - L[u[2]][q]);
+    }
+    even(y, Y);
+    if (Zs) even(zs, Zs);
+    if (Zd) {
+      Zd[0] = 0.25 * (zd[dir19(0, 1, 0)] + zd[dir19(0, -1, 0)] - zd[dir19(0, 0, 1)] -
+                      zd[dir19(0, 0, -1)]);
+      Zd[1] = 0.25 * (zd[dir19(-1, 1, 0)] + zd[dir19(-1, -1, 0)] - zd[dir19(-1, 0, 1)] -
+                      zd[dir19(-1, 0, -1)]);
+    }
+    X[0] = 0.5 * (x[dir19(0, 1, 0)] - x[dir19(0, -1, 0)]);
+    X[1] = 0.25 * (x[dir19(0, 1, 1)] + x[dir19(0, 1, -1)] - x[dir19(0, -1, 1)] -
+                   x[dir19(0, -1, -1)]);
+    X[2] = 0.5 * (x[dir19(-1, 1, 0)] - x[dir19(-1, -1, 0)]);
+  };
+  for (int v = 0; v < 2; ++v) {
+    split(op.Lf[v], F.Y[v], F.Zs[v], F.Zd[v], F.X[v]);
+    for (int e = 1; e < 5; ++e) {
+      F.Zss[v] += w2 * op.Ls[v][u[e]];
+      F.Zsk[v] += w2 * op.Lk[v][u[e]];
+    }
+    F.Ys[v] = w1 * op.Ls[v][u[0]] + F.Zss[v];
+    F.Yk[v] = w1 * op.Lk[v][u[0]] + F.Zsk[v];
+  }
+  split(op.Ld, F.Dy, nullptr, nullptr, F.Dx);
+  split(op.Lg0, F.Gy, nullptr, nullptr, F.Gx);
+  even(op.ga, F.ka);
+  even(op.ge, F.ke);
+  F.A0 = op.A0;
+  F.A1 = op.A1;
+  F.A2 = op.A2;
+  F.Hc = w1 * op.hc[u[0]];
+  F.H1 = w1 * op.h1[u[0]];
+  for (int e = 1; e < 5; ++e) {
+    F.Hc += w2 * op.hc[u[e]];
+    F.H1 += w2 * op.h1[u[e]];
   }
 }
 

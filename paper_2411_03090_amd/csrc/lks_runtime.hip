@@ -110,9 +110,9 @@ struct lks_ctx {
   void* d_ops = nullptr;   // adjoint boundary completion, RingFillT<R>
   lks::RingFillT<double> ops;
   lks::RingFillT<float> ops_f;
-  void* d_ops3 = nullptr;  // D3Q19 face operators (6 orientations), FaceOpT<R>
-  lks::FaceOp3 ops3[6];
-  lks::FaceOpT<float> ops3_f[6];
+  void* d_ops3 = nullptr;  // D3Q19 face completion, FaceFillT<R>
+  lks::FaceFillT<double> ops3{};
+  lks::FaceFillT<float> ops3_f{};
   int* copy3 = nullptr;  // D3Q19 edge and corner nodes (device)
   int* face3 = nullptr;  // D3Q19 boundary nodes by orientation (device)
   void* M3 = nullptr;    // D3Q19 adjoint moments of one step
@@ -208,7 +208,7 @@ size_t base_bytes(const lks_ctx* c) {
   b += 2 * nf * align256(N * r);             // adjoint ping-pong
   b += align256(sizeof(double) * acc_capacity(c));
   if (c->dim == 3) {
-    b += align256(6 * sizeof(lks::FaceOp3));  // face operators
+    b += align256(lks::FACE_OPS_BYTES);  // face operators
     b += align256(sizeof(int) * c->copy3h.size());  // edge and corner nodes
     b += align256(sizeof(int) * c->face3h.size());  // boundary nodes
     b += align256(size_t(moments3_fields(c)) * N * r);
@@ -970,7 +970,7 @@ struct Run {
         a.p1[f] = rp<R>(c->P[i1][f]);
       }
       a.m = rp<R>(c->M3);
-      a.ops = static_cast<const lks::FaceOpT<R>*>(c->d_ops3);
+      a.ops = static_cast<const lks::FaceFillT<R>*>(c->d_ops3);
       a.face = c->face3;
       a.nface = int(c->face3h.size());
       a.sens = sens;
@@ -1290,7 +1290,7 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
     g3.drho_out = g.drho_out;
     g3.zc = g3.zca = g3.zcf = 16;  // re-planned for the device at bind
     g3.fused = 1;
-    lks::build_face_ops3(g3.A, g3.Bf, c->ops3);
+    lks::build_face_fill(g3.A, g3.Bf, c->ops3);
     c->copy3h.resize(size_t(lks::copy_nodes3(g3, nullptr)));
     lks::copy_nodes3(g3, c->copy3h.data());
     c->face3h.resize(size_t(lks::face_nodes3(g3, nullptr)));
@@ -1390,7 +1390,7 @@ lks_status lks_bind_workspace(lks_ctx* c, void* dev_ptr, size_t bytes) {
   for (auto& p : c->lastv) p = nullptr;
   c->acc = reinterpret_cast<double*>(take(sizeof(double) * acc_capacity(c)));
   if (nu == 3) {
-    c->d_ops3 = take(6 * sizeof(lks::FaceOp3));
+    c->d_ops3 = take(lks::FACE_OPS_BYTES);
     c->copy3 = reinterpret_cast<int*>(take(sizeof(int) * c->copy3h.size()));
     c->face3 = reinterpret_cast<int*>(take(sizeof(int) * c->face3h.size()));
     c->M3 = take(size_t(moments3_fields(c)) * N * r);
@@ -1426,12 +1426,12 @@ lks_status lks_bind_workspace(lks_ctx* c, void* dev_ptr, size_t bytes) {
   const bool f32 = c->rsz == 4;
   if (f32) {
     c->ops_f = lks::ring_fill_as<float>(c->ops);
-    for (int o = 0; o < 6; ++o) c->ops3_f[o] = lks::face_op_as<float>(c->ops3[o]);
+    c->ops3_f = lks::face_fill_as<float>(c->ops3);
   }
   const void* ops_src = f32 ? static_cast<const void*>(&c->ops_f) : static_cast<const void*>(&c->ops);
   const size_t ops_bytes = f32 ? sizeof c->ops_f : sizeof c->ops;
   const void* ops3_src =
-      f32 ? static_cast<const void*>(c->ops3_f) : static_cast<const void*>(c->ops3);
+      f32 ? static_cast<const void*>(&c->ops3_f) : static_cast<const void*>(&c->ops3);
   const size_t ops3_bytes = f32 ? sizeof c->ops3_f : sizeof c->ops3;
   const bool ops_ok = nu == 3
       ? hip_ok(c, hipMemcpyAsync(c->d_ops3, ops3_src, ops3_bytes, hipMemcpyHostToDevice,
