@@ -4,19 +4,19 @@
 //
 // LKS step: one z-marching kernel. A block owns 64 x 4 columns and walks
 // through a range of z-planes with the state of two planes in LDS; per plane
-// it forms a0 = drho - 3/2 u.u, P = 9/2 u u + A (grad u + grad u^T),
-// G = 3 T u + B grad T and the equilibria f'_i^eq = w_i [a0 + 3 c.u + c.P.c],
-// g_i^eq = w_i [T + c.G] (eq:feq2, eq:geq2) of the tile and its ring, streams
-// them to the columns that pull them, and closes the plane behind with the
-// implicit Brinkman division and the face closures. Edge and corner nodes
-// are copied by a small second kernel.
-// ALKS step: two passes.
-//   pass 1  node-parallel: the pull of f~_i^eq = rho~ + c_i.V and
-//           g~_i^eq = Theta from x + c_i (eq:afeq, eq:ageq) through L1/L2,
-//           the face least-squares completion, the local terms and the
-//           moments rho~, u~, s~, T~, q~, stored to a scratch;
-//   pass 2  z-marching: V and Theta of the new level from the moments and
-//           the sensitivity 3 alpha' u.u~ - B' grad T.q~.
+// the tile and its ring leave a0 = drho - 3/2 u.u, P = 9/2 u u + A (grad u +
+// grad u^T), G = 3 T u + B grad T in LDS, from which the columns form the
+// equilibria f'_i^eq = w_i [a0 + 3 c.u + c.P.c], g_i^eq = w_i [T + c.G] (eq:feq2,
+// eq:geq2) that reach them, and the plane behind is closed with the implicit
+// Brinkman division and the face closures. Edge and corner nodes are copied by
+// a small second kernel.
+// ALKS step: the boundary nodes' moments (the pull of f~_i^eq = rho~ + c_i.V and
+// g~_i^eq = Theta from x + c_i, eq:afeq, eq:ageq, the face least-squares completion
+// and the local terms) go to a scratch; one z-march then forms the moments
+// rho~, u~, s~, T~, q~ of the other nodes and from them V and Theta of the new
+// level and the sensitivity 3 alpha' u.u~ - B' grad T.q~; a last kernel does the
+// end planes. The same step as three passes over the grid (pull, faces,
+// z-marching update) is kept beside it.
 // Blocks are mapped so that each XCD works on a contiguous slab of nodes,
 // keeping the neighbour planes of a block in that XCD's L2.
 #include <hip/hip_runtime.h>
@@ -323,46 +323,6 @@ __device__ inline void zregion(const Geo3& g, const ZTile& t, int off[SRL]) {
   }
 }
 
-// one plane of NF fields over the thread's region elements (zero where the
-// plane or the node does not exist)
-template <typename R, int NF>
-__device__ inline void zload(const R* const F[NF], bool exists, unsigned base, const int off[SRL],
-                             R v[SRL][NF]) {
-#pragma unroll
-  for (int r = 0; r < SRL; ++r) {
-    const bool in = exists && off[r] >= 0;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) v[r][f] = in ? F[f][base + unsigned(off[r])] : R(0);
-  }
-}
-template <typename R, int NF>
-__device__ inline void zstore(R (*dst)[NSR], const R v[SRL][NF]) {
-#pragma unroll
-  for (int r = 0; r < SRL; ++r) {
-    const int e = int(threadIdx.x) + r * ZT;
-    if (e < NSR)
-#pragma unroll
-      for (int f = 0; f < NF; ++f) dst[f][e] = v[r][f];
-  }
-}
-
-// difference at index i of an LDS field along a stride st: central, or
-// second-order one-sided at the low (e < 0) or high (e > 0) end of an axis
-template <typename R>
-__device__ inline R d1(const R* f, int i, int st, int e) {
-  if (e == 0) return R(0.5) * (f[i + st] - f[i - st]);
-  if (e < 0) return R(0.5) * (R(-3) * f[i] + R(4) * f[i + st] - f[i + 2 * st]);
-  return R(0.5) * (R(3) * f[i] - R(4) * f[i - st] + f[i - 2 * st]);
-}
-// d1 of the product f * h
-template <typename R>
-__device__ inline R d1p(const R* f, const R* h, int i, int st, int e) {
-  auto at = [&](int o) { return f[i + o * st] * h[i + o * st]; };
-  if (e == 0) return R(0.5) * (at(1) - at(-1));
-  if (e < 0) return R(0.5) * (R(-3) * at(0) + R(4) * at(1) - at(2));
-  return R(0.5) * (R(3) * at(0) - R(4) * at(-1) + at(-2));
-}
-
 // ---------------------------------------------------------------------------
 // LKS step
 // ---------------------------------------------------------------------------
@@ -427,12 +387,29 @@ __device__ inline T at_b(const T* p, unsigned o) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + o);
 }
 
+template <typename T>
+__device__ inline void put_b(T* p, unsigned o, T x) {
+  *reinterpret_cast<T*>(reinterpret_cast<char*>(p) + o) = x;
+}
+
 // x, formed anew by every loop iteration that uses it: without this the
 // compiler keeps an address per field and column across the march (24 registers
 // and then spills)
 __device__ inline unsigned anew(unsigned x) {
   asm volatile("" : "+v"(x));
   return x;
+}
+
+// The second argument of a kernel whose first one is a Geo3, read anew through
+// the scalar cache where it is used: a march has more field pointers than scalar
+// registers, and spilled ones cost two vector instructions at each use.
+template <typename A>
+__device__ inline const __attribute__((address_space(4))) A* arg2() {
+  using Bytes = const __attribute__((address_space(4))) char;
+  constexpr size_t off = (sizeof(Geo3) + alignof(A) - 1) / alignof(A) * alignof(A);
+  Bytes* p = (Bytes*)__builtin_amdgcn_kernarg_segment_ptr() + off;
+  asm volatile("" : "+s"(p));
+  return (const __attribute__((address_space(4))) A*)p;
 }
 
 // values of a source column that stay with it
@@ -624,14 +601,11 @@ __device__ inline void fwd3_out(const Geo3& g, const Fwd3Args<R>& a, size_t plan
     }
   }
   const unsigned ob = off * unsigned(sizeof(R));
-  auto put = [&](R* f, R x) {
-    *reinterpret_cast<R*>(reinterpret_cast<char*>(f + plane) + ob) = x;
-  };
-  put(a.s1[0], d);
-  put(a.s1[1], u[0]);
-  put(a.s1[2], u[1]);
-  put(a.s1[3], u[2]);
-  if constexpr (TH) put(a.s1[4], T);
+  put_b(a.s1[0] + plane, ob, d);
+  put_b(a.s1[1] + plane, ob, u[0]);
+  put_b(a.s1[2] + plane, ob, u[1]);
+  put_b(a.s1[3] + plane, ob, u[2]);
+  if constexpr (TH) put_b(a.s1[4] + plane, ob, T);
   if (a.acc) {
     if (a.objective == 1) {
       if (m & TAG_PROBE3) part += double(u[0]) * double(T);
@@ -822,55 +796,99 @@ __global__ __launch_bounds__(NT3) void copy3_kernel(Geo3 g, const int* __restric
 // ---------------------------------------------------------------------------
 // ALKS step
 // ---------------------------------------------------------------------------
-// raw moments of the 19 pulled values f~_q, g~_q, summed by weight class
-// (rest, the six axis directions, and the three diagonal planes):
-// rho~, u~ (3), s~ xx xy xz yy yz zz, T~, q~ (3)
-template <typename R, bool TH>
-__device__ inline void mom19(const R f[19], const R g[19], R M[14]) {
-  const R w0 = R(1.0 / 3), w1 = R(1.0 / 18), w2 = R(1.0 / 36);
-  // axis pairs (1,2) x, (3,4) y, (5,6) z
-  const R sa[3] = {f[1] + f[2], f[3] + f[4], f[5] + f[6]};
-  const R da[3] = {f[1] - f[2], f[3] - f[4], f[5] - f[6]};
-  // diagonal planes xy (7-10), xz (11-14), yz (15-18): directions
-  // (+,+), (-,-), (+,-), (-,+) in the plane's two axes
-  R ps[3], sab[3], d1[3], d2[3];
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    const int q = 7 + 4 * p;
-    const R s1 = f[q] + f[q + 1], s2 = f[q + 2] + f[q + 3];
-    d1[p] = f[q] - f[q + 1];
-    d2[p] = f[q + 2] - f[q + 3];
-    ps[p] = s1 + s2;
-    sab[p] = s1 - s2;
-  }
-  M[0] = w0 * f[0] + w1 * (sa[0] + sa[1] + sa[2]) + w2 * (ps[0] + ps[1] + ps[2]);
-  M[1] = w1 * da[0] + w2 * ((d1[0] + d2[0]) + (d1[1] + d2[1]));
-  M[2] = w1 * da[1] + w2 * ((d1[0] - d2[0]) + (d1[2] + d2[2]));
-  M[3] = w1 * da[2] + w2 * ((d1[1] - d2[1]) + (d1[2] - d2[2]));
-  M[4] = w1 * sa[0] + w2 * (ps[0] + ps[1]);
-  M[5] = w2 * sab[0];
-  M[6] = w2 * sab[1];
-  M[7] = w1 * sa[1] + w2 * (ps[0] + ps[2]);
-  M[8] = w2 * sab[2];
-  M[9] = w1 * sa[2] + w2 * (ps[1] + ps[2]);
+// Sums over the nine columns x + e around a column of one plane's rho~, V and
+// Theta, in units of w = 1/36. A node of this plane takes f~ of its in-plane
+// directions from them (I*), the nodes of the planes below and above take
+// f~ = E +- Vz of the five directions with c_z = +-1 (E = rho~ + e.V): p* goes to
+// the plane below (c_z = 1), m* to the plane above. All their values have the
+// same c_z, so three sums give rho~, u~, s~zz, s~xz and s~yz of them; g~ does not
+// depend on c and its sums serve both planes.
+template <typename R>
+struct AdjSums {
+  R I0, Ix, Iy, Ixx, Iyy, Ixy;
+  R pt, px, py, pxx, pyy, mt, mx, my, mxx, myy;
+  R G0, Gx, Gy, gt, gx, gy;
+};
+// at(1 + dx, 1 + dy): rho~, Vx, Vy, Vz of a column; th: its Theta
+template <typename R, bool TH, typename AT, typename GT>
+__device__ inline void adj_sums(const AT& at, const GT& th, AdjSums<R>& o) {
+#pragma clang fp contract(on)
+  const V4<R> c = at(1, 1), r = at(2, 1), l = at(0, 1), u = at(1, 2), d = at(1, 0);
+  const R er = r.x + r.y, el = l.x - l.y, eu = u.x + u.z, ed = d.x - d.z;
+  const R sx = er + el, sy = eu + ed, dx = er - el, dy = eu - ed, S = sx + sy;
+  const R zx = r.w + l.w, zy = u.w + d.w, vx = r.w - l.w, vy = u.w - d.w;
+  const R te = R(2) * c.x + S, to = R(2) * c.w + (zx + zy);
+  o.pt = te + to;
+  o.mt = te - to;
+  o.px = dx + vx;
+  o.mx = dx - vx;
+  o.py = dy + vy;
+  o.my = dy - vy;
+  o.pxx = sx + zx;
+  o.mxx = sx - zx;
+  o.pyy = sy + zy;
+  o.myy = sy - zy;
+  // (the reads below wait, here and further down: all at once they cost the
+  // registers of a wave per SIMD)
+  __builtin_amdgcn_sched_barrier(0);
+  const V4<R> a = at(2, 2), b = at(0, 0), e = at(2, 0), f = at(0, 2);
+  const R f1 = a.x + (a.y + a.z), f2 = b.x - (b.y + b.z);
+  const R f3 = e.x + (e.y - e.z), f4 = f.x - (f.y - f.z);
+  const R s1 = f1 + f2, s2 = f3 + f4, d1 = f1 - f2, d2 = f3 - f4, D = s1 + s2;
+  const R i0 = R(2) * S + D;
+  o.I0 = R(12) * c.x + i0;
+  o.Ix = R(2) * dx + (d1 + d2);
+  o.Iy = R(2) * dy + (d1 - d2);
+  o.Ixx = R(2) * sx + D;
+  o.Iyy = R(2) * sy + D;
+  o.Ixy = s1 - s2;
+  o.G0 = o.Gx = o.Gy = o.gt = o.gx = o.gy = R(0);
   if constexpr (TH) {
-    const R ga[3] = {g[1] + g[2], g[3] + g[4], g[5] + g[6]};
-    const R ha[3] = {g[1] - g[2], g[3] - g[4], g[5] - g[6]};
-    R gs[3], e1[3], e2[3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const int q = 7 + 4 * p;
-      gs[p] = (g[q] + g[q + 1]) + (g[q + 2] + g[q + 3]);
-      e1[p] = g[q] - g[q + 1];
-      e2[p] = g[q + 2] - g[q + 3];
-    }
-    M[10] = w0 * g[0] + w1 * (ga[0] + ga[1] + ga[2]) + w2 * (gs[0] + gs[1] + gs[2]);
-    M[11] = w1 * ha[0] + w2 * ((e1[0] + e2[0]) + (e1[1] + e2[1]));
-    M[12] = w1 * ha[1] + w2 * ((e1[0] - e2[0]) + (e1[2] + e2[2]));
-    M[13] = w1 * ha[2] + w2 * ((e1[1] - e2[1]) + (e1[2] - e2[2]));
-  } else {
-    M[10] = M[11] = M[12] = M[13] = R(0);
+    __builtin_amdgcn_sched_barrier(0);
+    const R t0 = th(1, 1), tr = th(2, 1), tl = th(0, 1), tu = th(1, 2), td = th(1, 0);
+    const R T = (tr + tl) + (tu + td);
+    o.gt = R(2) * t0 + T;
+    o.gx = tr - tl;
+    o.gy = tu - td;
+    const R g1 = th(2, 2), g2 = th(0, 0), g3 = th(2, 0), g4 = th(0, 2);
+    const R p = g1 - g2, m = g3 - g4;
+    const R q0 = R(2) * T + ((g1 + g2) + (g3 + g4));
+    o.G0 = R(12) * t0 + q0;
+    o.Gx = R(2) * o.gx + (p + m);
+    o.Gy = R(2) * o.gy + (p - m);
   }
+}
+// what a node of a plane keeps until the plane above comes: its in-plane sums
+// with what the plane below sent
+template <typename R>
+struct AdjPart {
+  R I0, Ix, Iy, xx, yy, xy, mt, mx, my, T, qx, qy, gm;
+};
+template <typename R>
+__device__ inline AdjPart<R> adj_part(const AdjSums<R>& o, R mt, R mx, R my, R mxx, R myy, R gt,
+                                      R gx, R gy) {
+  return {o.I0, o.Ix, o.Iy, o.Ixx + mxx, o.Iyy + myy, o.Ixy, mt, mx, my,
+          o.G0 + gt, o.Gx + gx, o.Gy + gy, gt};
+}
+// raw moments of the 19 pulled values: rho~, u~ (3), s~ xx xy xz yy yz zz, T~,
+// q~ (3); o: the sums of the plane above
+template <typename R, bool TH>
+__device__ inline void adj_close(const AdjPart<R>& c, const AdjSums<R>& o, R M[14]) {
+  const R w = R(1.0 / 36);
+  M[0] = w * (c.I0 + (c.mt + o.pt));
+  M[1] = w * (c.Ix + (c.mx + o.px));
+  M[2] = w * (c.Iy + (c.my + o.py));
+  M[3] = w * (o.pt - c.mt);
+  M[4] = w * (c.xx + o.pxx);
+  M[5] = w * c.xy;
+  M[6] = w * (o.px - c.mx);
+  M[7] = w * (c.yy + o.pyy);
+  M[8] = w * (o.py - c.my);
+  M[9] = w * (o.pt + c.mt);
+  M[10] = TH ? w * (c.T + o.gt) : R(0);
+  M[11] = TH ? w * (c.qx + o.gx) : R(0);
+  M[12] = TH ? w * (c.qy + o.gy) : R(0);
+  M[13] = TH ? w * (o.gt - c.gm) : R(0);
 }
 
 // Least-squares completion of a face node with orientation o (see FaceFillT)
@@ -978,8 +996,8 @@ __device__ inline void face_fill(const Adj3Args<R>& a, int o, int m, R un, R Tn,
 // local terms of the adjoint moments: the probe seed, the prescribed
 // temperature inside, the T q~ coupling and the Brinkman factor of u~
 template <typename R, bool TH>
-__device__ inline void adj_local(const Adj3Args<R>& a, int k, int m, int ne, R Tn, R s,
-                                 R M[14], R u0) {
+__device__ inline void adj_local(const Adj3Args<R>& a, int m, int ne, R Tn, R s, R M[14], R u0) {
+#pragma clang fp contract(on)
   if constexpr (TH) {
     const bool probe = (m & TAG_PROBE3) && a.seed_heat != 0.0;
     if (probe) M[10] -= R(a.seed_heat) * u0;
@@ -1000,24 +1018,26 @@ __device__ inline void adj_local(const Adj3Args<R>& a, int k, int m, int ne, R T
 // moments of the interior node p
 template <typename R, bool TH>
 __device__ inline void alks3_node(const Geo3& g, const Adj3Args<R>& a, P3 p, int k, R M[14]) {
-  R f[19], gq[19];
-#pragma unroll
-  for (int q = 0; q < 19; ++q) {
-    const int cq[3] = {QX[q], QY[q], QZ[q]};
-    const int z = nbr(g, p, cq[0], cq[1], cq[2]);
-    R v = a.p0[0][z];
-#pragma unroll
-    for (int x = 0; x < 3; ++x)
-      if (cq[x]) v += R(cq[x]) * a.p0[1 + x][z];
-    f[q] = v;
-    gq[q] = TH ? a.p0[4][z] : R(0);
-  }
-  mom19<R, TH>(f, gq, M);
+  AdjSums<R> below, here, above;
+  auto plane = [&](int dz, AdjSums<R>& o) {
+    auto at = [&](int dx, int dy) {
+      const int z = nbr(g, p, dx - 1, dy - 1, dz);
+      return V4<R>{a.p0[0][z], a.p0[1][z], a.p0[2][z], a.p0[3][z]};
+    };
+    auto th = [&](int dx, int dy) { return TH ? a.p0[4][nbr(g, p, dx - 1, dy - 1, dz)] : R(0); };
+    adj_sums<R, TH>(at, th, o);
+  };
+  plane(-1, below);
+  plane(0, here);
+  plane(1, above);
+  adj_close<R, TH>(adj_part(here, below.mt, below.mx, below.my, below.mxx, below.myy, below.gt,
+                            below.gx, below.gy),
+                   above, M);
   const int m = a.mask[k];
   const R Tn = TH ? a.T[k] : R(0);
   // exact mode: u~ stays undivided; the update pass divides V instead
   const bool probe = TH && (m & TAG_PROBE3) && a.seed_heat != 0.0;
-  adj_local<R, TH>(a, k, m, 0, Tn, a.exact ? R(1) : a.inv1pa[k], M, probe ? a.u[0][k] : R(0));
+  adj_local<R, TH>(a, m, 0, Tn, a.exact ? R(1) : a.inv1pa[k], M, probe ? a.u[0][k] : R(0));
 }
 
 // moments of the face node p with orientation o. Only the 14 known
@@ -1072,7 +1092,7 @@ __device__ inline void alks3_face_node(const Geo3& g, const Adj3Args<R>& a, P3 p
   }
   face_fill<R, TH>(a, o, m, un, Tn, f, gq, M);
   const bool probe = TH && (m & TAG_PROBE3) && a.seed_heat != 0.0;
-  adj_local<R, TH>(a, k, m, 1, Tn, ip, M, probe ? a.u[0][k] : R(0));
+  adj_local<R, TH>(a, m, 1, Tn, ip, M, probe ? a.u[0][k] : R(0));
 }
 
 // ALKS pass 1 at the interior nodes; the boundary nodes are left to
@@ -1141,106 +1161,142 @@ struct AdjIn {
   double so;  // the node's accumulated sensitivity (sens_mode 1), read ahead
 };
 
-// The ALKS update at node k of a z-march column (eq:afp - eq:agq): V and
-// Theta of the new level from the node's moments (cu), the in-plane moment
-// fields E (s~xx s~xy s~xz s~yy s~yz q~x q~y T B, 1-node halo, index ci,
-// end flags ex, ey) and the z differences zd of s~xz s~yz s~zz q~z T B (z
-// window zc, zm1, zn, z2 for the product difference of the exact mode), and
-// the sensitivity 3 alpha' u.u~ - B' grad T.q~ (paper) or its exact-mode
-// counterpart.
+// in-plane moment fields of a plane, 1-node halo: s~xy T B q~x; s~xx s~xz;
+// s~yy s~yz; q~y, grouped by the differences that read them
+template <typename R>
+struct AdjE {
+  V4<R> c[NCR];
+  V2<R> x[NCR], y[NCR];
+  R q[NCR];
+};
+template <typename R>
+__device__ inline void adj_e_put(AdjE<R>& E, int ci, const R M[14], R T, R B) {
+  E.c[ci] = V4<R>{M[5], T, B, M[11]};
+  E.x[ci] = V2<R>{M[4], M[6]};
+  E.y[ci] = V2<R>{M[7], M[8]};
+  E.q[ci] = M[12];
+}
+
+// The ALKS update at a node of a z-march column (eq:afp - eq:agq): V and Theta
+// of the new level from the node's moments (cu), the plane's moment fields
+// (column ci, end flags ex, ey) and the z differences zd of s~xz s~yz s~zz q~z
+// T B (z window zc, zm1, zn, z2 for the product difference of the exact mode),
+// and the sensitivity 3 alpha' u.u~ - B' grad T.q~ (paper) or its exact-mode
+// counterpart. The node lies at offset off of the plane.
 template <typename R, bool TH>
-__device__ inline void adj3_update(const Adj3Args<R>& a, const Geo3& g, unsigned k,
-                                   const R (*E)[NCR], int ci, int ex, int ey, int ez,
+__device__ inline void adj3_update(const Adj3Args<R>& a, const Geo3& g, size_t plane, unsigned off,
+                                   const AdjE<R>& E, int ci, int ex, int ey, int ez,
                                    const AdjIn<R>& cu, const R zd[6], const R zc[6],
                                    const R zm1[6], const R zn[6], const R z2[6]) {
-  // no fused multiply-adds here: the fused step passes z differences the
-  // compiler could fold into the sums below, the update pass selects them
-  // per plane, and both must round alike
-#pragma clang fp contract(off)
-  const R S[6] = {E[0][ci], E[1][ci], E[2][ci], E[3][ci], E[4][ci], zc[2]};
+  // products are fused with sums only within a statement, so that the fused
+  // step and the update pass round alike
+#pragma clang fp contract(on)
+  struct DV {
+    R s[3], q, T, B, Bq;  // s~x. or s~y., q~x or q~y, T, B, B q~
+  };
+  auto vx = [&](int o) {
+    const V4<R> c = E.c[ci + o];
+    const V2<R> x = E.x[ci + o];
+    return DV{{x.x, c.x, x.y}, c.w, c.y, c.z, c.z * c.w};
+  };
+  auto vy = [&](int o) {
+    const V4<R> c = E.c[ci + o * CXN];
+    const V2<R> y = E.y[ci + o * CXN];
+    const R q = E.q[ci + o * CXN];
+    return DV{{c.x, y.x, y.y}, q, c.y, c.z, c.z * q};
+  };
+  auto cen = [](R p, R m) { return R(0.5) * (p - m); };
+  auto one = [](R h, R f, R f1, R f2) { return h * (R(3) * f - R(4) * f1 + f2); };
+  auto diff = [&](const DV& p, const DV& m) {
+    return DV{{cen(p.s[0], m.s[0]), cen(p.s[1], m.s[1]), cen(p.s[2], m.s[2])},
+              TH ? cen(p.q, m.q) : R(0), TH ? cen(p.T, m.T) : R(0), TH ? cen(p.B, m.B) : R(0),
+              TH ? cen(p.Bq, m.Bq) : R(0)};
+  };
+  // second-order one-sided, f1 and f2 one and two steps inwards
+  auto end = [&](int e, const DV& f, const DV& f1, const DV& f2) {
+    const R h = e < 0 ? R(-0.5) : R(0.5);
+    return DV{{one(h, f.s[0], f1.s[0], f2.s[0]), one(h, f.s[1], f1.s[1], f2.s[1]),
+               one(h, f.s[2], f1.s[2], f2.s[2])},
+              TH ? one(h, f.q, f1.q, f2.q) : R(0), TH ? one(h, f.T, f1.T, f2.T) : R(0),
+              TH ? one(h, f.B, f1.B, f2.B) : R(0), TH ? one(h, f.Bq, f1.Bq, f2.Bq) : R(0)};
+  };
+  const DV c = vx(0), cy = vy(0);
+  DV dx = diff(vx(1), vx(-1));
+  if (ex) dx = end(ex, c, vx(-ex), vx(-2 * ex));
+  __builtin_amdgcn_sched_barrier(0);
+  DV dy = diff(vy(1), vy(-1));
+  if (ey) dy = end(ey, cy, vy(-ey), vy(-2 * ey));
+  const R S[6] = {c.s[0], c.s[1], c.s[2], cy.s[1], cy.s[2], zc[2]};
   const R A2 = R(2.0 * g.A);
-  const R ds[3] = {d1(E[0], ci, 1, ex) + d1(E[1], ci, CXN, ey) + zd[0],
-                   d1(E[1], ci, 1, ex) + d1(E[3], ci, CXN, ey) + zd[1],
-                   d1(E[2], ci, 1, ex) + d1(E[4], ci, CXN, ey) + zd[2]};
   R V[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    R su = R(0);
-#pragma unroll
-    for (int b = 0; b < 3; ++b) su += S[SI[c][b]] * cu.u[b];
-    V[c] = R(3) * cu.U[c] + R(9) * su - R(3) * cu.r * cu.u[c] - A2 * ds[c];
+  for (int i = 0; i < 3; ++i) {
+    const R ds = dx.s[i] + dy.s[i] + zd[i];
+    const R su = S[SI[i][0]] * cu.u[0] + S[SI[i][1]] * cu.u[1] + S[SI[i][2]] * cu.u[2];
+    const R ru = cu.r * cu.u[i];
+    V[i] = R(3) * cu.U[i] + R(9) * su - R(3) * ru - A2 * ds;
   }
   // the Brinkman pairing of the sensitivity: 3 alpha' u.u~ (paper) or
   // alpha' u.V / (1 + alpha) with the undivided V, which then propagates
   // divided by 1 + alpha (exact)
   double pair = 0.0;
+  if (a.sens_mode) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) pair += double(cu.u[c]) * double(a.exact ? V[c] : cu.U[c]);
-  if (a.exact) {
-    pair *= double(cu.ip) / 3.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) V[c] *= cu.ip;
+    for (int i = 0; i < 3; ++i) pair += double(cu.u[i]) * double(a.exact ? V[i] : cu.U[i]);
+    if (a.exact) pair *= double(cu.ip) / 3.0;
   }
-  a.p1[0][k] = cu.r;
-  a.p1[1][k] = V[0];
-  a.p1[2][k] = V[1];
-  a.p1[3][k] = V[2];
-  R qv[3] = {R(0), R(0), R(0)};
+  if (a.exact) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) V[i] *= cu.ip;
+  }
+  const unsigned ob = off * unsigned(sizeof(R));
+  const auto* out = arg2<Adj3Args<R>>();
+  put_b(out->p1[0] + plane, ob, cu.r);
+  put_b(out->p1[1] + plane, ob, V[0]);
+  put_b(out->p1[2] + plane, ob, V[1]);
+  put_b(out->p1[3] + plane, ob, V[2]);
+  const R qv[3] = {c.q, cy.q, zc[3]};
   if constexpr (TH) {
-    qv[0] = E[5][ci];
-    qv[1] = E[6][ci];
-    qv[2] = zc[3];
     const R qu = qv[0] * cu.u[0] + qv[1] * cu.u[1] + qv[2] * cu.u[2];
-    const R* Bp = E[8];
+    R th = cu.Tt + R(3) * qu;
     if (a.exact) {
       // exact: the transpose of the forward B c.grad_h T, -div_h (B q~)
       const R zbq = dz3(ez, zc[3] * zc[5], zm1[3] * zm1[5], zn[3] * zn[5], z2[3] * z2[5]);
-      const R dbq = d1p(Bp, E[5], ci, 1, ex) + d1p(Bp, E[6], ci, CXN, ey) + zbq;
-      a.p1[4][k] = cu.Tt + R(3) * qu - dbq;
+      th -= dx.Bq + dy.Bq + zbq;
     } else {
-      const R divq = d1(E[5], ci, 1, ex) + d1(E[6], ci, CXN, ey) + zd[3];
-      const R gbq = d1(Bp, ci, 1, ex) * qv[0] + d1(Bp, ci, CXN, ey) * qv[1] + zd[5] * qv[2];
-      a.p1[4][k] = cu.Tt + R(3) * qu - Bp[ci] * divq - gbq;
+      const R divq = dx.q + dy.q + zd[3];
+      const R gbq = dx.B * qv[0] + dy.B * qv[1] + zd[5] * qv[2];
+      th = th - c.B * divq - gbq;
     }
+    put_b(out->p1[4] + plane, ob, th);
   }
   if (a.sens_mode) {
     double sv = 0.0;
     if (!ex && !ey && !ez && !(cu.mk & TAG_SOLID3)) {
       sv = a.sens_b_only ? 0.0 : double(cu.dA) * pair;
       if constexpr (TH) {
-        const R* Tp = E[7];
-        const R gt[3] = {d1(Tp, ci, 1, ex), d1(Tp, ci, CXN, ey), zd[4]};
-        double gq = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) gq += double(gt[c]) * double(qv[c]);
+        double gq = double(dx.T) * double(qv[0]);
+        gq += double(dy.T) * double(qv[1]);
+        gq += double(zd[4]) * double(qv[2]);
         sv -= double(cu.dB) * gq;
       }
     }
     // the accumulated value was read with the node's other inputs, a plane
     // ahead, so that the read-modify-write does not wait for it here
-    if (a.sens_mode == 1) a.sens[k] = cu.so + sv;
-    else a.sens[k] = sv;
+    put_b(out->sens + plane, off * 8u, a.sens_mode == 1 ? cu.so + sv : sv);
   }
 }
 
 // ALKS pass 2, z-marching: V, Theta (eq:afp - eq:agq) and the sensitivity
 // from the moments; x and y differences from an LDS plane, z differences
 // from a window of three planes in registers.
-// The update pass. LDS plane fields: s~xx s~xy s~xz s~yy s~yz (q~x q~y T B),
-// 1-node halo, two planes.
-template <typename R, bool TH>
-struct AdjELds {
-  static constexpr int NE = TH ? 9 : 5;
-  R e[2][NE][NCR];
-};
-
 // ENDS: only the two end planes of a non-periodic z axis (after the fused
 // step, which leaves them): tile chunk 0 takes plane 0, chunk 1 plane nz - 1
 template <typename R, bool TH, bool ENDS = false>
 __global__ __launch_bounds__(ZT) void alks3e_kernel(Geo3 g, Adj3Args<R> a) {
-  constexpr int NE = AdjELds<R, TH>::NE;
+  constexpr int NE = TH ? 9 : 5;  // s~xx s~xy s~xz s~yy s~yz (q~x q~y T B)
   constexpr int NZ = TH ? 6 : 3;  // z window: s~xz s~yz s~zz (q~z T B)
-  __shared__ AdjELds<R, TH> L;
+  __shared__ AdjE<R> L[2];
   ZTile t;
   if constexpr (ENDS) {
     if (!ztile(g, t, 0, 2, 2)) return;
@@ -1286,9 +1342,13 @@ __global__ __launch_bounds__(ZT) void alks3e_kernel(Geo3 g, Adj3Args<R> a) {
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       const int e = tid + r * ZT;
-      if (e < NCR)
+      if (e >= NCR) continue;
+      R M[14];
 #pragma unroll
-        for (int f = 0; f < NE; ++f) L.e[slot][f][e] = v[r][f];
+      for (int f = 0; f < 5; ++f) M[4 + f] = v[r][f];
+      M[11] = TH ? v[r][TH ? 5 : 0] : R(0);
+      M[12] = TH ? v[r][TH ? 6 : 0] : R(0);
+      adj_e_put(L[slot], e, M, TH ? v[r][TH ? 7 : 0] : R(0), TH ? v[r][TH ? 8 : 0] : R(0));
     }
   };
   auto zload = [&](int s, R z[6]) {
@@ -1354,8 +1414,8 @@ __global__ __launch_bounds__(ZT) void alks3e_kernel(Geo3 g, Adj3Args<R> a) {
 #pragma unroll
     for (int f = 0; f < 6; ++f) zd[f] = dz3(ez, zc[f], zm1[f], zn[f], z2[f]);
     if (own)
-      adj3_update<R, TH>(a, g, unsigned(p) * nxy + unsigned(n0.off), L.e[sc], ci, n0.ex, n0.ey,
-                         ez, cu, zd, zc, zm1, zn, z2);
+      adj3_update<R, TH>(a, g, size_t(p) * nxy, unsigned(n0.off), L[sc], ci, n0.ex, n0.ey, ez, cu,
+                         zd, zc, zm1, zn, z2);
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
       zm1[f] = zc[f];
@@ -1370,310 +1430,246 @@ __global__ __launch_bounds__(ZT) void alks3e_kernel(Geo3 g, Adj3Args<R> a) {
 // ---------------------------------------------------------------------------
 // One z-march per block over the planes 1 .. nz-2 of a non-periodic z axis
 // (every plane of a periodic one). At plane s every column of the tile and of
-// its 1-node ring forms its moments of plane s: an interior node pulls
-// f~_q = rho~ + c_q.V and g~_q = Theta from x + c_q (eq:afeq, eq:ageq) out
-// of three LDS plane slots of the level-(n+1) coefficients (tile plus a
-// 2-node halo; the next plane waits in registers) and applies the local
-// terms, as the pull pass does; a
-// boundary node takes the moments the face pass left in the scratch. The
-// plane's in-plane moment fields go to LDS, the column keeps its own in
-// registers, and plane s - 1 is updated (adj3_update) from the moments of
-// planes s - 2, s - 1 and s. The moments that never leave the block are not
-// stored; only the z-window moments of planes 1, 2, nz-3 and nz-2 go to the
-// scratch, for the end planes that alks3e<ENDS> updates afterwards.
-// FP32 keeps three coefficient slots and one plane of moment fields, with
-// three barriers per plane (their LDS allows three blocks per CU); FP64, held
-// to one block per CU by its registers either way, keeps four slots and two
-// moment planes with one barrier per plane
-template <typename R, bool TH>
-struct AdjFLds {
-  static constexpr int NP = TH ? 5 : 4;  // rho~, Vx, Vy, Vz (, Theta)
-  static constexpr int NE = TH ? 9 : 5;  // s~xx s~xy s~xz s~yy s~yz (q~x q~y T B)
-  static constexpr bool LEAN = sizeof(R) == 4;
-  static constexpr int NS = LEAN ? 3 : 4;
-  R p[NS][NP][NSR];
-  R e[LEAN ? 1 : 2][NE][NCR];
-};
-
-// node of a column at one plane: index, class, boundary count, T, B and
-// 1/(1 + alpha)
+// its 1-node ring forms the sums of plane s (adj_sums) from the level-(n+1)
+// coefficients in LDS (tile plus a 2-node halo; the next plane waits in
+// registers). They close the moments of plane s - 1 (eq:afeq, eq:ageq), to which
+// the local terms are applied as in the pull pass; a boundary node takes the
+// moments the face pass left in the scratch. Plane s - 2 is then updated
+// (adj3_update) from its in-plane moment fields in LDS and the own column's
+// moments of planes s - 3, s - 2 and s - 1, after which the fields of plane s - 1
+// and the coefficients of plane s + 1 take their places in LDS. The moments
+// that never leave the block are not stored; only the z-window moments of
+// planes 1, 2, nz-3 and nz-2 go to the scratch, for the end planes that
+// alks3e<ENDS> updates afterwards.
+// Bound by instructions. Reading the 19 values of a node from three planes of
+// LDS took 157 us on 256 x 128 x 128 in FP32 and 58 us on 97 x 61 x 53 in FP64;
+// this way it is 121 and 41 us, 523 MB passing below the L2 in the first (4.3
+// TB/s, a copy reaches 6.2).
 template <typename R>
-struct ColIn {
-  unsigned k;
-  int m, ne, valid;
-  R T, B, ip;
+struct AdjFLds {
+  V4<R> p[NSR];  // rho~, V of plane s
+  R t[NSR];      // Theta
+  AdjE<R> e;     // moment fields of plane s - 2
 };
 
 template <typename R, bool TH>
-__global__ __launch_bounds__(ZT) void alks3f_kernel(Geo3 g, Adj3Args<R> a) {
-  constexpr int NP = AdjFLds<R, TH>::NP, NS = AdjFLds<R, TH>::NS;
-  constexpr bool LEAN = AdjFLds<R, TH>::LEAN;
+__global__ __launch_bounds__(ZT, sizeof(R) == 4 ? 3 : 1) void alks3f_kernel(Geo3 g, Adj3Args<R> a) {
   constexpr int NM = TH ? 14 : 10;
-  __shared__ AdjFLds<R, TH> L;
+  __shared__ AdjFLds<R> L;
   const int pz = g.periodic & 4;
   ZTile t;
   if (!ztile(g, t, pz ? 0 : 1, pz ? g.nz : g.nz - 1)) return;
   const int tid = int(threadIdx.x), lx = tid % ZX, ly = tid / ZX;
-  const unsigned nxy = unsigned(g.nx) * unsigned(g.ny);
+  const size_t nxy = size_t(g.nx) * size_t(g.ny);
   const size_t N = size_t(g.N);
-  int roff[SRL];
-  zregion(g, t, roff);
+  // byte offsets in a plane of the thread's elements of the 2-node halo region;
+  // an element off the domain reads the plane's first node, which nothing uses
+  unsigned roff[SRL];
+  {
+    int off[SRL];
+    zregion(g, t, off);
+#pragma unroll
+    for (int r = 0; r < SRL; ++r)
+      roff[r] = off[r] < 0 ? 0u : unsigned(off[r]) * unsigned(sizeof(R));
+  }
   const ZNode n0 = znode(g, t, lx, ly, lx < t.w && ly < t.h);
-  const ZNode n1 = zring(g, t);
+  ZNode n1 = zring(g, t);
+  n1.on = n1.on && n1.off >= 0;
   const bool own = n0.on && t.x0 + lx >= t.xo && t.y0 + ly >= t.yo;
-  const R* F[NP];
-#pragma unroll
-  for (int f = 0; f < NP; ++f) F[f] = a.p0[f];
-  // planes that exist (INT_MIN: none, to skip a column's inputs)
-  auto has = [&](int q) { return q != INT_MIN && (pz || (q >= 0 && q < g.nz)); };
-  const int base = t.z0 - 2;  // first plane held in the LDS slots
-  auto slot = [&](int q) { return (q - base) % NS; };
-  const int last = t.z1 + 1;  // last plane the pulls read
-  R v[SRL][NP];
-  auto load = [&](int q) {
-    zload<R, NP>(F, has(q), unsigned(zwrap(q, g.nz)) * nxy, roff, v);
-  };
-  auto store = [&](int q) { zstore<R, NP>(L.p[slot(q)], v); };
-  auto col_in = [&](const ZNode& n, int q, ColIn<R>& c) {
-    c.k = 0;
-    c.m = c.ne = c.valid = 0;
-    c.T = c.B = c.ip = R(0);
-    if (!n.on || n.off < 0 || !has(q)) return;
-    const int zq = zwrap(q, g.nz);
-    c.k = unsigned(zq) * nxy + unsigned(n.off);
-    c.valid = 1;
-    c.ne = (n.ex != 0) + (n.ey != 0) + (endof(zq, g.nz, pz) != 0);
-    c.m = a.mask[c.k];
-    if constexpr (TH) {
-      c.T = a.T[c.k];
-      c.B = a.B[c.k];
+  const bool xy0 = n0.ex || n0.ey, xy1 = n1.ex || n1.ey;
+  // offsets in a plane, and the positions from which the LDS reads count up
+  unsigned off0 = n0.on ? unsigned(n0.off) : 0u, off1 = n1.on ? unsigned(n1.off) : 0u;
+  unsigned i0 = unsigned(n0.lds - SX - 1), i1 = unsigned(n1.lds - SX - 1);
+  unsigned e0 = unsigned(n0.ci), e1 = unsigned(n1.ci);
+  auto has = [&](int q) { return pz || (q >= 0 && q < g.nz); };
+  // first node of plane q (of the nearest one that exists)
+  auto plane = [&](int q) {
+    if (pz) {
+      const int c = zwrap(q, g.nz);
+      return size_t(c < 0 ? c + g.nz : (c >= g.nz ? c - g.nz : c)) * nxy;  // nz >= 3, -4 <= q < nz + 4
     }
-    if (!a.exact && !c.ne) c.ip = a.inv1pa[c.k];
+    return size_t(q < 0 ? 0 : (q >= g.nz ? g.nz - 1 : q)) * nxy;
   };
-  // the face pass's moments of a boundary node (all NM for the own column,
-  // the in-plane fields for a ring column) and the probe's velocity, read at
-  // the top of the plane so that their latency hides behind the pulls
-  auto bnd_in = [&](const ColIn<R>& c, bool all, R Mb[14], R& u0) {
+  auto zend = [&](int q) { return !pz && (q <= 0 || q >= g.nz - 1); };
+  V4<R> v[SRL];
+  R vt[SRL];
+  auto load = [&](const auto* in, size_t b) {
+    const R *F0 = in->p0[0] + b, *F1 = in->p0[1] + b, *F2 = in->p0[2] + b, *F3 = in->p0[3] + b;
+    const R* F4 = TH ? in->p0[4] + b : F0;
 #pragma unroll
-    for (int i = 0; i < 14; ++i) Mb[i] = R(0);
-    u0 = R(0);
-    if (!c.valid) return;
-    if (c.ne) {
-#pragma unroll
-      for (int i = 0; i < NM; ++i)
-        if (all || i == 4 || i == 5 || i == 6 || i == 7 || i == 8 || i == 11 || i == 12)
-          Mb[i] = a.m[size_t(i) * N + c.k];
-    } else if (TH && (c.m & TAG_PROBE3) && a.seed_heat != 0.0) {
-      u0 = a.u[0][c.k];
+    for (int r = 0; r < SRL; ++r) {
+      v[r].x = at_b(F0, roff[r]);
+      v[r].y = at_b(F1, roff[r]);
+      v[r].z = at_b(F2, roff[r]);
+      v[r].w = at_b(F3, roff[r]);
+      if constexpr (TH) vt[r] = at_b(F4, roff[r]);
     }
   };
-  // moments of a column's node at plane q
-  auto moments = [&](const ZNode& n, const ColIn<R>& c, int q, const R Mb[14], R u0, R M[14]) {
+  auto store = [&]() {
 #pragma unroll
-    for (int i = 0; i < 14; ++i) M[i] = R(0);
-    if (!c.valid) return;
-    if (c.ne) {
-#pragma unroll
-      for (int i = 0; i < 14; ++i) M[i] = Mb[i];
-      return;
-    }
-    const int sl[3] = {slot(q - 1), slot(q), slot(q + 1)};
-    R f[19], gq[19];
-#pragma unroll
-    for (int d = 0; d < 19; ++d) {
-      const int o = n.lds + QX[d] + QY[d] * SX;
-      const int pl = sl[QZ[d] + 1];
-      R x = L.p[pl][0][o];
-      if (QX[d]) x += R(QX[d]) * L.p[pl][1][o];
-      if (QY[d]) x += R(QY[d]) * L.p[pl][2][o];
-      if (QZ[d]) x += R(QZ[d]) * L.p[pl][3][o];
-      f[d] = x;
-      gq[d] = TH ? L.p[pl][TH ? 4 : 0][o] : R(0);
-    }
-    mom19<R, TH>(f, gq, M);
-    adj_local<R, TH>(a, int(c.k), c.m, 0, c.T, a.exact ? R(1) : c.ip, M, u0);
+    for (int r = 0; r < SRL; ++r)
+      if ((r + 1) * ZT <= NSR || tid + r * ZT < NSR) {
+        L.p[tid + r * ZT] = v[r];
+        if constexpr (TH) L.t[tid + r * ZT] = vt[r];
+      }
   };
-  auto store_e = [&](const ZNode& n, const R M[14], const ColIn<R>& c, int sl) {
-    if (!n.on) return;
-    R(*E)[NCR] = L.e[sl];
-    E[0][n.ci] = M[4];
-    E[1][n.ci] = M[5];
-    E[2][n.ci] = M[6];
-    E[3][n.ci] = M[7];
-    E[4][n.ci] = M[8];
-    if constexpr (TH) {
-      E[TH ? 5 : 0][n.ci] = M[11];
-      E[TH ? 6 : 0][n.ci] = M[12];
-      E[TH ? 7 : 0][n.ci] = c.T;
-      E[TH ? 8 : 0][n.ci] = c.B;
-    }
+  // class, T and B of a column's node
+  struct Col {
+    int m;
+    R T, B;
   };
-  // the own node's inputs of the update at plane q
-  auto upd_in = [&](int q, AdjIn<R>& u) {
-    u.r = u.Tt = u.dA = u.dB = R(0);
-    u.ip = R(1);
-    u.mk = 0;
-    u.so = 0.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) u.U[c] = u.u[c] = R(0);
-    if (!own || !has(q)) return;
-    const unsigned k = unsigned(zwrap(q, g.nz)) * nxy + unsigned(n0.off);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) u.u[c] = a.u[c][k];
-    u.mk = a.mask[k];
-    if (a.exact) u.ip = a.inv1pa[k];
-    if (a.sens_mode) {
-      u.dA = a.dA3[k];
-      if constexpr (TH) u.dB = a.dB[k];
-      if (a.sens_mode == 1) u.so = a.sens[k];
-    }
+  auto col_in = [&](const auto* in, size_t b, unsigned off) {
+    const unsigned ob = off * unsigned(sizeof(R));
+    return Col{int(at_b(in->mask + b, off)), TH ? at_b(in->T + b, ob) : R(0),
+               TH ? at_b(in->B + b, ob) : R(0)};
   };
-  // the planes z0 - 2 .. z0 in the slots, z0 + 1 in flight
-  load(base);
-  store(base);
-  load(base + 1);
-  store(base + 1);
-  load(base + 2);
-  store(base + 2);
-  load(base + 3);
-  ColIn<R> c0, c1;
-  col_in(n0, t.z0 - 1, c0);
-  col_in(n1, t.z0 - 1, c1);
-  AdjIn<R> ucur, unext;
-  upd_in(INT_MIN, ucur);
-  R Mc[14];
+  // sums of the plane in LDS
+  auto sums = [&](unsigned i, AdjSums<R>& o) {
+    adj_sums<R, TH>([&](int dx, int dy) { return L.p[i + unsigned(dy * SX + dx)]; },
+                    [&](int dx, int dy) { return TH ? L.t[i + unsigned(dy * SX + dx)] : R(0); }, o);
+  };
+  const int first = t.z0 - 2, last = t.z1 + 1;  // planes the sums are taken of
+  load(&a, plane(first));
+  store();
+  Col c0 = col_in(&a, plane(first), off0);  // own node at plane s - 1
+  int mc = 0;                           // class of the own node at plane s - 2
+  AdjPart<R> P0 = {}, P1 = {};  // partial moments of the columns at plane s - 1
+  // what plane s - 1 sends to plane s: t, x, y, xx, yy; T, x, y
+  R m0[8] = {}, m1[8] = {};
+  R Mc[5] = {};  // rho~, u~, T~ of the own node at plane s - 2
+  R zm1[6] = {}, zc[6] = {}, zn[6] = {};
+  const R z0v[6] = {};
+  lds_barrier();
+  // first nodes of the planes s - 2 .. s + 1
+  size_t b2 = plane(first - 2), b1 = plane(first - 1), b0 = plane(first), bn = plane(first + 1);
+  for (int s = first; s <= last; ++s) {
+    off0 = anew(off0);
+    off1 = anew(off1);
+    i0 = anew(i0);
+    i1 = anew(i1);
+    e0 = anew(e0);
+    e1 = anew(e1);
 #pragma unroll
-  for (int i = 0; i < 14; ++i) Mc[i] = R(0);
-  R zm1[6], zc[6], zn[6];
-  const R z0v[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
+    for (int r = 0; r < SRL; ++r) roff[r] = anew(roff[r]);
+    const unsigned ob0 = off0 * unsigned(sizeof(R));
+    const auto* in = arg2<Adj3Args<R>>();
+    // Inputs of the update, of the ring's E fields and of the own node's next
+    // closing, and the face pass's moments of boundary nodes; then the next plane
+    AdjIn<R> cu;
+    cu.dA = cu.dB = R(0);
+    cu.ip = R(1);
+    cu.so = 0.0;
 #pragma unroll
-  for (int f = 0; f < 6; ++f) zm1[f] = zc[f] = R(0);
-  // FP32, three barriers per plane: the pulls of plane s read three
-  // coefficient slots; after them plane s + 2 takes the slot of plane s - 1
-  // and the update of plane s - 1 reads the in-plane moment fields; after
-  // that plane s replaces them
-  if constexpr (LEAN) {
-    for (int s = t.z0 - 1; s <= t.z1; ++s) {
-      lds_barrier();
-      ColIn<R> c0n, c1n;
-      col_in(n0, s + 1 <= t.z1 ? s + 1 : INT_MIN, c0n);
-      col_in(n1, s + 1 <= t.z1 ? s + 1 : INT_MIN, c1n);
-      upd_in(s >= t.z0 && s < t.z1 ? s : INT_MIN, unext);
-      // (in FP64 the own column's reads wait until the ring column is done:
-      // held across its pulls they cost more registers than they save)
-      R M[14], Mr[14], Mb0[14], u00;
-      if constexpr (sizeof(R) == 4) bnd_in(c0, true, Mb0, u00);
-      {
-        R Mb1[14], u01;
-        bnd_in(c1, false, Mb1, u01);
-        moments(n1, c1, s, Mb1, u01, Mr);
-      }
-      if constexpr (sizeof(R) != 4) bnd_in(c0, true, Mb0, u00);
-      moments(n0, c0, s, Mb0, u00, M);
-      lds_barrier();
-      if (s + 2 <= last) store(s + 2);
-      if (s + 3 <= last) load(s + 3);
-      zn[0] = M[6];
-      zn[1] = M[8];
-      zn[2] = M[9];
-      zn[3] = TH ? M[13] : R(0);
-      zn[4] = c0.T;
-      zn[5] = c0.B;
-      if (own && s - 1 >= t.z0) {
-        AdjIn<R> cu = ucur;
-        cu.r = Mc[0];
+    for (int c = 0; c < 3; ++c) cu.u[c] = R(0);
+    Col c0n = {}, c1 = {};
+    if (n0.on) c0n = col_in(in, b0, off0);
+    if (own && s - 2 >= t.z0) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cu.U[c] = Mc[1 + c];
-        cu.Tt = TH ? Mc[10] : R(0);
-        R zd[6];
-#pragma unroll
-        for (int f = 0; f < 6; ++f) zd[f] = dz3(0, zc[f], zm1[f], zn[f], R(0));
-        adj3_update<R, TH>(a, g, unsigned(zwrap(s - 1, g.nz)) * nxy + unsigned(n0.off), L.e[0],
-                           n0.ci, n0.ex, n0.ey, 0, cu, zd, zc, zm1, zn, z0v);
-      }
-      // the z-window moments next to the end planes, for alks3e<ENDS>
-      if (!pz && own && c0.valid && !c0.ne && s >= t.z0 && s < t.z1 &&
-          (s <= 2 || s >= g.nz - 3)) {
-        a.m[6 * N + c0.k] = M[6];
-        a.m[8 * N + c0.k] = M[8];
-        a.m[9 * N + c0.k] = M[9];
-        if constexpr (TH) a.m[13 * N + c0.k] = M[13];
-      }
-      lds_barrier();
-      store_e(n1, Mr, c1, 0);
-      store_e(n0, M, c0, 0);
-#pragma unroll
-      for (int f = 0; f < 6; ++f) {
-        zm1[f] = zc[f];
-        zc[f] = zn[f];
-      }
-#pragma unroll
-      for (int i = 0; i < 14; ++i) Mc[i] = M[i];
-      ucur = unext;
-      c0 = c0n;
-      c1 = c1n;
+      for (int c = 0; c < 3; ++c) cu.u[c] = at_b(in->u[c] + b2, ob0);
+      cu.ip = at_b(in->inv1pa + b2, ob0);
+      cu.dA = at_b(in->dA3 + b2, ob0);
+      cu.dB = TH ? at_b(in->dB + b2, ob0) : R(0);
+      if (a.sens_mode == 1) cu.so = at_b(in->sens + b2, anew(off0) * 8u);
     }
-  } else {
-    // FP64, one barrier per plane: plane s + 2 goes to the fourth slot and
-    // the moment fields alternate between two planes
-    for (int s = t.z0 - 1; s <= t.z1; ++s) {
-      lds_barrier();
-      if (s + 2 <= last) store(s + 2);
-      if (s + 3 <= last) load(s + 3);
-      ColIn<R> c0n, c1n;
-      col_in(n0, s + 1 <= t.z1 ? s + 1 : INT_MIN, c0n);
-      col_in(n1, s + 1 <= t.z1 ? s + 1 : INT_MIN, c1n);
-      upd_in(s >= t.z0 && s < t.z1 ? s : INT_MIN, unext);
-      // (in FP64 the own column's reads wait until the ring column is done:
-      // held across its pulls they cost more registers than they save)
-      R M[14], Mb0[14], u00;
-      if constexpr (sizeof(R) == 4) bnd_in(c0, true, Mb0, u00);
-      {
-        R Mr[14], Mb1[14], u01;
-        bnd_in(c1, false, Mb1, u01);
-        moments(n1, c1, s, Mb1, u01, Mr);
-        store_e(n1, Mr, c1, s & 1);
-      }
-      if constexpr (sizeof(R) != 4) bnd_in(c0, true, Mb0, u00);
-      moments(n0, c0, s, Mb0, u00, M);
-      store_e(n0, M, c0, s & 1);
-      zn[0] = M[6];
-      zn[1] = M[8];
-      zn[2] = M[9];
-      zn[3] = TH ? M[13] : R(0);
-      zn[4] = c0.T;
-      zn[5] = c0.B;
-      if (own && s - 1 >= t.z0) {
-        AdjIn<R> cu = ucur;
-        cu.r = Mc[0];
+    const bool close = s >= t.z0;  // plane s - 1 is one whose moments are used
+    const bool bnd0 = xy0 || zend(s - 1), bnd1 = xy1 || zend(s - 1);
+    R M[14], Mr[14];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cu.U[c] = Mc[1 + c];
-        cu.Tt = TH ? Mc[10] : R(0);
-        R zd[6];
+    for (int i = 0; i < 14; ++i) M[i] = Mr[i] = R(0);
+    if (close) {
+      if (n1.on) c1 = col_in(in, b1, off1);
+      if (n0.on && bnd0)
 #pragma unroll
-        for (int f = 0; f < 6; ++f) zd[f] = dz3(0, zc[f], zm1[f], zn[f], R(0));
-        adj3_update<R, TH>(a, g, unsigned(zwrap(s - 1, g.nz)) * nxy + unsigned(n0.off),
-                           L.e[(s - 1) & 1], n0.ci, n0.ex, n0.ey, 0, cu, zd, zc, zm1, zn, z0v);
-      }
-      // the z-window moments next to the end planes, for alks3e<ENDS>
-      if (!pz && own && c0.valid && !c0.ne && s >= t.z0 && s < t.z1 &&
-          (s <= 2 || s >= g.nz - 3)) {
-        a.m[6 * N + c0.k] = M[6];
-        a.m[8 * N + c0.k] = M[8];
-        a.m[9 * N + c0.k] = M[9];
-        if constexpr (TH) a.m[13 * N + c0.k] = M[13];
-      }
+        for (int i = 0; i < NM; ++i) M[i] = at_b(in->m + (size_t(i) * N + b1), ob0);
+      if (n1.on && bnd1)
 #pragma unroll
-      for (int f = 0; f < 6; ++f) {
-        zm1[f] = zc[f];
-        zc[f] = zn[f];
-      }
-#pragma unroll
-      for (int i = 0; i < 14; ++i) Mc[i] = M[i];
-      ucur = unext;
-      c0 = c0n;
-      c1 = c1n;
+        for (int i = 4; i < NM; ++i)
+          if (i < 9 || i == 11 || i == 12)
+            Mr[i] = at_b(in->m + (size_t(i) * N + b1), off1 * unsigned(sizeof(R)));
     }
+    load(in, bn);
+    if (n0.on) {
+      AdjSums<R> o;
+      sums(i0, o);
+      if (close && !bnd0) {
+        adj_close<R, TH>(P0, o, M);
+        if (TH && ((c0.m >> 2) & 3) == THERM_DIRICHLET3) M[11] = M[12] = M[13] = R(0);
+      }
+      P0 = adj_part(o, m0[0], m0[1], m0[2], m0[3], m0[4], m0[5], m0[6], m0[7]);
+      const R nm[8] = {o.mt, o.mx, o.my, o.mxx, o.myy, o.gt, o.gx, o.gy};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m0[i] = nm[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (n1.on) {
+      AdjSums<R> o;
+      sums(i1, o);
+      if (close && !bnd1) {
+        adj_close<R, TH>(P1, o, Mr);
+        if (TH && ((c1.m >> 2) & 3) == THERM_DIRICHLET3) Mr[11] = Mr[12] = R(0);
+      }
+      P1 = adj_part(o, m1[0], m1[1], m1[2], m1[3], m1[4], m1[5], m1[6], m1[7]);
+      const R nm[8] = {o.mt, o.mx, o.my, o.mxx, o.myy, o.gt, o.gx, o.gy};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m1[i] = nm[i];
+    }
+    zn[0] = M[6];
+    zn[1] = M[8];
+    zn[2] = M[9];
+    zn[3] = M[13];
+    zn[4] = c0.T;
+    zn[5] = c0.B;
+    if (own && s - 2 >= t.z0) {
+      if (!xy0) {
+        R m[14];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) m[c] = Mc[c];
+        m[10] = Mc[4];
+        m[11] = L.e.c[e0].w;
+        m[12] = L.e.q[e0];
+        m[13] = zc[3];
+        adj_local<R, TH>(a, mc, 0, zc[4], a.exact ? R(1) : cu.ip, m, cu.u[0]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) Mc[c] = m[c];
+        Mc[4] = m[10];
+      }
+      cu.mk = mc;
+      cu.r = Mc[0];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cu.U[c] = Mc[1 + c];
+      cu.Tt = Mc[4];
+      R zd[6];
+#pragma unroll
+      for (int f = 0; f < 6; ++f) zd[f] = dz3(0, zc[f], zm1[f], zn[f], R(0));
+      adj3_update<R, TH>(a, g, b2, off0, L.e, int(e0), n0.ex, n0.ey, 0, cu, zd, zc, zm1, zn, z0v);
+    }
+    // the z-window moments next to the end planes, for alks3e<ENDS>
+    const int q = s - 1;
+    if (!pz && own && !bnd0 && q >= t.z0 && q < t.z1 && (q <= 2 || q >= g.nz - 3)) {
+      put_b(a.m + (6 * N + b1), ob0, M[6]);
+      put_b(a.m + (8 * N + b1), ob0, M[8]);
+      put_b(a.m + (9 * N + b1), ob0, M[9]);
+      if constexpr (TH) put_b(a.m + (13 * N + b1), ob0, M[13]);
+    }
+    lds_barrier();
+    if (n1.on) adj_e_put(L.e, int(e1), Mr, c1.T, c1.B);
+    if (n0.on) adj_e_put(L.e, int(e0), M, c0.T, c0.B);
+    store();
+    lds_barrier();
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      zm1[f] = zc[f];
+      zc[f] = zn[f];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Mc[i] = M[i];
+    Mc[4] = M[10];
+    mc = c0.m;
+    c0 = c0n;
+    b2 = b1;
+    b1 = b0;
+    b0 = bn;
+    bn = plane(s + 2);
   }
 }
 
