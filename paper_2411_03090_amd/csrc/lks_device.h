@@ -279,8 +279,8 @@ struct Geo3 {
   int nx, ny, nz, N;
   int periodic;     // bit 0: x, bit 1: y, bit 2: z
   int thermal;
-  int zc, zca;      // z-planes per block: LKS step, ALKS update pass (>= 2)
-  int zcf;          // z-planes per block of the fused ALKS step (>= 2)
+  int zc, zca;      // chunks of the z axis: LKS step, ALKS update pass (<= nz / 2)
+  int zcf;          // chunks of the fused ALKS step
   int fused;        // ALKS step: 1 fused z-march, 0 pull, face and update passes
   double A;         // eq:A
   double Bf;        // B of the fluid, used on boundary nodes
@@ -379,8 +379,8 @@ struct Adj3Args {
 int blocks3(int N);  // blocks of a node-parallel 3D launch (multiple of 8)
 // blocks of the z-marching step kernels, each with one objective accumulator
 int zblocks3(const Geo3& g);
-// z-planes per block for the device: each kernel's launch fills whole rounds of
-// its resident blocks
+// chunks of the z axis: before the device is known, and for the device
+int zchunks_default(int nz);
 void zplan3(Geo3& g, int rsz);
 // edge and corner nodes in increasing order (out may be null); returns the count
 int copy_nodes3(const Geo3& g, int* out);

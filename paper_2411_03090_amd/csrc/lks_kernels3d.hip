@@ -202,10 +202,7 @@ constexpr int CXN = ZX + 2, NCR = CXN * (ZY + 2);  // tile + 1-node halo
 constexpr int SRL = (NSR + ZT - 1) / ZT;           // halo-region loads per thread
 static_assert(ZT == NT3, "one block size for the 3D kernels");
 
-__host__ __device__ inline int zchunks(const Geo3& g) {
-  const int zc = g.zc < 2 ? 2 : g.zc;
-  return g.nz / zc > 1 ? g.nz / zc : 1;
-}
+__host__ __device__ inline int zchunks(const Geo3& g) { return g.zc; }
 __host__ __device__ inline int ztiles(int n, int t) { return (n + t - 1) / t; }
 
 struct ZTile {
@@ -344,7 +341,8 @@ __device__ inline void zregion(const Geo3& g, const ZTile& t, int off[SRL]) {
 // Bound by instructions. Forming all 19 values at the source and sending each
 // behind a test of its target, with a branch for each difference, took 135 us
 // on 256 x 128 x 128 in FP32 and 74 us on 97 x 61 x 53 in FP64; this way it is
-// 76 and 41 us (172 MB of FP32 traffic, 28 us at the rate of a copy).
+// 75 and 41 us, and 29 us in whole rounds of blocks (172 MB of FP32 traffic, 28 us
+// at the rate of a copy).
 template <typename R>
 struct alignas(2 * sizeof(R)) V2 {
   R x, y;
@@ -1706,39 +1704,46 @@ int blocks3(int N) {
 int zblocks3(const Geo3& g) { return ztiles(g.nx, ZX) * ztiles(g.ny, ZY) * zchunks(g); }
 
 namespace {
-// planes per chunk so that tiles x chunks fills whole rounds of the kernel's
-// resident blocks (one round when the grid allows)
+// Chunks a march of the planes is split into: the number for which the rounds of
+// the kernel's resident blocks, times the planes a block walks through (its
+// chunk and halo planes more), are fewest. On 97 x 61 x 53 (32 tiles, FP64) the
+// forward step takes 30 us with 16 chunks and 41 us with the 17 of three planes
+// that overflow one round.
 template <typename K>
-int zplanes(const Geo3& g, K kernel, int nt = ZT) {
+int chunks_for(const Geo3& g, K kernel, int planes, int halo) {
   int dev = 0, ncu = 0, bpc = 0;
+  const int most = g.nz / 2 > 1 ? g.nz / 2 : 1;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, kernel, nt, 0) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, kernel, ZT, 0) != hipSuccess ||
       ncu <= 0 || bpc <= 0)
-    return 16;
-  const int tiles = ztiles(g.nx, ZX) * ztiles(g.ny, ZY);
-  int nch = (bpc * ncu) / tiles;
-  if (nch < 1) nch = 1;
-  if (nch > g.nz / 2) nch = g.nz / 2 > 1 ? g.nz / 2 : 1;
-  const int zc = g.nz / nch;
-  return zc < 2 ? 2 : zc;
+    return zchunks_default(g.nz);
+  const long long tiles = (long long)ztiles(g.nx, ZX) * ztiles(g.ny, ZY), res = (long long)bpc * ncu;
+  long long best = LLONG_MAX;
+  int nch = 1;
+  for (int n = 1; n <= most; ++n) {
+    const long long cost = ((tiles * n + res - 1) / res) * ((planes + n - 1) / n + halo);
+    if (cost < best) {
+      best = cost;
+      nch = n;
+    }
+  }
+  return nch;
 }
 }  // namespace
 
+int zchunks_default(int nz) { return nz / 16 > 1 ? nz / 16 : 1; }
+
+template <typename R, bool TH>
+void zplan3(Geo3& g) {
+  const int pz = g.periodic & 4;
+  g.zc = chunks_for(g, lks3z_kernel<R, TH>, g.nz, 2);
+  g.zca = chunks_for(g, alks3e_kernel<R, TH>, g.nz, 2);
+  g.zcf = chunks_for(g, alks3f_kernel<R, TH>, pz ? g.nz : g.nz - 2, 4);
+}
 void zplan3(Geo3& g, int rsz) {
-  if (rsz == 8) {
-    g.zc = g.thermal ? zplanes(g, lks3z_kernel<double, true>) : zplanes(g, lks3z_kernel<double, false>);
-    g.zca = g.thermal ? zplanes(g, alks3e_kernel<double, true>)
-                      : zplanes(g, alks3e_kernel<double, false>);
-    g.zcf = g.thermal ? zplanes(g, alks3f_kernel<double, true>)
-                      : zplanes(g, alks3f_kernel<double, false>);
-  } else {
-    g.zc = g.thermal ? zplanes(g, lks3z_kernel<float, true>) : zplanes(g, lks3z_kernel<float, false>);
-    g.zca = g.thermal ? zplanes(g, alks3e_kernel<float, true>)
-                      : zplanes(g, alks3e_kernel<float, false>);
-    g.zcf = g.thermal ? zplanes(g, alks3f_kernel<float, true>)
-                      : zplanes(g, alks3f_kernel<float, false>);
-  }
+  if (rsz == 8) g.thermal ? zplan3<double, true>(g) : zplan3<double, false>(g);
+  else g.thermal ? zplan3<float, true>(g) : zplan3<float, false>(g);
 }
 
 int copy_nodes3(const Geo3& g, int* out) {

@@ -1288,7 +1288,7 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
     g3.A = g.A;
     g3.Bf = g.Bf;
     g3.drho_out = g.drho_out;
-    g3.zc = g3.zca = g3.zcf = 16;  // re-planned for the device at bind
+    g3.zc = g3.zca = g3.zcf = lks::zchunks_default(g3.nz);  // planned for the device at bind
     g3.fused = 1;
     lks::build_face_fill(g3.A, g3.Bf, c->ops3);
     c->copy3h.resize(size_t(lks::copy_nodes3(g3, nullptr)));
