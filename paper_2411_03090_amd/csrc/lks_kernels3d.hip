@@ -1038,61 +1038,6 @@ __device__ inline void alks3_node(const Geo3& g, const Adj3Args<R>& a, P3 p, int
   adj_local<R, TH>(a, m, 0, Tn, a.exact ? R(1) : a.inv1pa[k], M, probe ? a.u[0][k] : R(0));
 }
 
-// moments of the face node p with orientation o. Only the 14 known
-// populations are read, at offsets formed from the orientation, so that all
-// their loads are in flight together; read direction by direction behind a test
-// of c.n each one waited for the last (57.7 us on 256 x 128 x 128 in FP32 with a
-// 5 x 19 operator per orientation, now 47.5; 97 x 61 x 53 FP64 23.1, now 18.9).
-template <typename R, bool TH>
-__device__ inline void alks3_face_node(const Geo3& g, const Adj3Args<R>& a, P3 p, int k, int o,
-                                       R M[14]) {
-  const int ax = o >> 1, sg = (o & 1) ? 1 : -1;
-  // steps along the normal (inwards) and the tangents; a face node has
-  // neighbours along its tangents, wrapped on a periodic axis
-  const int c[3] = {p.i, p.j, p.l}, n3[3] = {g.nx, g.ny, g.nz};
-  const int st[3] = {1, g.nx, g.nx * g.ny};
-  auto at = [&](const int (&x)[3], int e) { return e == 0 ? x[0] : (e == 1 ? x[1] : x[2]); };
-  auto side = [&](int e, int d) {
-    const int x = at(c, e), n = at(n3, e), s = at(st, e);
-    return (x + d < 0 ? n - 1 : (x + d >= n ? 1 - n : d)) * s;
-  };
-  const int a1 = ax == 2 ? 0 : ax + 1, a2 = ax == 0 ? 2 : ax - 1;
-  const int in = -sg * at(st, ax);
-  const int p1 = side(a1, 1), m1 = side(a1, -1), p2 = side(a2, 1), m2 = side(a2, -1);
-  const int off[14] = {0,       p1,      m1,      p2, m2,      p1 + p2, p1 + m2,
-                       m1 + p2, m1 + m2, in, in + p1, in + m1, in + p2, in + m2};
-  constexpr int C1[14] = {0, 1, -1, 0, 0, 1, 1, -1, -1, 0, 1, -1, 0, 0};
-  constexpr int C2[14] = {0, 0, 0, 1, -1, 1, -1, 1, -1, 0, 0, 0, 1, -1};
-  const R* const V[3] = {a.p0[1], a.p0[2], a.p0[3]};
-  const R* Vn = ax == 0 ? V[0] : (ax == 1 ? V[1] : V[2]);
-  const R* V1 = a1 == 0 ? V[0] : (a1 == 1 ? V[1] : V[2]);
-  const R* V2 = a2 == 0 ? V[0] : (a2 == 1 ? V[1] : V[2]);
-  R f[14], gq[14], vn[5], v1[14], v2[14];
-#pragma unroll
-  for (int q = 0; q < 14; ++q) {
-    const int z = k + off[q];
-    f[q] = a.p0[0][z];
-    if (q >= 9) vn[q - 9] = Vn[z];
-    if (C1[q]) v1[q] = V1[z];
-    if (C2[q]) v2[q] = V2[z];
-    gq[q] = TH ? a.p0[4][z] : R(0);
-  }
-  const int m = a.mask[k];
-  const R Tn = TH ? a.T[k] : R(0);
-  const R* un_src = ax == 0 ? a.u[0] : (ax == 1 ? a.u[1] : a.u[2]);
-  const R un = TH ? R(sg) * un_src[k] : R(0);
-  const R ip = a.exact ? R(1) : a.inv1pa[k];
-#pragma unroll
-  for (int q = 0; q < 14; ++q) {
-    if (q >= 9) f[q] -= R(sg) * vn[q - 9];
-    if (C1[q]) f[q] += R(C1[q]) * v1[q];
-    if (C2[q]) f[q] += R(C2[q]) * v2[q];
-  }
-  face_fill<R, TH>(a, o, m, un, Tn, f, gq, M);
-  const bool probe = TH && (m & TAG_PROBE3) && a.seed_heat != 0.0;
-  adj_local<R, TH>(a, m, 1, Tn, ip, M, probe ? a.u[0][k] : R(0));
-}
-
 // ALKS pass 1 at the interior nodes; the boundary nodes are left to
 // alks3_face_kernel, so the face completion does not diverge inside the
 // waves of the rows that end on an x face
@@ -1111,27 +1056,149 @@ __global__ __launch_bounds__(NT3) void alks3_pull_kernel(Geo3 g, Adj3Args<R> a) 
   for (int c = 0; c < NM; ++c) a.m[c * N + k] = mom[c];
 }
 
-// ALKS pass 1 at the boundary nodes of the host-built list (faces grouped by
-// orientation, then edges and corners, which take the moments of the node
-// one step inwards along y and z)
+// Tiles of the face nodes: a block takes FP x FQ nodes of one face, p along the
+// axis with the smaller stride (64 x 4 where that is x, whose rows are contiguous,
+// 16 x 16 on the x faces). The face nodes of an axis: all of a periodic one, else
+// those that are not at its ends.
+struct FaceTiles {
+  int np, nq;  // face nodes along p and q
+  int tp, tq;  // tiles
+};
+__host__ __device__ inline FaceTiles face_tiles(const Geo3& g, int ax) {
+  const int n[3] = {g.nx - ((g.periodic & 1) ? 0 : 2), g.ny - ((g.periodic & 2) ? 0 : 2),
+                    g.nz - ((g.periodic & 4) ? 0 : 2)};
+  FaceTiles t;
+  t.np = ax == 0 ? n[1] : n[0];
+  t.nq = ax == 2 ? n[1] : n[2];
+  const int FP = ax == 0 ? 16 : 64, FQ = NT3 / FP;
+  t.tp = (t.np + FP - 1) / FP;
+  t.tq = (t.nq + FQ - 1) / FQ;
+  return t;
+}
+
+// ALKS pass 1 at the boundary nodes: blocks of face tiles (two faces of each
+// non-periodic axis), then the host-built list of the edge and corner nodes that
+// copy the moments of an interior node (those that copy a face node's are written
+// with it; all of them lie on the x faces).
+// A tile's rho~, V and Theta of the face plane and the plane inwards (all that
+// the 14 known populations need) pass through LDS: on the x faces, where every
+// node has a cache line of its own, the block reads each line it needs once and
+// not once per population. Bound by latency: 48 us on 256 x 128 x 128 in FP32 (160k
+// boundary nodes) and 19 us on 97 x 61 x 53 in FP64 with 50 reads per node, 23 and
+// 12 us this way.
 template <typename R, bool TH>
 __global__ __launch_bounds__(NT3) void alks3_face_kernel(Geo3 g, Adj3Args<R> a) {
-  const int t = int(blockIdx.x) * NT3 + int(threadIdx.x);
-  if (t >= a.nface) return;
-  const int k = a.face[t];
-  const P3 p = decode(g, k);
-  int o;
-  const int ne = ends(g, p, &o);
-  R mom[14];
-  // edges and corners take the moments of the node one step inwards
-  const P3 s = ne >= 2 ? copy_src(g, p) : p;
-  const int ks = (s.l * g.ny + s.j) * g.nx + s.i;
-  if (ends(g, s, &o)) alks3_face_node<R, TH>(g, a, s, ks, o, mom);
-  else alks3_node<R, TH>(g, a, s, ks, mom);
-  const size_t N = size_t(g.N);
   constexpr int NM = TH ? 14 : 10;
+  constexpr int NREG = (64 + 2) * (4 + 2);  // tile with a 1-node halo, the larger one
+  // face plane: rho~, V1, V2, Theta; plane inwards: rho~, Vn, V1, V2, Theta
+  __shared__ R L[TH ? 9 : 7][NREG];
+  const int tid = int(threadIdx.x);
+  const size_t N = size_t(g.N);
+  int b = int(blockIdx.x), ax = 0, face = -1;
+  FaceTiles ft{};
+  for (; ax < 3; ++ax) {
+    if ((g.periodic >> ax) & 1) continue;
+    ft = face_tiles(g, ax);
+    const int nt = ft.tp * ft.tq;
+    if (b < 2 * nt) {
+      face = b / nt;
+      b -= face * nt;
+      break;
+    }
+    b -= 2 * nt;
+  }
+  if (face < 0) {
+    const int t = b * NT3 + tid;
+    if (t >= a.nface) return;
+    const int k = a.face[t];
+    const P3 s = copy_src(g, decode(g, k));
+    R mom[14];
+    alks3_node<R, TH>(g, a, s, (s.l * g.ny + s.j) * g.nx + s.i, mom);
 #pragma unroll
-  for (int c = 0; c < NM; ++c) a.m[c * N + k] = mom[c];
+    for (int c = 0; c < NM; ++c) a.m[c * N + k] = mom[c];
+    return;
+  }
+  const int sg = face ? 1 : -1;
+  const int FP = ax == 0 ? 16 : 64, FQ = NT3 / FP, PW = FP + 2;
+  // axes p, q: extents, strides and periodicity
+  const int ap = ax == 0 ? 1 : 0, aq = ax == 2 ? 1 : 2;
+  const int st[3] = {1, g.nx, g.nx * g.ny}, n3[3] = {g.nx, g.ny, g.nz};
+  auto at3 = [](const int (&x)[3], int e) { return e == 0 ? x[0] : (e == 1 ? x[1] : x[2]); };
+  const int Np = at3(n3, ap), Nq = at3(n3, aq), sp = at3(st, ap), sq = at3(st, aq);
+  const int perp = (g.periodic >> ap) & 1, perq = (g.periodic >> aq) & 1;
+  const int sn = at3(st, ax), kn = face ? (at3(n3, ax) - 1) * sn : 0;
+  const int p0 = (b % ft.tp) * FP, q0 = (b / ft.tp) * FQ;  // within the face nodes
+  const int lop = perp ? 0 : 1, loq = perq ? 0 : 1;
+  // the node of this thread
+  const int lp = tid % FP, lq = tid / FP;
+  const bool on = p0 + lp < ft.np && q0 + lq < ft.nq;
+  const int cp = p0 + lp + lop, cq = q0 + lq + loq;
+  const int k = on ? kn + cp * sp + cq * sq : 0;
+  const R* Vn = ax == 0 ? a.p0[1] : (ax == 1 ? a.p0[2] : a.p0[3]);
+  const R* V1 = ax == 0 ? a.p0[2] : (ax == 1 ? a.p0[3] : a.p0[1]);
+  const R* V2 = ax == 0 ? a.p0[3] : (ax == 1 ? a.p0[1] : a.p0[2]);
+#pragma unroll
+  for (int r = 0; r < (NREG + NT3 - 1) / NT3; ++r) {
+    const int e = tid + r * NT3;
+    if (e >= PW * (FQ + 2)) continue;
+    // wrapped on a periodic axis; positions beyond the last node are not used
+    const int i = p0 + e % PW - 1 + lop, j = q0 + e / PW - 1 + loq;
+    const int ci = i < 0 ? i + Np : (i >= Np ? (perp ? (i - Np) % Np : Np - 1) : i);
+    const int cj = j < 0 ? j + Nq : (j >= Nq ? (perq ? (j - Nq) % Nq : Nq - 1) : j);
+    const int z = kn + ci * sp + cj * sq, y = z - sg * sn;
+    L[0][e] = a.p0[0][z];
+    L[1][e] = V1[z];
+    L[2][e] = V2[z];
+    L[3][e] = a.p0[0][y];
+    L[4][e] = Vn[y];
+    L[5][e] = V1[y];
+    L[6][e] = V2[y];
+    if constexpr (TH) {
+      L[TH ? 7 : 0][e] = a.p0[4][z];
+      L[TH ? 8 : 0][e] = a.p0[4][y];
+    }
+  }
+  const int m = a.mask[k];
+  const R Tn = TH ? a.T[k] : R(0);
+  const R* us = ax == 0 ? a.u[0] : (ax == 1 ? a.u[1] : a.u[2]);
+  const R un = TH ? R(sg) * us[k] : R(0);
+  const R ip = a.exact ? R(1) : a.inv1pa[k];
+  const bool probe = TH && (m & TAG_PROBE3) && a.seed_heat != 0.0;
+  const R u0 = probe ? a.u[0][k] : R(0);
+  __syncthreads();
+  if (!on) return;
+  // steps of the tangents t1, t2 (the axes after the normal's) in the tile
+  const int i0 = (lq + 1) * PW + lp + 1;
+  const int s1 = ax == 1 ? PW : 1, s2 = ax == 1 ? 1 : PW;
+  constexpr int C1[14] = {0, 1, -1, 0, 0, 1, 1, -1, -1, 0, 1, -1, 0, 0};
+  constexpr int C2[14] = {0, 0, 0, 1, -1, 1, -1, 1, -1, 0, 0, 0, 1, -1};
+  R f[14], gq[14], M[14];
+#pragma unroll
+  for (int q = 0; q < 14; ++q) {
+    const int i = i0 + C1[q] * s1 + C2[q] * s2;
+    R x = L[q < 9 ? 0 : 3][i];
+    if (q >= 9) x -= R(sg) * L[4][i];
+    if (C1[q]) x += R(C1[q]) * L[q < 9 ? 1 : 5][i];
+    if (C2[q]) x += R(C2[q]) * L[q < 9 ? 2 : 6][i];
+    f[q] = x;
+    gq[q] = TH ? L[TH ? (q < 9 ? 7 : 8) : 0][i] : R(0);
+  }
+  face_fill<R, TH>(a, 2 * ax + face, m, un, Tn, f, gq, M);
+  adj_local<R, TH>(a, m, 1, Tn, ip, M, u0);
+#pragma unroll
+  for (int c = 0; c < NM; ++c) a.m[c * N + k] = M[c];
+  if (ax != 0) return;
+  // the edges and corners of an x face copy the node one step inwards
+  const int j[3] = {cp, cp == 1 && !perp ? 0 : -1, cp == Np - 2 && !perp ? Np - 1 : -1};
+  const int l[3] = {cq, cq == 1 && !perq ? 0 : -1, cq == Nq - 2 && !perq ? Nq - 1 : -1};
+#pragma unroll
+  for (int x = 0; x < 9; ++x) {
+    const int jj = j[x % 3], ll = l[x / 3];
+    if (x == 0 || jj < 0 || ll < 0) continue;
+    const int z = kn + jj * sp + ll * sq;
+#pragma unroll
+    for (int c = 0; c < NM; ++c) a.m[c * N + z] = M[c];
+  }
 }
 
 // in-plane offsets of the thread's elements of the 1-node halo region; -1
@@ -1763,29 +1830,31 @@ int copy_nodes3(const Geo3& g, int* out) {
   return n;
 }
 
-int face_nodes3(const Geo3& g, int* out) {
-  const int n3[3] = {g.nx, g.ny, g.nz};
-  std::vector<int> bucket[7];  // orientations 0..5, then edges and corners
-  for (int l = 0; l < g.nz; ++l)
-    for (int j = 0; j < g.ny; ++j)
-      for (int i = 0; i < g.nx; ++i) {
-        const int c[3] = {i, j, l};
-        int ne = 0, o = -1;
-        for (int ax = 0; ax < 3; ++ax) {
-          if ((g.periodic >> ax) & 1) continue;
-          if (c[ax] == 0) { ++ne; o = 2 * ax; }
-          else if (c[ax] == n3[ax] - 1) { ++ne; o = 2 * ax + 1; }
-        }
-        if (ne) bucket[ne >= 2 ? 6 : o].push_back((l * g.ny + j) * g.nx + i);
-      }
+int edge_nodes3(const Geo3& g, int* out) {
+  const bool py = g.periodic & 2, pz = g.periodic & 4, px = g.periodic & 1;
+  if (py || pz) return 0;
   int n = 0;
-  for (const auto& v : bucket)
-    for (int k : v) {
-      if (out) out[n] = k;
-      ++n;
-    }
+  for (int l : {0, g.nz - 1})
+    for (int j : {0, g.ny - 1})
+      for (int i = px ? 0 : 1; i < (px ? g.nx : g.nx - 1); ++i) {
+        if (out) out[n] = (l * g.ny + j) * g.nx + i;
+        ++n;
+      }
   return n;
 }
+
+namespace {
+// blocks of alks3_face_kernel
+unsigned face_blocks(const Geo3& g, int nedge) {
+  int n = (nedge + NT3 - 1) / NT3;
+  for (int ax = 0; ax < 3; ++ax) {
+    if ((g.periodic >> ax) & 1) continue;
+    const FaceTiles t = face_tiles(g, ax);
+    n += 2 * t.tp * t.tq;
+  }
+  return unsigned(n);
+}
+}  // namespace
 
 template <typename R>
 void launch_coef3(const Geo3& g, const uint8_t* mask, const double* gamma, double alpha_max,
@@ -1824,8 +1893,8 @@ void launch_alks3_fused(const Geo3& g0, const Adj3Args<R>& a, hipStream_t s) {
   Geo3 g = g0;
   g.zc = g0.zcf;
   const unsigned nz = unsigned(NXCD * ((zblocks3(g) + NXCD - 1) / NXCD));
-  const unsigned nf = unsigned((a.nface + NT3 - 1) / NT3);
-  if (a.nface) alks3_face_kernel<R, TH><<<nf, NT3, 0, s>>>(g, a);
+  const unsigned nf = face_blocks(g, a.nface);
+  if (nf) alks3_face_kernel<R, TH><<<nf, NT3, 0, s>>>(g, a);
   alks3f_kernel<R, TH><<<nz, ZT, 0, s>>>(g, a);
   if (!(g.periodic & 4)) {
     const int ends = 2 * ztiles(g.nx, ZX) * ztiles(g.ny, ZY);
@@ -1844,14 +1913,14 @@ void launch_alks3_step(const Geo3& g0, const Adj3Args<R>& a, hipStream_t s) {
   g.zc = g0.zca;
   const unsigned nb = unsigned(blocks3(g.N));
   const unsigned nz = unsigned(NXCD * ((zblocks3(g) + NXCD - 1) / NXCD));
-  const unsigned nf = unsigned((a.nface + NT3 - 1) / NT3);
+  const unsigned nf = face_blocks(g, a.nface);
   if (g.thermal) {
     alks3_pull_kernel<R, true><<<nb, NT3, 0, s>>>(g, a);
-    if (a.nface) alks3_face_kernel<R, true><<<nf, NT3, 0, s>>>(g, a);
+    if (nf) alks3_face_kernel<R, true><<<nf, NT3, 0, s>>>(g, a);
     alks3e_kernel<R, true><<<nz, ZT, 0, s>>>(g, a);
   } else {
     alks3_pull_kernel<R, false><<<nb, NT3, 0, s>>>(g, a);
-    if (a.nface) alks3_face_kernel<R, false><<<nf, NT3, 0, s>>>(g, a);
+    if (nf) alks3_face_kernel<R, false><<<nf, NT3, 0, s>>>(g, a);
     alks3e_kernel<R, false><<<nz, ZT, 0, s>>>(g, a);
   }
 }

@@ -114,7 +114,7 @@ struct lks_ctx {
   lks::FaceFillT<double> ops3{};
   lks::FaceFillT<float> ops3_f{};
   int* copy3 = nullptr;  // D3Q19 edge and corner nodes (device)
-  int* face3 = nullptr;  // D3Q19 boundary nodes by orientation (device)
+  int* face3 = nullptr;  // D3Q19 edge nodes that copy an interior node (device)
   void* M3 = nullptr;    // D3Q19 adjoint moments of one step
   std::vector<int> copy3h, face3h;
   double* acc = nullptr; // per-tile objective accumulators
@@ -210,7 +210,7 @@ size_t base_bytes(const lks_ctx* c) {
   if (c->dim == 3) {
     b += align256(lks::FACE_OPS_BYTES);  // face operators
     b += align256(sizeof(int) * c->copy3h.size());  // edge and corner nodes
-    b += align256(sizeof(int) * c->face3h.size());  // boundary nodes
+    b += align256(sizeof(int) * c->face3h.size());  // edge nodes of the adjoint
     b += align256(size_t(moments3_fields(c)) * N * r);
   } else {
     b += align256(lks::RING_OPS_BYTES);  // ring completion and accumulators
@@ -1293,8 +1293,8 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
     lks::build_face_fill(g3.A, g3.Bf, c->ops3);
     c->copy3h.resize(size_t(lks::copy_nodes3(g3, nullptr)));
     lks::copy_nodes3(g3, c->copy3h.data());
-    c->face3h.resize(size_t(lks::face_nodes3(g3, nullptr)));
-    lks::face_nodes3(g3, c->face3h.data());
+    c->face3h.resize(size_t(lks::edge_nodes3(g3, nullptr)));
+    lks::edge_nodes3(g3, c->face3h.data());
   }
   c->stream = static_cast<hipStream_t>(hip_stream);
   c->budget = mem_budget_bytes;
@@ -1441,7 +1441,7 @@ lks_status lks_bind_workspace(lks_ctx* c, void* dev_ptr, size_t bytes) {
                    "upload edge nodes", &st) &&
             hip_ok(c, hipMemcpyAsync(c->face3, c->face3h.data(), sizeof(int) * c->face3h.size(),
                                      hipMemcpyHostToDevice, c->stream),
-                   "upload boundary nodes", &st)
+                   "upload edge nodes of the adjoint", &st)
       : hip_ok(c, hipMemcpyAsync(c->d_ops, ops_src, ops_bytes, hipMemcpyHostToDevice, c->stream),
                "upload ring operators", &st);
   if (!ops_ok ||
