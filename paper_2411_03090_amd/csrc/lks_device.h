@@ -203,6 +203,7 @@ struct MultiShape {
 struct MultiPlan {
   int k = 0, ntx = 0, nty = 0, variant = 0;
 };
+constexpr int MARCH = 3;  // variant of the marching kernels (lks_march.hip)
 // where the level after each step of a forward launch is kept (drho, ux, uy,
 // T; ux null: not kept, drho null: without density)
 template <typename R>
@@ -432,6 +433,13 @@ void launch_alks_step2(const Geo& g, const AdjArgs<float>& a, hipStream_t s);
 // the last entry of the inflow table; a.d1 ... are not used (lv). Adjoint:
 // a.ux, a.uy, a.T are not used (sv).
 MultiPlan multi_plan(const Geo& g, int rsz, bool adjoint, int max_tiles);
+// large grids: waves that march along y (steady sweeps without temperature on
+// a bounded domain; k = 0 elsewhere); forward: a.d1 ... take the last level
+MultiPlan march_plan(const Geo& g, int rsz);
+template <typename R>
+void launch_lks_march(const Geo& g, int steps, const FwdArgs<R>& a, hipStream_t s);
+template <typename R>
+void launch_alks_march(const Geo& g, int steps, const AdjArgs<R>& a, hipStream_t s);
 // batches: steps per launch kf, ka (0: the tile kernels run the batch) on tiles
 // of at most `tile` nodes along each axis, and the block variants
 struct BatchPlan {

@@ -871,6 +871,13 @@ void with_block(bool th, int variant, F&& f) {
 template <typename R>
 void launch_lks_multi(const Geo& g, const MultiPlan& p, int steps, const FwdArgs<R>& a,
                       const MultiLevels<R>& lv, hipStream_t s) {
+  if (p.variant == MARCH) {
+    FwdArgs<R> b = a;
+    b.d1 = lv.f[steps - 1][0];
+    b.ux1 = lv.f[steps - 1][1];
+    b.uy1 = lv.f[steps - 1][2];
+    return launch_lks_march<R>(g, steps, b, s);
+  }
   const MultiShape ms{p.ntx, p.nty, steps};
   with_block<R, false>(g.thermal, p.variant, [&](auto th, auto nt, auto npt, auto nmax) {
     lks_multi_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>
@@ -880,6 +887,7 @@ void launch_lks_multi(const Geo& g, const MultiPlan& p, int steps, const FwdArgs
 template <typename R>
 void launch_alks_multi(const Geo& g, const MultiPlan& p, int steps, const AdjArgs<R>& a,
                        const MultiStates<R>& sv, hipStream_t s) {
+  if (p.variant == MARCH) return launch_alks_march<R>(g, steps, a, s);
   const MultiShape ms{p.ntx, p.nty, steps};
   with_block<R, true>(g.thermal, p.variant, [&](auto th, auto nt, auto npt, auto nmax) {
     alks_multi_kernel<R, decltype(th)::value, nt.value, npt.value, nmax.value>

@@ -86,12 +86,14 @@ __device__ inline void ring_at(const Geo& g, const RingSet& s, int t, int* i, in
 // LDS finite difference along one axis at position p of a field with the
 // given step: central (e = 0), or second-order one-sided at the low (e = 1)
 // or high (e = -1) end of the axis. Without branches: a wave of ring nodes
-// holds all three kinds, and each branch would wait for LDS on its own.
+// holds all three kinds, and each branch would wait for LDS on its own. The
+// product by 3 is the one that rounds, and is fused here rather than where the
+// compiler likes, so that all kernels round alike.
 template <typename R>
 __device__ inline R end_f(R f0, R f1, R f2, int e) {
   const R mid = R(0.5) * (f1 - f2);
-  const R lo = R(0.5) * (R(-3) * f0 + R(4) * f1 - f2);
-  const R hi = R(0.5) * (R(3) * f0 - R(4) * f1 + f2);
+  const R lo = R(0.5) * (__builtin_elementwise_fma(R(-3), f0, R(4) * f1) - f2);
+  const R hi = R(0.5) * (__builtin_elementwise_fma(R(3), f0, R(-4) * f1) + f2);
   return e == 0 ? mid : (e > 0 ? lo : hi);
 }
 template <typename R>

@@ -1305,6 +1305,8 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
                                                   ? std::max(lks::RING_ACC, max_tiles(g))
                                                   : 1 << 20);
     c->ma = lks::multi_plan(g, c->rsz, true, 1 << 20);
+    const lks::MultiPlan march = lks::march_plan(g, c->rsz);
+    if (c->mode != LKS_UNSTEADY && march.k) c->mf = c->ma = march;
   }
   st = plan_memory(c);
   if (st != LKS_OK) {

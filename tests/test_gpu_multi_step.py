@@ -56,6 +56,15 @@ def test_steady(nx, ny, n, m, prec):
     _same(W.steady_channel_uniform(nx, ny, seed=3, n_fwd=n, n_adj=m), prec)
 
 
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "mixed"])
+@pytest.mark.parametrize("nx,ny,n,m", [(1251, 1000, 1, 1), (1800, 1670, 7, 8), (128, 9800, 6, 7),
+                                       (129, 23300, 5, 4), (9801, 129, 8, 7)])
+def test_steady_large(nx, ny, n, m, prec):
+    """The marching kernels: odd sides, strips whose last lanes lie off the grid,
+    two strips, chunks of a few rows, remainders of two and three steps."""
+    _same(W.steady_channel_uniform(nx, ny, seed=3, n_fwd=n, n_adj=m), prec)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 @pytest.mark.parametrize("n", [7, 70, 201])
 def test_heat_source(n, prec):
