@@ -445,6 +445,16 @@ void launch_alks_march(const Geo& g, int steps, const AdjArgs<R>& a, hipStream_t
 struct BatchPlan {
   int tile = 0, kf = 0, vf = 0, ka = 0, va = 0;
 };
+// ... of the marching kernels (vf = MARCH; `tile` rows per chunk), the waves of a
+// design under it, and `steps` <= kf, ka steps of every design
+BatchPlan march_batch_plan(const Geo* const* g, int n, int rsz);
+int march_waves(const Geo& g, int k, int rows);
+template <typename R>
+void launch_lks_march_batch(const BatchFwd<R>* d, const int* tmap, int total, const BatchPlan& p,
+                            int steps, int parity, hipStream_t s);
+template <typename R>
+void launch_alks_march_batch(const BatchAdj<R>* d, const int* tmap, int total, const BatchPlan& p,
+                             int steps, int parity, int last, hipStream_t s);
 BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool thermal);
 void multi_batch_tiles(const Geo& g, int tile, int* ntx, int* nty);
 bool multi_fits(const Geo& g, int ntx, int nty, int rsz, bool adjoint, int variant, int steps);

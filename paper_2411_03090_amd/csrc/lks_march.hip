@@ -52,17 +52,27 @@ __device__ inline T& at(T* p, size_t row, int col) {
   return *reinterpret_cast<T*>(reinterpret_cast<C*>(p + row) + unsigned(col) * unsigned(sizeof(T)));
 }
 
-// strips of K steps: consecutive ones overlap by the 4K lanes that only feed others
-__host__ __device__ inline int strips(int nx, int K) {
-  return nx <= 64 ? 1 : (nx - 4 * K + 64 - 4 * K - 1) / (64 - 4 * K);
-}
-
-// The waves of a launch: ntx strips, cut into nty chunks of rows, the strips at
-// the ends of x into nte; the chunks at the ends of y are `pad` rows shorter.
+// The waves of a launch of up to k steps: ntx strips, consecutive ones
+// overlapping by the 4k lanes that only feed others, cut into nty chunks of rows,
+// the strips at the ends of x into nte; the chunks at the ends of y are `pad`
+// rows shorter. The strips at the ends of x form more values and choose among
+// them, and the chunks at the ends of y push some rows one by one: with the same
+// rows as the others they end a launch late (2048 x 2048 FP32 adjoint: 31 us per
+// step instead of 19), so they get a third of the rows and 24 rows less.
 struct MarchShape {
-  int ntx, nty, nte, pad;
+  int k, ntx, nty, nte, pad;
   __host__ __device__ int waves() const { return max(ntx - 2, 0) * nty + min(ntx, 2) * nte; }
 };
+__host__ __device__ inline MarchShape march_shape(int nx, int ny, int k, int nty) {
+  const int most = max(ny / 8, 1), w = 64 - 4 * k;
+  MarchShape ms;
+  ms.k = k;
+  ms.ntx = nx <= 64 ? 1 : (nx - 4 * k + w - 1) / w;
+  ms.nty = max(1, min(nty, most));
+  ms.nte = min(3 * ms.nty, most);
+  ms.pad = max(0, min(24, ny / ms.nte - 8));
+  return ms;
+}
 
 template <int K>
 __device__ inline Strip strip_of(const Geo& g, int t, const MarchShape& ms) {
@@ -71,23 +81,29 @@ __device__ inline Strip strip_of(const Geo& g, int t, const MarchShape& ms) {
   const bool in = t < nin;
   const int q = in ? t : t - nin, per = in ? mid : nend, n = in ? ms.nty : ms.nte;
   const int by = q / per, bx = in ? 1 + q % per : (q % per) * (ms.ntx - 1);
-  const int lane_ = int(threadIdx.x) & 63;
-  const int X0 = bx * (64 - 4 * K);
+  const int l = int(threadIdx.x) & 63, h = 2 * ms.k;
   auto row = [&](int b) {
     const int y = int((long long)b * (g.ny + 2 * ms.pad) / n) - ms.pad;
-    return b == n ? g.ny : max(y, 0);
+    return b == n ? g.ny : min(max(y, 0), g.ny);
   };
   c.nx = g.nx;
   c.ny = g.ny;
-  c.i = X0 + lane_;
+  c.i = bx * (64 - 2 * h) + l;
   c.ic = min(c.i, g.nx - 1);
-  c.y0 = min(row(by), g.ny);
-  c.y1 = min(row(by + 1), g.ny);
+  c.y0 = row(by);
+  c.y1 = row(by + 1);
   c.Y0 = max(c.y0 - 2 * K, 0);
   c.ex = end_of(c.i, g.nx, 0);
   c.xe = bx == 0 || bx == ms.ntx - 1;
-  c.own = c.i < g.nx && (bx == 0 || lane_ >= 2 * K) && (bx == ms.ntx - 1 || lane_ < 64 - 2 * K);
+  c.own = c.i < g.nx && (bx == 0 || l >= h) && (bx == ms.ntx - 1 || l < 64 - h);
   return c;
+}
+// index of this wave among `total`, or -1
+__device__ inline int march_wave(int total) {
+  const int b = xcd_tile((total + 3) / 4);
+  if (b < 0) return -1;
+  const int t = __builtin_amdgcn_readfirstlane(4 * b + (int(threadIdx.x) >> 6));
+  return t < total ? t : -1;
 }
 
 // How much of the boundary a push has to handle: nothing, the columns at the
@@ -287,11 +303,8 @@ __device__ __forceinline__ void march_chunk(const Strip& c, F&& read, P&& push, 
 }
 
 template <typename R, int K>
-__global__ __launch_bounds__(256) void lks_march_kernel(Geo g, FwdArgs<R> a, MarchShape ms) {
-  const int b = xcd_tile((ms.waves() + 3) / 4);
-  if (b < 0) return;
-  const int t = __builtin_amdgcn_readfirstlane(4 * b + (int(threadIdx.x) >> 6));
-  if (t >= ms.waves()) return;
+__device__ __forceinline__ void march_fwd(const Geo& g, const FwdArgs<R>& a, int t,
+                                          const MarchShape& ms) {
   FwdMarch<R, K> w{a, g, strip_of<K>(g, t, ms), R(g.A)};
   const Strip& c = w.c;
   FwdLevel<R> L[K] = {};
@@ -461,11 +474,8 @@ __device__ __forceinline__ void adj_push(const AdjMarch<R>& w, AdjLevel<R>* L, i
 }
 
 template <typename R, int K>
-__global__ __launch_bounds__(256) void alks_march_kernel(Geo g, AdjArgs<R> a, MarchShape ms) {
-  const int b = xcd_tile((ms.waves() + 3) / 4);
-  if (b < 0) return;
-  const int t = __builtin_amdgcn_readfirstlane(4 * b + (int(threadIdx.x) >> 6));
-  if (t >= ms.waves()) return;
+__device__ __forceinline__ void march_adj(const Geo& g, const AdjArgs<R>& a, int t,
+                                          const MarchShape& ms) {
   AdjMarch<R> w{a, g, strip_of<K>(g, t, ms)};
   const Strip& c = w.c;
   AdjLevel<R> L[K] = {};
@@ -495,6 +505,75 @@ __global__ __launch_bounds__(256) void alks_march_kernel(Geo g, AdjArgs<R> a, Ma
       });
 }
 
+// ---------------------------------------------------------------------------
+// kernels
+// ---------------------------------------------------------------------------
+template <typename R, int K>
+__global__ __launch_bounds__(256) void lks_march_kernel(Geo g, FwdArgs<R> a, MarchShape ms) {
+  const int t = march_wave(ms.waves());
+  if (t < 0) return;
+  march_fwd<R, K>(g, a, t, ms);
+}
+template <typename R, int K>
+__global__ __launch_bounds__(256) void alks_march_kernel(Geo g, AdjArgs<R> a, MarchShape ms) {
+  const int t = march_wave(ms.waves());
+  if (t < 0) return;
+  march_adj<R, K>(g, a, t, ms);
+}
+
+// chunks of about `rows` rows of a design of a batch
+__host__ __device__ inline MarchShape batch_shape(const Geo& g, int k, int rows) {
+  return march_shape(g.nx, g.ny, k, (g.ny + rows - 1) / rows);
+}
+// batches: tmap holds the design and the wave within it; k is the step count of
+// the plan, whose waves a launch of K <= k steps takes
+template <typename R, int K>
+__global__ __launch_bounds__(256) void lks_march_batch_kernel(const BatchFwd<R>* __restrict__ d,
+                                                              const int* __restrict__ tmap,
+                                                              int total, int k, int rows,
+                                                              int parity) {
+  const int t = march_wave(total);
+  if (t < 0) return;
+  const int di = tmap[2 * t];
+  const Geo g = d[di].g;
+  FwdArgs<R> a = d[di].a[parity];
+  a.level_mid = a.level_out;
+  march_fwd<R, K>(g, a, tmap[2 * t + 1], batch_shape(g, k, rows));
+}
+template <typename R, int K>
+__global__ __launch_bounds__(256) void alks_march_batch_kernel(const BatchAdj<R>* __restrict__ d,
+                                                               const int* __restrict__ tmap,
+                                                               int total, int k, int rows,
+                                                               int parity, int last) {
+  const int t = march_wave(total);
+  if (t < 0) return;
+  const int di = tmap[2 * t];
+  const Geo g = d[di].g;
+  AdjArgs<R> a = d[di].a[parity];
+  a.sens_mode = last ? 2 : 0;
+  march_adj<R, K>(g, a, tmap[2 * t + 1], batch_shape(g, k, rows));
+}
+
+// Waves of a launch: one per SIMD in FP64 and two in FP32, what the registers of
+// three and two steps allow. A second round of waves costs more than it hides
+// (2048 x 2048 FP32 adjoint, 8 % over one round: 31 instead of 19 us).
+constexpr int round_waves(int rsz) { return (rsz == 8 ? 1024 : 2048) - 8; }
+
+// f(K) for the launch of `steps` steps
+template <int RSZ, typename F>
+void with_steps(int steps, F&& f) {
+  if (steps == 1) f(std::integral_constant<int, 1>());
+  else if (steps == 2) f(std::integral_constant<int, 2>());
+  else if constexpr (RSZ == 8) f(std::integral_constant<int, 3>());
+}
+template <int RSZ>
+MarchShape shape_for(const Geo& g, int k) {
+  const int ntx = march_shape(g.nx, g.ny, k, 1).ntx;
+  return march_shape(g.nx, g.ny, k,
+                     round_waves(RSZ) / (std::max(ntx - 2, 0) + 3 * std::min(ntx, 2)));
+}
+unsigned blocks_of(int waves) { return unsigned(xcd_blocks((waves + 3) / 4)); }
+
 }  // namespace
 
 // The march needs one round of waves whose chunks are well over 4K rows tall.
@@ -514,48 +593,75 @@ MultiPlan march_plan(const Geo& g, int rsz) {
   return p;
 }
 
-namespace {
-// f(K, shape, blocks) for the launch of `steps` steps. One wave per SIMD in FP64
-// and two in FP32: what the registers of three and two steps allow, and a second
-// round of waves costs more than it hides (2048 x 2048 FP32 adjoint, 8 % over
-// one round: 31 instead of 19 us). The strips at the ends of x form more values
-// and choose among them, and the chunks at the ends of y push some rows one by
-// one: alone in their time they would end a launch late (FP32 31 us), so they
-// get a third of the rows and 24 rows less.
-template <int RSZ, typename F>
-void with_steps(const Geo& g, int steps, F&& f) {
-  auto go = [&](auto k) {
-    constexpr int K = decltype(k)::value;
-    const int waves = (RSZ == 8 ? 1024 : 2048) - 8, most = g.ny / 8;
-    MarchShape ms;
-    ms.ntx = strips(g.nx, K);
-    ms.nty = std::max(1, std::min(waves / (std::max(ms.ntx - 2, 0) + 3 * std::min(ms.ntx, 2)), most));
-    ms.nte = std::min(3 * ms.nty, most);
-    ms.pad = std::max(0, std::min(24, g.ny / ms.nte - 8));
-    f(k, ms, unsigned(xcd_blocks((ms.waves() + 3) / 4)));
-  };
-  if (steps == 1) go(std::integral_constant<int, 1>());
-  else if (steps == 2) go(std::integral_constant<int, 2>());
-  else if constexpr (RSZ == 8) go(std::integral_constant<int, 3>());
+int march_waves(const Geo& g, int k, int rows) { return batch_shape(g, k, rows).waves(); }
+
+// Batches: the same lines on the nodes of all designs, in the shortest chunks
+// of which all waves fit one round. us per step of all designs, several-steps
+// kernels -> march (forward, adjoint): FP32 32 designs of 128 to 512, 3.2M nodes, 43.9,
+// 38.3 -> 27.8, 25.1; 256 of 128 x 128 89.8, 56.3 -> 75.8, 55.9; 10 of 380 x 380 21.0,
+// 18.5 -> 14.8, 16.0. In FP64 half the waves share the work and the rows at the
+// ends of a small design outweigh the others: 64 of 256 x 256 75, 64 -> 108, 111, 16 of
+// 512 x 512 68, 62 -> 62, 65, 2 of 900 x 900 26.4, 23.5 -> 17.8, 19.4, so only large
+// designs march.
+BatchPlan march_batch_plan(const Geo* const* g, int n, int rsz) {
+  BatchPlan p;
+  long long N = 0;
+  for (int d = 0; d < n; ++d) {
+    if (g[d]->thermal || g[d]->periodic) return p;
+    N += g[d]->N;
+  }
+  if (N < (rsz == 8 ? std::max(1LL << 20, 750000LL * n) : 1250000)) return p;
+  const int k = rsz == 8 && N >= 3000000 ? 3 : 2;
+  for (int rows = 8; rows <= (1 << 14); rows += std::max(1, rows / 32)) {
+    long long waves = 0;
+    for (int d = 0; d < n; ++d) waves += march_waves(*g[d], k, rows);
+    if (waves > round_waves(rsz)) continue;
+    p.tile = rows;
+    p.kf = p.ka = k;
+    p.vf = p.va = MARCH;
+    break;
+  }
+  return p;
 }
-}  // namespace
 
 template <typename R>
 void launch_lks_march(const Geo& g, int steps, const FwdArgs<R>& a, hipStream_t s) {
-  with_steps<sizeof(R)>(g, steps, [&](auto k, const MarchShape& ms, unsigned blocks) {
-    lks_march_kernel<R, decltype(k)::value><<<blocks, 256, 0, s>>>(g, a, ms);
+  with_steps<sizeof(R)>(steps, [&](auto k) {
+    const MarchShape ms = shape_for<sizeof(R)>(g, k.value);
+    lks_march_kernel<R, decltype(k)::value><<<blocks_of(ms.waves()), 256, 0, s>>>(g, a, ms);
   });
 }
 template <typename R>
 void launch_alks_march(const Geo& g, int steps, const AdjArgs<R>& a, hipStream_t s) {
-  with_steps<sizeof(R)>(g, steps, [&](auto k, const MarchShape& ms, unsigned blocks) {
-    alks_march_kernel<R, decltype(k)::value><<<blocks, 256, 0, s>>>(g, a, ms);
+  with_steps<sizeof(R)>(steps, [&](auto k) {
+    const MarchShape ms = shape_for<sizeof(R)>(g, k.value);
+    alks_march_kernel<R, decltype(k)::value><<<blocks_of(ms.waves()), 256, 0, s>>>(g, a, ms);
+  });
+}
+template <typename R>
+void launch_lks_march_batch(const BatchFwd<R>* d, const int* tmap, int total, const BatchPlan& p,
+                            int steps, int parity, hipStream_t s) {
+  with_steps<sizeof(R)>(steps, [&](auto k) {
+    lks_march_batch_kernel<R, decltype(k)::value>
+        <<<blocks_of(total), 256, 0, s>>>(d, tmap, total, p.kf, p.tile, parity);
+  });
+}
+template <typename R>
+void launch_alks_march_batch(const BatchAdj<R>* d, const int* tmap, int total, const BatchPlan& p,
+                             int steps, int parity, int last, hipStream_t s) {
+  with_steps<sizeof(R)>(steps, [&](auto k) {
+    alks_march_batch_kernel<R, decltype(k)::value>
+        <<<blocks_of(total), 256, 0, s>>>(d, tmap, total, p.ka, p.tile, parity, last);
   });
 }
 
-#define LKS_MARCH_INSTANTIATE(R)                                                      \
-  template void launch_lks_march<R>(const Geo&, int, const FwdArgs<R>&, hipStream_t); \
-  template void launch_alks_march<R>(const Geo&, int, const AdjArgs<R>&, hipStream_t);
+#define LKS_MARCH_INSTANTIATE(R)                                                              \
+  template void launch_lks_march<R>(const Geo&, int, const FwdArgs<R>&, hipStream_t);         \
+  template void launch_alks_march<R>(const Geo&, int, const AdjArgs<R>&, hipStream_t);        \
+  template void launch_lks_march_batch<R>(const BatchFwd<R>*, const int*, int,                \
+                                          const BatchPlan&, int, int, hipStream_t);           \
+  template void launch_alks_march_batch<R>(const BatchAdj<R>*, const int*, int,               \
+                                           const BatchPlan&, int, int, int, hipStream_t);
 LKS_MARCH_INSTANTIATE(float)
 LKS_MARCH_INSTANTIATE(double)
 

@@ -2000,7 +2000,10 @@ void batch_tiles(lks_batch* b) {
   b->nty.assign(size_t(b->n), 0);
   for (int d = 0; d < b->n; ++d) {
     const Geo& g = b->ctx[d]->geo;
-    if (b->multi.kf) {
+    if (b->multi.vf == lks::MARCH) {
+      b->ntx[d] = lks::march_waves(g, b->multi.kf, b->multi.tile);
+      b->nty[d] = 1;
+    } else if (b->multi.kf) {
       lks::multi_batch_tiles(g, b->multi.tile, &b->ntx[d], &b->nty[d]);
     } else {
       b->ntx[d] = g.ntx;
@@ -2011,11 +2014,16 @@ void batch_tiles(lks_batch* b) {
   }
 }
 
-// takes the several-steps plan where every design's tiles fit its blocks and
-// its accumulators
+// takes the marching plan of a large steady batch, else the several-steps plan
+// where every design's tiles fit its blocks and its accumulators
 void batch_multi(lks_batch* b) {
   std::vector<const Geo*> geos;
   for (const lks_ctx* c : b->ctx) geos.push_back(&c->geo);
+  if (!b->unsteady) b->multi = lks::march_batch_plan(geos.data(), b->n, b->rsz);
+  if (b->multi.kf) {
+    batch_tiles(b);
+    if (b->total_tiles <= b->max_tiles) return;  // (the table holds that many)
+  }
   b->multi = lks::multi_batch_plan(geos.data(), b->n, b->rsz, b->thermal);
   if (b->multi.kf) batch_tiles(b);
   for (int d = 0; d < b->n && b->multi.kf; ++d) {
@@ -2198,15 +2206,25 @@ void enqueue_batch_steps(lks_batch* b, int nf, int na, hipStream_t s) {
   auto* Aj = static_cast<const lks::BatchAdj<R>*>(b->d_adj);
   if (b->multi.kf) {
     const lks::BatchPlan& p = b->multi;
+    const bool march = p.vf == lks::MARCH;
     int i = 0;
-    for (int n = 0; n < nf; n += p.kf, ++i)
-      lks::launch_lks_multi_batch<R>(F, b->d_tmap, b->total_tiles, b->thermal, p.vf,
-                                     std::min(p.kf, nf - n), i & 1, s);
+    for (int n = 0; n < nf; n += p.kf, ++i) {
+      const int m = std::min(p.kf, nf - n);
+      if (march) lks::launch_lks_march_batch<R>(F, b->d_tmap, b->total_tiles, p, m, i & 1, s);
+      else
+        lks::launch_lks_multi_batch<R>(F, b->d_tmap, b->total_tiles, b->thermal, p.vf, m, i & 1, s);
+    }
     lks::launch_pressure_drop_batch<R>(F, b->n, i & 1, b->d_J, s);
     i = 0;
-    for (int n = 0; n < na; n += p.ka, ++i)
-      lks::launch_alks_multi_batch<R>(i ? Aj : Aj + 2 * b->n, b->d_tmap, b->total_tiles, b->thermal,
-                                      p.va, std::min(p.ka, na - n), i & 1, n + p.ka >= na, s);
+    for (int n = 0; n < na; n += p.ka, ++i) {
+      const lks::BatchAdj<R>* D = i ? Aj : Aj + 2 * b->n;
+      const int m = std::min(p.ka, na - n), last = n + p.ka >= na;
+      if (march)
+        lks::launch_alks_march_batch<R>(D, b->d_tmap, b->total_tiles, p, m, i & 1, last, s);
+      else
+        lks::launch_alks_multi_batch<R>(D, b->d_tmap, b->total_tiles, b->thermal, p.va, m, i & 1,
+                                        last, s);
+    }
     return;
   }
   for (int k = 0; k < nf; ++k)

@@ -125,12 +125,16 @@ def _batch(wls, prec, rows, n, m, **kw):
 
 
 # the first batch fits one round of the smallest tiles, the second takes the
-# tiles of several rounds
+# tiles of several rounds; MARCHED take the marching kernels (the first in FP32 only)
 BATCHES = [[(31, 31), (5, 4), (64, 40)], [(150, 131), (512, 300), (700, 513)]]
 
 
+MARCHED = [[(5, 4), (1100, 900), (64, 65), (65, 9), (700, 701)],
+           [(5, 4), (1400, 1100)], [(257, 1030), (1700, 1600), (130, 120), (4, 30)]]
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
-@pytest.mark.parametrize("sizes", BATCHES)
+@pytest.mark.parametrize("sizes", BATCHES + MARCHED)
 def test_steady_batch(sizes, prec):
     wls = [W.steady_channel_uniform(x, y, Re=20.0, seed=d, n_fwd=11, n_adj=10)
            for d, (x, y) in enumerate(sizes)]
