@@ -1077,6 +1077,23 @@ __host__ __device__ inline FaceTiles face_tiles(const Geo3& g, int ax) {
   return t;
 }
 
+// Where the scratch of the fused step holds the moments of an x-face node (end
+// flag ex, row j) of plane l, in its plane: in a row of the faces' own where the
+// march leaves the plane's interior free (it uses that of planes 1, 2, nz-3 and
+// nz-2). At the node's own place, a row away from the next one, each of the 14
+// values would dirty a line of its own: on 256 x 128 x 128 the face pass took 22.8
+// us and the march 123.6, packed 17.9 and 107.7. Not in FP64, whose march has no
+// registers left for the second address (97 x 61 x 53: face pass 11.9 -> 10.4 us,
+// march 41.2 -> 43.5).
+template <typename R>
+__device__ inline bool xface_packed(const Geo3& g, int l) {
+  return sizeof(R) == 4 && g.fused && g.nx >= 8 && g.ny >= 8 &&
+         ((g.periodic & 4) || (l >= 3 && l <= g.nz - 4));
+}
+__device__ inline int xface_row(const Geo3& g, int ex, int j) {
+  return g.nx + (ex > 0 ? g.ny : 0) + j;
+}
+
 // ALKS pass 1 at the boundary nodes: blocks of face tiles (two faces of each
 // non-periodic axis), then the host-built list of the edge and corner nodes that
 // copy the moments of an interior node (those that copy a face node's are written
@@ -1186,8 +1203,15 @@ __global__ __launch_bounds__(NT3) void alks3_face_kernel(Geo3 g, Adj3Args<R> a) 
   }
   face_fill<R, TH>(a, 2 * ax + face, m, un, Tn, f, gq, M);
   adj_local<R, TH>(a, m, 1, Tn, ip, M, u0);
+  // place of the x-face node (j, l)
+  auto at_x = [&](int j, int l) {
+    return xface_packed<R>(g, l) ? l * sq + xface_row(g, sg, j) : kn + j * sp + l * sq;
+  };
+  int k0 = k;
+  if constexpr (sizeof(R) == 4)
+    if (ax == 0) k0 = at_x(cp, cq);
 #pragma unroll
-  for (int c = 0; c < NM; ++c) a.m[c * N + k] = M[c];
+  for (int c = 0; c < NM; ++c) a.m[c * N + k0] = M[c];
   if (ax != 0) return;
   // the edges and corners of an x face copy the node one step inwards
   const int j[3] = {cp, cp == 1 && !perp ? 0 : -1, cp == Np - 2 && !perp ? Np - 1 : -1};
@@ -1196,7 +1220,7 @@ __global__ __launch_bounds__(NT3) void alks3_face_kernel(Geo3 g, Adj3Args<R> a) 
   for (int x = 0; x < 9; ++x) {
     const int jj = j[x % 3], ll = l[x / 3];
     if (x == 0 || jj < 0 || ll < 0) continue;
-    const int z = kn + jj * sp + ll * sq;
+    const int z = at_x(jj, ll);
 #pragma unroll
     for (int c = 0; c < NM; ++c) a.m[c * N + z] = M[c];
   }
@@ -1529,7 +1553,7 @@ __global__ __launch_bounds__(ZT) void alks3e_kernel(Geo3 g, Adj3Args<R> a) {
 // alks3e<ENDS> updates afterwards.
 // Bound by instructions. Reading the 19 values of a node from three planes of
 // LDS took 157 us on 256 x 128 x 128 in FP32 and 58 us on 97 x 61 x 53 in FP64;
-// this way it is 121 and 41 us, 523 MB passing below the L2 in the first (4.3
+// this way it is 121 and 41 us (108 with packed x-face moments), 523 MB passing below the L2 in the first (4.3
 // TB/s, a copy reaches 6.2).
 template <typename R>
 struct AdjFLds {
@@ -1565,6 +1589,15 @@ __global__ __launch_bounds__(ZT, sizeof(R) == 4 ? 3 : 1) void alks3f_kernel(Geo3
   const bool xy0 = n0.ex || n0.ey, xy1 = n1.ex || n1.ey;
   // offsets in a plane, and the positions from which the LDS reads count up
   unsigned off0 = n0.on ? unsigned(n0.off) : 0u, off1 = n1.on ? unsigned(n1.off) : 0u;
+  // ... those of an x-face column's moments (xface_packed)
+  auto packed = [&](const ZNode& n, unsigned off) {
+    return n.ex ? unsigned(xface_row(g, n.ex, int(off) / g.nx)) : off;
+  };
+  unsigned pk0 = 0, pk1 = 0;
+  if constexpr (sizeof(R) == 4) {
+    pk0 = packed(n0, off0);
+    pk1 = packed(n1, off1);
+  }
   unsigned i0 = unsigned(n0.lds - SX - 1), i1 = unsigned(n1.lds - SX - 1);
   unsigned e0 = unsigned(n0.ci), e1 = unsigned(n1.ci);
   auto has = [&](int q) { return pz || (q >= 0 && q < g.nz); };
@@ -1664,14 +1697,22 @@ __global__ __launch_bounds__(ZT, sizeof(R) == 4 ? 3 : 1) void alks3f_kernel(Geo3
     for (int i = 0; i < 14; ++i) M[i] = Mr[i] = R(0);
     if (close) {
       if (n1.on) c1 = col_in(in, b1, off1);
-      if (n0.on && bnd0)
+      if (n0.on && bnd0) {
+        unsigned om = ob0;
+        if constexpr (sizeof(R) == 4)
+          if (xface_packed<R>(g, s - 1)) om = pk0 * unsigned(sizeof(R));
 #pragma unroll
-        for (int i = 0; i < NM; ++i) M[i] = at_b(in->m + (size_t(i) * N + b1), ob0);
-      if (n1.on && bnd1)
+        for (int i = 0; i < NM; ++i) M[i] = at_b(in->m + (size_t(i) * N + b1), om);
+      }
+      if (n1.on && bnd1) {
+        unsigned om = off1;
+        if constexpr (sizeof(R) == 4)
+          if (xface_packed<R>(g, s - 1)) om = pk1;
 #pragma unroll
         for (int i = 4; i < NM; ++i)
           if (i < 9 || i == 11 || i == 12)
-            Mr[i] = at_b(in->m + (size_t(i) * N + b1), off1 * unsigned(sizeof(R)));
+            Mr[i] = at_b(in->m + (size_t(i) * N + b1), om * unsigned(sizeof(R)));
+      }
     }
     load(in, bn);
     if (n0.on) {

@@ -31,6 +31,7 @@ SIZES = {
     "box_66x5x4": lambda: _box(66, 5, 4),
     "duct_65x9x5": lambda: base._duct(65, 9, 5),
     "duct_12x6x41": lambda: base._duct(12, 6, 41),
+    "duct_8x8x7": lambda: base._duct(8, 8, 7),  # one plane of packed x-face moments
 }
 
 
