@@ -270,17 +270,19 @@ lks_status lks_write_field(lks_ctx *ctx, int which, const double *dev_in);
 /* Small and medium D2Q9 grids: until a launch shape is set explicitly
  * (lks_set_tile_rows, lks_set_steps_per_launch), sweeps take kernels that run
  * several steps per launch on about one tile per compute unit, with a shape
- * chosen from the grid's size and precision. They give the bits of the tiled
- * kernels; an unsteady objective sums the same terms in another order.
+ * chosen from the grid's size and precision; steady sweeps of large grids
+ * without temperature take kernels whose waves march along y, two or three
+ * steps per launch. Both give the bits of the tiled kernels; an unsteady
+ * objective sums the same terms in another order.
  *
  * Tile autotuner: times `steps` forward and `steps` adjoint steps of the
  * design gamma_dev for each launch shape the kernels provide (tiles of
  * 64 x 4, 64 x 8 and, where supported, 64 x 16 nodes; one or, where
- * supported, two steps per launch; the several-steps kernels above)
+ * supported, two steps per launch; the several-steps or marching kernels above)
  * on this context's stream, keeps the fastest and reports its tile height in
  * *tile_rows (lks_launch_shape gives the whole shape; each sweep direction
- * that is faster with the several-steps kernels keeps them). Synchronises; the forward and adjoint states are discarded
- * (run lks_forward afterwards). D2Q9 only (LKS_E_UNSUPPORTED for D3Q19,
+ * that is faster with those kernels keeps them). Synchronises; the forward and
+ * adjoint states are discarded (run lks_forward afterwards). D2Q9 only (LKS_E_UNSUPPORTED for D3Q19,
  * whose node-parallel kernels have no tile shape). */
 lks_status lks_autotune(lks_ctx *ctx, const double *gamma_dev, int steps, int *tile_rows);
 
