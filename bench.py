@@ -220,9 +220,10 @@ def headline(args, dev, shapes):
             c.autotune(g, 200)
         ctxs[prec] = c
     cm = lks.LKS(wl, precision="mixed", device=dev)
-    # the FP64 forward's tile height, the FP32 adjoint's steps per launch
-    apply_shape(cm, fixed.get("mixed", (ctxs["fp64"].launch_shape()[0], 1,
-                                        ctxs["fp32"].launch_shape()[2])))
+    if "mixed" in fixed:
+        apply_shape(cm, fixed["mixed"])
+    else:
+        cm.autotune(g, 200)
     ctxs["mixed"] = cm
 
     def gradient(ctx, out):
