@@ -268,7 +268,8 @@ lks_status lks_read_field(lks_ctx *ctx, int which, double *dev_out);
 lks_status lks_write_field(lks_ctx *ctx, int which, const double *dev_in);
 
 /* Small and medium D2Q9 grids: until a launch shape is set explicitly
- * (lks_set_tile_rows, lks_set_steps_per_launch), sweeps take kernels that run
+ * (lks_set_tile_rows, lks_set_steps_per_launch; lks_set_launch_plan turns them
+ * on again), sweeps take kernels that run
  * several steps per launch on about one tile per compute unit, with a shape
  * chosen from the grid's size and precision; steady sweeps of large grids
  * without temperature take kernels whose waves march along y, two or three
@@ -333,9 +334,31 @@ lks_status lks_set_adjoint_mode(lks_ctx *ctx, int mode);
 lks_status lks_set_fused_adjoint(lks_ctx *ctx, int fused);
 
 /* The launch shape of the tiled kernels: tile height (0 for D3Q19) and steps
- * per launch of the forward and adjoint sweeps. */
+ * per launch of the forward and adjoint sweeps. A sweep whose kernel
+ * (lks_launch_plan) is not LKS_KERNEL_TILE does not use it. */
 lks_status lks_launch_shape(const lks_ctx *ctx, int *tile_rows, int *forward_steps,
                             int *adjoint_steps);
+
+/* Kernels of a D2Q9 sweep */
+#define LKS_KERNEL_TILE 0  /* tiles of the launch shape (and the D3Q19 kernels) */
+#define LKS_KERNEL_MULTI 1 /* several steps per launch, about one tile per compute unit */
+#define LKS_KERNEL_MARCH 2 /* waves that march along y */
+
+/* The kernels the forward and adjoint sweeps take now (LKS_KERNEL_*) and the
+ * most steps one launch of them runs (a sweep's last launch may run fewer). A
+ * MIXED context reports its FP64 forward and FP32 adjoint. Any pointer may be
+ * NULL. Makes no HIP call. */
+lks_status lks_launch_plan(const lks_ctx *ctx, int *forward_kernel, int *forward_steps,
+                           int *adjoint_kernel, int *adjoint_steps);
+
+/* Choose each sweep's kernel: LKS_KERNEL_TILE, or the kernel a new context of
+ * this grid takes by default. With lks_set_tile_rows and
+ * lks_set_steps_per_launch before it, it gives a context the launch shape that
+ * lks_launch_shape and lks_launch_plan reported of another one of the same
+ * problem. Keeps the forward and adjoint states. Errors: LKS_E_INVALID for
+ * another value, LKS_E_UNSUPPORTED where the grid has no such kernel (nothing
+ * is changed). */
+lks_status lks_set_launch_plan(lks_ctx *ctx, int forward_kernel, int adjoint_kernel);
 
 /* Memory plan: bytes of checkpoint + replay storage, bytes of the rest of
  * the workspace, and the checkpoint interval K (N when the whole trajectory
@@ -431,6 +454,13 @@ lks_status lks_batch_autotune(lks_batch *b, const double *const *gamma_dev, int 
 /* Tile height of a batch's step launches (as lks_set_tile_rows; 4 or 8 for
  * unsteady batches). */
 lks_status lks_batch_set_tile_rows(lks_batch *b, int tile_rows);
+/* The kernel of a batch's step launches (LKS_KERNEL_*) and the most steps a
+ * launch runs, forward and adjoint (as lks_launch_plan). */
+lks_status lks_batch_launch_plan(const lks_batch *b, int *kernel, int *forward_steps,
+                                 int *adjoint_steps);
+/* Choose it (as lks_set_launch_plan); the results of the last run are
+ * discarded. */
+lks_status lks_batch_set_launch_plan(lks_batch *b, int kernel);
 /* Field `which` of design d at its final forward / adjoint level (unsteady
  * batches: adjoint fields only, those of level 0; LKS_E_UNSUPPORTED for
  * forward fields, whose last levels the replays overwrite). */

@@ -77,9 +77,9 @@ struct lks_ctx {
   int dim = 2;         // 2: D2Q9, 3: D3Q19
   int spl_f = 1;       // steady sweeps: time steps per launch (1 or 2),
   int spl_a = 1;       // forward and adjoint
-  // several steps per launch on small D2Q9 grids, until a launch shape is set
-  // explicitly (k = 0: the tile kernels run the sweep)
-  lks::MultiPlan mf, ma;
+  // several steps per launch on D2Q9 grids, until a launch shape is set
+  // explicitly (k = 0: the tile kernels run the sweep), and the grid's own plans
+  lks::MultiPlan mf, ma, grid_mf, grid_ma;
   int N = 0;           // nodes
   Geo geo{};           // D2Q9 geometry
   lks::Geo3 geo3{};    // D3Q19 geometry
@@ -1307,6 +1307,8 @@ lks_status lks_create(const lks_grid* grid, const lks_phys* phys, const lks_bc* 
     c->ma = lks::multi_plan(g, c->rsz, true, 1 << 20);
     const lks::MultiPlan march = lks::march_plan(g, c->rsz);
     if (c->mode != LKS_UNSTEADY && march.k) c->mf = c->ma = march;
+    c->grid_mf = c->mf;
+    c->grid_ma = c->ma;
   }
   st = plan_memory(c);
   if (st != LKS_OK) {
@@ -1794,6 +1796,59 @@ lks_status lks_launch_shape(const lks_ctx* c, int* tile_rows, int* forward_steps
   return LKS_OK;
 }
 
+}  // extern "C"
+
+namespace {
+// LKS_KERNEL_* of a plan in use
+int kernel_of(const lks::MultiPlan& p) {
+  return p.k == 0 ? LKS_KERNEL_TILE : (p.variant == lks::MARCH ? LKS_KERNEL_MARCH : LKS_KERNEL_MULTI);
+}
+// kernel and steps per launch of a context's sweep
+void sweep_plan(const lks_ctx* c, bool adjoint, int* kernel, int* steps) {
+  const bool unsteady = c->mode == LKS_UNSTEADY;
+  const bool binomial = unsteady && c->plan.scheme == LKS_CKPT_BINOMIAL;
+  // (a binomial reversal takes its adjoint steps one by one)
+  const lks::MultiPlan p = !adjoint ? c->mf : (binomial ? lks::MultiPlan() : c->ma);
+  if (kernel) *kernel = kernel_of(p);
+  if (!steps) return;
+  const bool two = c->dim == 2 && c->geo.ty != 16 && !binomial &&
+                   (adjoint ? c->rsz == 4 && !unsteady : c->rsz == 4 || !c->phys.thermal);
+  *steps = p.k ? p.k : (two ? (adjoint ? c->spl_a : c->spl_f) : 1);
+}
+// sets `use` to the plan that `kernel` names; false where the grid has none
+bool choose_plan(int kernel, const lks::MultiPlan& grid, lks::MultiPlan* use) {
+  if (kernel == LKS_KERNEL_TILE) *use = lks::MultiPlan();
+  else if (kernel == kernel_of(grid)) *use = grid;
+  else return false;
+  return true;
+}
+}  // namespace
+
+extern "C" {
+
+lks_status lks_launch_plan(const lks_ctx* c, int* forward_kernel, int* forward_steps,
+                           int* adjoint_kernel, int* adjoint_steps) {
+  if (!c) return LKS_E_INVALID;
+  sweep_plan(c, false, forward_kernel, forward_steps);
+  sweep_plan(c->lo ? c->lo : c, true, adjoint_kernel, adjoint_steps);
+  return LKS_OK;
+}
+
+lks_status lks_set_launch_plan(lks_ctx* c, int forward_kernel, int adjoint_kernel) {
+  if (!c) return LKS_E_INVALID;
+  for (int k : {forward_kernel, adjoint_kernel})
+    if (k < LKS_KERNEL_TILE || k > LKS_KERNEL_MARCH)
+      return fail(c, LKS_E_INVALID, "kernel must be LKS_KERNEL_TILE, _MULTI or _MARCH");
+  lks_ctx* ca = c->lo ? c->lo : c;  // mixed: the FP32 part runs the adjoint
+  lks::MultiPlan mf, ma;
+  if (!choose_plan(forward_kernel, c->grid_mf, &mf) ||
+      !choose_plan(adjoint_kernel, ca->grid_ma, &ma))
+    return fail(c, LKS_E_UNSUPPORTED, "not a kernel of this grid");
+  c->mf = mf;
+  ca->ma = ma;
+  return LKS_OK;
+}
+
 lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* tile_rows) {
   if (!c || !gamma_dev || steps < 1) return LKS_E_INVALID;
   if (c->lo) {
@@ -1942,7 +1997,7 @@ struct lks_batch {
   int total_tiles = 0;
   // several steps per launch, until a tile height is set (kf = 0: the tile
   // kernels), and the designs' tile counts then
-  lks::BatchPlan multi;
+  lks::BatchPlan multi, own_multi;  // the plan in use, and the batch's own
   std::vector<int> ntx, nty;
   int max_tiles = 0;        // tiles of all designs at the shortest tile height
   std::vector<int> tmap;    // (design, tile within the design) of every global tile
@@ -2035,6 +2090,11 @@ void batch_multi(lks_batch* b) {
       b->multi = lks::BatchPlan();
   }
   batch_tiles(b);
+}
+
+// LKS_KERNEL_* of a batch's plan
+int batch_kernel(const lks::BatchPlan& p) {
+  return p.kf == 0 ? LKS_KERNEL_TILE : (p.vf == lks::MARCH ? LKS_KERNEL_MARCH : LKS_KERNEL_MULTI);
 }
 
 // workspace slices of the designs, then the batch's own tables
@@ -2372,6 +2432,7 @@ lks_status lks_batch_create(int n, const lks_grid* grids, const lks_phys* phys, 
   b->rsz = b->ctx[0]->rsz;
   b->thermal = phys[0].thermal ? 1 : 0;
   batch_multi(b);
+  b->own_multi = b->multi;
   if (b->unsteady) {
     // tile heights of the unsteady step launches: 4 and 8
     if (b->ty == 16) batch_set_tile_rows(b, 8, b->multi);
@@ -2672,6 +2733,28 @@ lks_status lks_batch_set_tile_rows(lks_batch* b, int tile_rows) {
     return bfail(b, LKS_E_INVALID,
                  "tile height must be 4 or 8 (or 16 for FP32 non-thermal steady batches)");
   lks_status st = batch_set_tile_rows(b, tile_rows, lks::BatchPlan());
+  if (st == LKS_OK) b->have_run = false;
+  return st;
+}
+
+lks_status lks_batch_launch_plan(const lks_batch* b, int* kernel, int* forward_steps,
+                                 int* adjoint_steps) {
+  if (!b) return LKS_E_INVALID;
+  const lks::BatchPlan& p = b->multi;
+  if (kernel) *kernel = batch_kernel(p);
+  if (forward_steps) *forward_steps = std::max(1, p.kf);
+  if (adjoint_steps) *adjoint_steps = std::max(1, p.ka);
+  return LKS_OK;
+}
+
+lks_status lks_batch_set_launch_plan(lks_batch* b, int kernel) {
+  if (!b) return LKS_E_INVALID;
+  if (kernel < LKS_KERNEL_TILE || kernel > LKS_KERNEL_MARCH)
+    return bfail(b, LKS_E_INVALID, "kernel must be LKS_KERNEL_TILE, _MULTI or _MARCH");
+  if (kernel != LKS_KERNEL_TILE && kernel != batch_kernel(b->own_multi))
+    return bfail(b, LKS_E_UNSUPPORTED, "not a kernel of this batch");
+  lks_status st =
+      batch_set_tile_rows(b, b->ty, kernel == LKS_KERNEL_TILE ? lks::BatchPlan() : b->own_multi);
   if (st == LKS_OK) b->have_run = false;
   return st;
 }

@@ -47,6 +47,8 @@ LKS_STEADY, LKS_UNSTEADY = 0, 1
 LKS_ADJ_PAPER, LKS_ADJ_EXACT = 0, 1
 LKS_CKPT_AUTO, LKS_CKPT_TWO_LEVEL, LKS_CKPT_BINOMIAL = 0, 1, 2
 _CKPT = {"auto": LKS_CKPT_AUTO, "two_level": LKS_CKPT_TWO_LEVEL, "binomial": LKS_CKPT_BINOMIAL}
+LKS_KERNEL_TILE, LKS_KERNEL_MULTI, LKS_KERNEL_MARCH = 0, 1, 2
+KERNELS = ("tile", "multi", "march")  # names of LKS_KERNEL_*
 FIELDS = {"drho": 0, "ux": 1, "uy": 2, "T": 3,
           "adj_rho": 4, "adj_vx": 5, "adj_vy": 6, "adj_theta": 7,
           "uz": 8, "adj_vz": 9}
@@ -62,7 +64,8 @@ EXPORTED = ("lks_create", "lks_workspace_size", "lks_bind_workspace", "lks_forwa
             "lks_set_checkpointing", "lks_checkpoint_info", "lks_gradient_status",
             "lks_bind_static_workspace", "lks_batch_set_memory_budget",
             "lks_batch_set_adjoint_mode", "lks_batch_checkpoint_info",
-            "lks_set_fused_adjoint")
+            "lks_set_fused_adjoint", "lks_launch_plan", "lks_set_launch_plan",
+            "lks_batch_launch_plan", "lks_batch_set_launch_plan")
 
 # LKS_STATIC_WORKSPACE_BYTES of lks.h
 STATIC_WORKSPACE_BYTES = 64 * 1024 * 1024
@@ -153,6 +156,14 @@ _lib.lks_set_steps_per_launch.argtypes = [_vp, ctypes.c_int, ctypes.c_int]
 _lib.lks_set_steps_per_launch.restype = _st
 _lib.lks_launch_shape.argtypes = [_vp] + [ctypes.POINTER(ctypes.c_int)] * 3
 _lib.lks_launch_shape.restype = _st
+_lib.lks_launch_plan.argtypes = [_vp] + [ctypes.POINTER(ctypes.c_int)] * 4
+_lib.lks_launch_plan.restype = _st
+_lib.lks_set_launch_plan.argtypes = [_vp, ctypes.c_int, ctypes.c_int]
+_lib.lks_set_launch_plan.restype = _st
+_lib.lks_batch_launch_plan.argtypes = [_vp] + [ctypes.POINTER(ctypes.c_int)] * 3
+_lib.lks_batch_launch_plan.restype = _st
+_lib.lks_batch_set_launch_plan.argtypes = [_vp, ctypes.c_int]
+_lib.lks_batch_set_launch_plan.restype = _st
 _lib.lks_set_adjoint_mode.argtypes = [_vp, ctypes.c_int]
 _lib.lks_set_adjoint_mode.restype = _st
 _lib.lks_set_fused_adjoint.argtypes = [_vp, ctypes.c_int]
@@ -308,16 +319,22 @@ class LKS:
         _check(_lib.lks_write_field(self.ctx, FIELDS[name], _vp(t.data_ptr())), self.ctx)
 
     def autotune(self, gamma, steps=200):
-        """Pick the fastest tile height; returns it."""
+        """Pick the fastest launch shape and kernels (launch_shape, launch_plan)
+        by timing them; returns the tile height of the shape."""
         ty = ctypes.c_int()
         _check(_lib.lks_autotune(self.ctx, _vp(gamma.data_ptr()), int(steps), ctypes.byref(ty)),
                self.ctx)
         return ty.value
 
     def set_tile_rows(self, ty):
+        """Tile height of the tile kernels; both sweeps take these from here on
+        (set_launch_plan turns the others on again)."""
         _check(_lib.lks_set_tile_rows(self.ctx, int(ty)), self.ctx)
 
     def set_steps_per_launch(self, forward, adjoint=None):
+        """Steps per launch (1 or 2) of the tile kernels; both sweeps take these
+        from here on, whatever ran before (set_launch_plan turns the others on
+        again)."""
         adjoint = forward if adjoint is None else adjoint
         _check(_lib.lks_set_steps_per_launch(self.ctx, int(forward), int(adjoint)), self.ctx)
 
@@ -357,11 +374,27 @@ class LKS:
         return {"scheme": name, "count": n.value, "replay_steps": r.value}
 
     def launch_shape(self):
-        """(tile rows, forward steps per launch, adjoint steps per launch)."""
+        """(tile rows, forward steps per launch, adjoint steps per launch) of the
+        tile kernels; launch_plan says which kernels run."""
         ty, sf, sa = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
         _check(_lib.lks_launch_shape(self.ctx, ctypes.byref(ty), ctypes.byref(sf),
                                      ctypes.byref(sa)), self.ctx)
         return ty.value, sf.value, sa.value
+
+    def launch_plan(self):
+        """((kernel, steps), (kernel, steps)) of the forward and the adjoint
+        sweep: the kernels that run, "tile", "multi" (several steps per launch)
+        or "march", and the most steps of one launch."""
+        v = [ctypes.c_int() for _ in range(4)]
+        _check(_lib.lks_launch_plan(self.ctx, *[ctypes.byref(x) for x in v]), self.ctx)
+        kf, sf, ka, sa = [x.value for x in v]
+        return (KERNELS[kf], sf), (KERNELS[ka], sa)
+
+    def set_launch_plan(self, forward, adjoint):
+        """Choose the kernel of each sweep: "tile", or the one a new context of
+        this problem takes (see lks_set_launch_plan)."""
+        _check(_lib.lks_set_launch_plan(self.ctx, KERNELS.index(forward), KERNELS.index(adjoint)),
+               self.ctx)
 
     def memory_report(self):
         a, b, k = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_int()
@@ -389,8 +422,9 @@ def _bcheck(status, b=None):
 
 
 class Batch:
-    """Many independent designs advanced together: one kernel launch per step
-    for all designs, the step sequence replayed as a HIP graph. Steady
+    """Many independent designs advanced together: one kernel launch for one or
+    several steps of all designs (launch_plan), the step sequence replayed as a
+    HIP graph. Steady
     pressure-drop designs, or unsteady designs sharing one horizon, whose
     sweeps are checkpointed with one interval chosen for mem_budget bytes
     (0: every level kept)."""
@@ -463,7 +497,20 @@ class Batch:
         return ty.value
 
     def set_tile_rows(self, ty):
+        """Tile height of the tile kernels, which run the batch from here on
+        (set_launch_plan turns the others on again)."""
         _bcheck(_lib.lks_batch_set_tile_rows(self.b, int(ty)), self.b)
+
+    def launch_plan(self):
+        """(kernel, forward steps per launch, adjoint steps per launch): the
+        kernels that run the batch, named as in LKS.launch_plan."""
+        v = [ctypes.c_int() for _ in range(3)]
+        _bcheck(_lib.lks_batch_launch_plan(self.b, *[ctypes.byref(x) for x in v]), self.b)
+        return (KERNELS[v[0].value], v[1].value, v[2].value)
+
+    def set_launch_plan(self, kernel):
+        """"tile", or the kernel a new batch of these designs takes."""
+        _bcheck(_lib.lks_batch_set_launch_plan(self.b, KERNELS.index(kernel)), self.b)
 
     def read(self, design, name, out=None):
         import torch

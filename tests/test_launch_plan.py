@@ -1,0 +1,78 @@
+"""Which kernels a context or batch takes can be read, and a launch shape can be
+carried over to another context (planning only, no GPU)."""
+import pytest
+
+from paper_2411_03090_amd import lks, workloads as W
+
+
+def _ctx(nx, ny, precision="fp32"):
+    return lks.LKS(W.steady_channel_uniform(nx, ny, n_fwd=4, n_adj=4), precision=precision,
+                   bind=False)
+
+
+def _copy_shape(src, dst):
+    """What a program that keeps launch shapes does with them."""
+    ty, sf, sa = src.launch_shape()
+    (kf, _), (ka, _) = src.launch_plan()
+    dst.set_tile_rows(ty)
+    dst.set_steps_per_launch(sf, sa)
+    dst.set_launch_plan(kf, ka)
+
+
+@pytest.mark.parametrize("nx,ny,precision,kernel", [
+    (64, 64, "fp64", "multi"), (512, 512, "fp32", "multi"), (512, 512, "mixed", "multi"),
+    (2048, 2048, "fp32", "march"), (2048, 2048, "fp64", "march"), (1024, 1024, "fp32", "tile")])
+def test_plan_is_reported_and_restored(nx, ny, precision, kernel):
+    a = _ctx(nx, ny, precision)
+    (kf, sf), (ka, sa) = plan = a.launch_plan()
+    assert kf == ka == kernel
+    assert (sf > 1 and sa > 1) if kernel != "tile" else (sf, sa) == (1, 1)
+    b = _ctx(nx, ny, precision)
+    b.set_tile_rows(4)
+    assert b.launch_plan() == (("tile", 1), ("tile", 1))
+    b.set_steps_per_launch(2, 1)
+    assert b.launch_plan() == (("tile", 2), ("tile", 1))
+    _copy_shape(a, b)
+    assert b.launch_plan() == plan and b.launch_shape() == a.launch_shape()
+    b.set_launch_plan("tile", ka)
+    assert b.launch_plan() == (("tile", 1), (ka, sa))
+
+
+def test_refused_plans_change_nothing():
+    a = _ctx(64, 64)
+    plan = a.launch_plan()
+    for fwd, adj in (("march", "multi"), ("multi", "march")):
+        with pytest.raises(lks.LKSError) as e:
+            a.set_launch_plan(fwd, adj)
+        assert e.value.status == lks.LKS_E_UNSUPPORTED
+    with pytest.raises(lks.LKSError) as e:
+        lks._check(lks._lib.lks_set_launch_plan(a.ctx, 0, 3), a.ctx)
+    assert e.value.status == lks.LKS_E_INVALID
+    assert a.launch_plan() == plan
+    d = lks.LKS(W.heated_block_duct(16, 8, 8, Re=20.0, n_steps=10), precision="fp32", bind=False)
+    assert d.launch_plan() == (("tile", 1), ("tile", 1))
+    with pytest.raises(lks.LKSError):
+        d.set_launch_plan("multi", "tile")
+
+
+def test_unsteady_plans():
+    wl = W.unsteady_thermal_channel(64, 48, n_steps=50)
+    c = lks.LKS(wl, precision="fp32", bind=False)
+    (kf, sf), (ka, sa) = c.launch_plan()
+    assert (kf, ka) == ("multi", "multi") and sf > 1 and sa > 1
+    c.set_checkpointing("binomial", 4)  # whose reversal takes its adjoint steps one by one
+    assert c.launch_plan() == ((kf, sf), ("tile", 1))
+
+
+def test_batch_plan_is_reported_and_restored():
+    wls = [W.steady_channel_uniform(512, 400, seed=d, n_fwd=4, n_adj=4) for d in range(16)]
+    b = lks.Batch(wls, precision="fp32", bind=False)
+    plan = b.launch_plan()
+    assert plan == ("march", 2, 2)
+    b.set_tile_rows(8)
+    assert b.launch_plan() == ("tile", 1, 1)
+    with pytest.raises(lks.LKSError) as e:
+        b.set_launch_plan("multi")
+    assert e.value.status == lks.LKS_E_UNSUPPORTED and b.launch_plan() == ("tile", 1, 1)
+    b.set_launch_plan("march")
+    assert b.launch_plan() == plan
