@@ -1871,7 +1871,8 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
   // per tile height, the forward and adjoint sweeps with one and (where
   // supported) two steps per launch, timed separately
   float best = 0.0f, best_tf = 0.0f, best_ta = 0.0f;
-  int best_ty = c->geo.ty, best_f = c->spl_f, best_a = c->spl_a;
+  const int ty0 = c->geo.ty, spl_f0 = c->spl_f, spl_a0 = c->spl_a;
+  int best_ty = ty0, best_f = spl_f0, best_a = spl_a0;
   const int mode = c->mode;
   // two steps per launch exist for FP32 sweeps and the FP64 non-thermal
   // forward; an unsteady adjoint sweep runs one step per launch
@@ -1898,9 +1899,12 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
       hipEventElapsedTime(ta, e[1], e[2]);
     }
   };
-  // the several-steps kernels of the grid's size, if any
-  const lks::MultiPlan mf = c->mf, ma = c->ma;
+  // the several-steps kernels of the grid's size, if any, whether or not they
+  // are in use
+  const lks::MultiPlan mf = c->grid_mf, ma = c->grid_ma, use_f = c->mf, use_a = c->ma;
   float tmf = 0.0f, tma = 0.0f;
+  c->mf = mf;
+  c->ma = ma;
   if (mf.k || ma.k) time_sweeps(&tmf, &tma);
   c->mf = c->ma = lks::MultiPlan();
   for (int ty : TILE_ROWS) {
@@ -1935,9 +1939,17 @@ lks_status lks_autotune(lks_ctx* c, const double* gamma_dev, int steps, int* til
   c->have_forward = false;
   c->have_adjoint = false;
   c->last_level = 0;
+  if (st == LKS_OK) st = check_launch(c);
+  if (st != LKS_OK) {  // the launch shape of before
+    set_tile_rows(c->geo, ty0);
+    c->spl_f = spl_f0;
+    c->spl_a = spl_a0;
+    c->mf = use_f;
+    c->ma = use_a;
+    return st;
+  }
   if (tile_rows) *tile_rows = best_ty;
-  if (st != LKS_OK) return st;
-  return check_launch(c);
+  return LKS_OK;
 }
 
 lks_status lks_memory_report(const lks_ctx* c, size_t* ckpt_bytes, size_t* state_bytes, int* K) {
@@ -2693,8 +2705,10 @@ lks_status lks_batch_autotune(lks_batch* b, const double* const* gamma_dev, int 
   if (!hip_ok(nullptr, hipEventCreate(&e0), "event", &st) ||
       !hip_ok(nullptr, hipEventCreate(&e1), "event", &st))
     return bfail(b, st, g_create_error);
-  // the several-steps plan first (where it is in use), then each tile height
-  const lks::BatchPlan plan = b->multi;
+  // the batch's several-steps plan first, whether or not it is in use, then each
+  // tile height
+  const lks::BatchPlan plan = b->own_multi, use = b->multi;
+  const int ty0 = b->ty;
   lks::BatchPlan best_plan;
   auto time_shape = [&](int ty, const lks::BatchPlan& p) {
     if ((st = batch_set_tile_rows(b, ty, p)) != LKS_OK) return;
@@ -2718,7 +2732,10 @@ lks_status lks_batch_autotune(lks_batch* b, const double* const* gamma_dev, int 
     if (st == LKS_OK && tile_rows_ok(ty, b->rsz, b->thermal)) time_shape(ty, lks::BatchPlan());
   hipEventDestroy(e0);
   hipEventDestroy(e1);
-  if (st != LKS_OK) return st;
+  if (st != LKS_OK) {
+    batch_set_tile_rows(b, ty0, use);  // the launch shape of before
+    return st;
+  }
   if ((st = batch_set_tile_rows(b, best_ty, best_plan)) != LKS_OK) return st;
   if (tile_rows) *tile_rows = best_ty;
   b->have_run = false;
