@@ -1694,13 +1694,11 @@ lks_status lks_write_field(lks_ctx* c, int which, const double* dev_in) {
 
 lks_status lks_set_tile_rows(lks_ctx* c, int tile_rows) {
   if (!c) return LKS_E_INVALID;
-  if (c->lo) {
-    lks_status st = lks_set_tile_rows(c->lo, tile_rows);
-    if (st != LKS_OK) return fail(c, st, c->lo->err);
-  }
   if (c->dim == 3) return fail(c, LKS_E_UNSUPPORTED, "D3Q19 kernels are not tiled");
   for (int ty : TILE_ROWS)
     if (ty == tile_rows && tile_rows_ok(ty, c->rsz, c->phys.thermal)) {
+      // (mixed: a height of the FP64 part is one of the FP32 part too)
+      if (c->lo) lks_set_tile_rows(c->lo, tile_rows);
       set_tile_rows(c->geo, ty);
       c->mf = c->ma = lks::MultiPlan();
       c->have_forward = false;
@@ -1712,24 +1710,19 @@ lks_status lks_set_tile_rows(lks_ctx* c, int tile_rows) {
 
 lks_status lks_set_steps_per_launch(lks_ctx* c, int forward_steps, int adjoint_steps) {
   if (!c) return LKS_E_INVALID;
-  if (c->lo) {
-    // mixed: the forward runs in FP64, the adjoint in FP32
-    lks_status st = lks_set_steps_per_launch(c->lo, 1, adjoint_steps);
-    if (st != LKS_OK) return fail(c, st, c->lo->err);
-    lks_ctx* lo = c->lo;
-    c->lo = nullptr;
-    st = lks_set_steps_per_launch(c, forward_steps, 1);
-    c->lo = lo;
-    return st;
-  }
   for (int s : {forward_steps, adjoint_steps}) {
     if (s != 1 && s != 2) return fail(c, LKS_E_INVALID, "steps per launch must be 1 or 2");
     if (s == 2 && c->dim != 2)
       return fail(c, LKS_E_UNSUPPORTED, "two steps per launch need a D2Q9 problem");
   }
-  if (c->rsz == 8 && ((forward_steps == 2 && c->phys.thermal) || adjoint_steps == 2))
+  // mixed: the forward runs in FP64, the adjoint in FP32
+  if (c->rsz == 8 && ((forward_steps == 2 && c->phys.thermal) || (adjoint_steps == 2 && !c->lo)))
     return fail(c, LKS_E_UNSUPPORTED,
                 "FP64 sweeps run two steps per launch for the non-thermal forward only");
+  if (c->lo) {
+    lks_set_steps_per_launch(c->lo, 1, adjoint_steps);
+    adjoint_steps = 1;
+  }
   c->spl_f = forward_steps;
   c->spl_a = adjoint_steps;
   c->mf = c->ma = lks::MultiPlan();

@@ -76,3 +76,21 @@ def test_batch_plan_is_reported_and_restored():
     assert e.value.status == lks.LKS_E_UNSUPPORTED and b.launch_plan() == ("tile", 1, 1)
     b.set_launch_plan("march")
     assert b.launch_plan() == plan
+
+
+def test_refused_shapes_change_nothing_in_a_mixed_context():
+    """The FP32 part takes 16 rows, the FP64 part does not; FP64 thermal sweeps
+    run one step per launch, FP32 ones two."""
+    a = _ctx(512, 512, "mixed")
+    plan = a.launch_plan()
+    with pytest.raises(lks.LKSError):
+        a.set_tile_rows(16)
+    assert a.launch_plan() == plan
+    b = lks.LKS(W.heat_exchanger(n=64, n_fwd=4, n_adj=4), precision="mixed", bind=False)
+    plan = b.launch_plan()
+    for steps in ((2, 2), (1, 3), (3, 1)):
+        with pytest.raises(lks.LKSError):
+            b.set_steps_per_launch(*steps)
+        assert b.launch_plan() == plan
+    b.set_steps_per_launch(1, 2)
+    assert b.launch_plan() == (("tile", 1), ("tile", 2))
