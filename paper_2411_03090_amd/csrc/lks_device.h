@@ -8,6 +8,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <functional>
+
 namespace lks {
 
 // Tile of the 2D kernels: 64 nodes along x (one wavefront) by TY rows, 256
@@ -455,7 +457,8 @@ void launch_lks_march_batch(const BatchFwd<R>* d, const int* tmap, int total, co
 template <typename R>
 void launch_alks_march_batch(const BatchAdj<R>* d, const int* tmap, int total, const BatchPlan& p,
                              int steps, int parity, int last, hipStream_t s);
-BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool thermal);
+BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool thermal,
+                           const std::function<bool(const BatchPlan&)>& holds);
 void multi_batch_tiles(const Geo& g, int tile, int* ntx, int* nty);
 bool multi_fits(const Geo& g, int ntx, int nty, int rsz, bool adjoint, int variant, int steps);
 // steady batches: `steps` steps of every design (descriptors as for the tile

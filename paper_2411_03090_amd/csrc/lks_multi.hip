@@ -812,13 +812,18 @@ void multi_batch_tiles(const Geo& g, int tile, int* ntx, int* nty) {
 // Batches. While the tiles of all designs fit one round of blocks, the
 // smallest tiles that do, with the steps their region holds (8 designs of 64 to
 // 256 nodes a side, FP32: 28 x 28 tiles, 4 steps, 2.9 us per step of all; 36 x
-// 36, 2 steps, 4.2; the tile kernels 6.4). Over several rounds larger tiles with
+// 36, 2 steps, 4.2; the tile kernels 6.4. 4 designs of 64 x 64: 8 x 8 tiles, 6
+// steps, 2.2 us against 5.4 of the 64 x 4 tile kernels, FP64 2.4 and 5.7, thermal 3.6
+// and 7.9, FP64 4.6 and 8.6). Over several rounds larger tiles with
 // fewer steps: 32 designs of 128 to 512, 3.26M nodes, FP32 36 x 36 and 2 steps
 // 37.3 forward and 38.4 us adjoint against 41.0 and 39.6 of the 64 x 8 tile
 // kernels, FP64 30 x 30 and 3 steps 46.9, 48.4 against 65.9, 79.3; 16 thermal
 // ones, 1.46M nodes, FP32 33.9, 38.0 against 39.5, 41.6, FP64 24 x 24 and 2 steps
 // 61.9, 71.5 against 82.8, 92.5.
-BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th) {
+// The first candidate that `holds`: from the smallest tiles of one round of
+// blocks on to the largest ones.
+BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th,
+                           const std::function<bool(const BatchPlan&)>& holds) {
   struct Cand {
     int tile, k, variant;
   };
@@ -829,8 +834,8 @@ BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th) {
   static const Cand f64t[] = {{8, 6, 1}, {12, 5, 1}, {16, 4, 1}, {20, 3, 1}, {24, 2, 1}};
   const Cand* c = rsz == 4 ? f32 : (th ? f64t : f64);
   const int nc = rsz == 4 ? 8 : (th ? 5 : 7);
-  BatchPlan p;
   for (int i = 0; i < nc; ++i) {
+    BatchPlan p;
     p.tile = c[i].tile;
     p.kf = p.ka = c[i].k;
     p.vf = p.va = c[i].variant;
@@ -840,9 +845,9 @@ BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th) {
       multi_batch_tiles(*g[d], p.tile, &x, &y);
       tiles += (long long)x * y;
     }
-    if (tiles <= 256) break;
+    if ((tiles <= 256 || i == nc - 1) && holds(p)) return p;
   }
-  return p;
+  return BatchPlan();
 }
 
 // whether `steps` steps of a design's tiles fit the block of a variant

@@ -6,6 +6,7 @@
 // the forward sweep, the adjoint sweep and the checkpoint replay on one HIP
 // stream.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -186,6 +187,16 @@ int moments3_fields(const lks_ctx* c) { return c->phys.thermal ? 14 : 10; }
 int acc_capacity(const lks_ctx* c) {
   return c->dim == 3 ? std::max(acc_bound3(c), lks::tag_sum3_parts()) : max_tiles(c->geo);
 }
+
+// the accumulators of `n` tiles of an unsteady forward sweep, and the most there
+// are: many small tiles can outnumber those of the smallest tile height, which
+// take the ones behind the boundary operators
+double* acc_for(lks_ctx* c, int n) {
+  if (n <= acc_capacity(c)) return c->acc;
+  return reinterpret_cast<double*>(static_cast<char*>(c->d_ops) + lks::RING_OPS_BYTES -
+                                   lks::RING_ACC * sizeof(double));
+}
+int acc_most(const lks_ctx* c) { return std::max(acc_capacity(c), lks::RING_ACC); }
 
 size_t traj_bytes(const lks_ctx* c, int K) {
   const size_t N = size_t(c->N), r = size_t(c->rsz);
@@ -691,12 +702,7 @@ struct Run {
   // accumulators of an unsteady forward sweep, zeroed
   void clear_acc() {
     c->acc_n = c->mf.k ? c->mf.ntx * c->mf.nty : acc_count(c);
-    // (many small tiles can outnumber the tiles of the smallest tile height)
-    c->acc_run = c->acc_n <= acc_capacity(c)
-                     ? c->acc
-                     : reinterpret_cast<double*>(static_cast<char*>(c->d_ops) +
-                                                 lks::RING_OPS_BYTES -
-                                                 lks::RING_ACC * sizeof(double));
+    c->acc_run = acc_for(c, c->acc_n);
     lks::launch_fill(c->acc_run, size_t(c->acc_n), 0.0, c->stream);
   }
 
@@ -2005,6 +2011,7 @@ struct lks_batch {
   lks::BatchPlan multi, own_multi;  // the plan in use, and the batch's own
   std::vector<int> ntx, nty;
   int max_tiles = 0;        // tiles of all designs at the shortest tile height
+  int table_tiles = 0;      // ... those the tile table holds: of the plan, if more
   std::vector<int> tmap;    // (design, tile within the design) of every global tile
   // device
   int* d_tmap = nullptr;
@@ -2074,27 +2081,39 @@ void batch_tiles(lks_batch* b) {
   }
 }
 
-// takes the marching plan of a large steady batch, else the several-steps plan
-// where every design's tiles fit its blocks and its accumulators
-void batch_multi(lks_batch* b) {
+// The batch's own plan, which it takes when `use` is set: the marching plan of a
+// large steady batch, else the first several-steps candidate whose tiles fit
+// the tile table (of `most` tiles), the blocks and, unsteady, the accumulators
+// of every design.
+void batch_multi(lks_batch* b, int most, bool use) {
   std::vector<const Geo*> geos;
   for (const lks_ctx* c : b->ctx) geos.push_back(&c->geo);
-  if (!b->unsteady) b->multi = lks::march_batch_plan(geos.data(), b->n, b->rsz);
-  if (b->multi.kf) {
+  const lks::BatchPlan in_use = b->multi;
+  auto holds = [&](const lks::BatchPlan& p) {
+    b->multi = p;
     batch_tiles(b);
-    if (b->total_tiles <= b->max_tiles) return;  // (the table holds that many)
-  }
-  b->multi = lks::multi_batch_plan(geos.data(), b->n, b->rsz, b->thermal);
-  if (b->multi.kf) batch_tiles(b);
-  for (int d = 0; d < b->n && b->multi.kf; ++d) {
-    const lks_ctx* c = b->ctx[d];
-    const int x = b->ntx[d], y = b->nty[d];
-    if (x * y > acc_capacity(c) ||
-        !lks::multi_fits(c->geo, x, y, b->rsz, false, b->multi.vf, b->multi.kf) ||
-        !lks::multi_fits(c->geo, x, y, b->rsz, true, b->multi.va, b->multi.ka))
-      b->multi = lks::BatchPlan();
-  }
+    if (b->total_tiles > most) return false;
+    for (int d = 0; d < b->n && p.vf != lks::MARCH; ++d) {
+      const lks_ctx* c = b->ctx[d];
+      const int x = b->ntx[d], y = b->nty[d];
+      if ((b->unsteady && x * y > acc_most(c)) ||
+          !lks::multi_fits(c->geo, x, y, b->rsz, false, p.vf, p.kf) ||
+          !lks::multi_fits(c->geo, x, y, b->rsz, true, p.va, p.ka))
+        return false;
+    }
+    return true;
+  };
+  lks::BatchPlan p;
+  if (!b->unsteady) p = lks::march_batch_plan(geos.data(), b->n, b->rsz);
+  if (!p.kf || !holds(p))
+    p = lks::multi_batch_plan(geos.data(), b->n, b->rsz, b->thermal, holds);
+  b->own_multi = b->multi = p;
   batch_tiles(b);
+  b->table_tiles = std::max(b->max_tiles, b->total_tiles);
+  if (!use) {
+    b->multi = in_use;
+    batch_tiles(b);
+  }
 }
 
 // LKS_KERNEL_* of a batch's plan
@@ -2112,7 +2131,7 @@ void batch_layout(lks_batch* b) {
   }
   const size_t fwd = sizeof(lks::BatchFwd<double>) * b->n;  // the double variants are larger
   const size_t adj = sizeof(lks::BatchAdj<double>) * 3 * b->n;
-  off += align256(sizeof(int) * 2 * size_t(b->max_tiles)) + align256(fwd) + align256(adj) +
+  off += align256(sizeof(int) * 2 * size_t(b->table_tiles)) + align256(fwd) + align256(adj) +
          align256(sizeof(double) * b->n);
   off += align256(sizeof(double) * b->maxN * b->n) + align256(size_t(b->rsz) * b->maxN);
   off += align256(sizeof(lks::BatchStore<double>) * b->n);
@@ -2205,7 +2224,7 @@ void build_batch_desc(lks_batch* b, double seed, int nf, std::vector<char>& fwd,
       a.ux1 = rp<R>(c->S[p ^ 1][1]);
       a.uy1 = rp<R>(c->S[p ^ 1][2]);
       a.T1 = rp<R>(c->S[p ^ 1][3]);
-      a.acc = b->unsteady ? c->acc : nullptr;
+      a.acc = b->unsteady ? acc_for(c, b->ntx[d] * b->nty[d]) : nullptr;
       a.objective = c->objective;
     }
     const int fin = launches(nf, b->multi.kf) & 1;  // buffer of the final forward level
@@ -2436,8 +2455,7 @@ lks_status lks_batch_create(int n, const lks_grid* grids, const lks_phys* phys, 
   }
   b->rsz = b->ctx[0]->rsz;
   b->thermal = phys[0].thermal ? 1 : 0;
-  batch_multi(b);
-  b->own_multi = b->multi;
+  batch_multi(b, INT_MAX, true);
   if (b->unsteady) {
     // tile heights of the unsteady step launches: 4 and 8
     if (b->ty == 16) batch_set_tile_rows(b, 8, b->multi);
@@ -2459,18 +2477,26 @@ lks_status lks_batch_set_memory_budget(lks_batch* b, size_t bytes) {
   if (b->bound) return bfail(b, LKS_E_STATE, "the budget is planned before lks_batch_bind_workspace");
   const size_t old = b->budget;
   b->budget = bytes;
-  if (!b->unsteady) {
-    if (bytes != 0 && b->total > bytes) {
-      b->budget = old;
-      return bfail(b, LKS_E_NOMEM, "the batch's workspace exceeds the budget");
-    }
-    return LKS_OK;
+  auto plan = [&]() {
+    if (b->unsteady) return plan_batch(b);
+    batch_layout(b);
+    return bytes != 0 && b->total > bytes
+               ? bfail(b, LKS_E_NOMEM, "the batch's workspace exceeds the budget") : LKS_OK;
+  };
+  lks_status st = plan();
+  if (st != LKS_OK && b->table_tiles > b->max_tiles) {
+    // a budget that has no room for the tile table of the several-steps plan
+    // may hold that of another one
+    const bool use = b->multi.kf > 0;
+    batch_multi(b, b->max_tiles, use);
+    st = plan();
+    if (st != LKS_OK) batch_multi(b, INT_MAX, use);
   }
-  lks_status st = plan_batch(b);
   if (st != LKS_OK) {
     const std::string msg = b->err;
     b->budget = old;
-    plan_batch(b);
+    if (b->unsteady) plan_batch(b);
+    else batch_layout(b);
     return bfail(b, st, msg);
   }
   return LKS_OK;
@@ -2517,7 +2543,7 @@ lks_status lks_batch_bind_workspace(lks_batch* b, void* dev_ptr, size_t bytes) {
     p += align256(s);
     return q;
   };
-  b->d_tmap = reinterpret_cast<int*>(take(sizeof(int) * 2 * size_t(b->max_tiles)));
+  b->d_tmap = reinterpret_cast<int*>(take(sizeof(int) * 2 * size_t(b->table_tiles)));
   b->d_fwd = take(sizeof(lks::BatchFwd<double>) * b->n);
   b->d_adj = take(sizeof(lks::BatchAdj<double>) * 3 * b->n);
   b->d_J = reinterpret_cast<double*>(take(sizeof(double) * b->n));

@@ -94,3 +94,65 @@ def test_refused_shapes_change_nothing_in_a_mixed_context():
         assert b.launch_plan() == plan
     b.set_steps_per_launch(1, 2)
     assert b.launch_plan() == (("tile", 1), ("tile", 2))
+
+
+def _designs(sizes, thermal):
+    if thermal:
+        return [W.unsteady_thermal_channel(x, y, Re=60.0, seed=d, n_steps=9)
+                for d, (x, y) in enumerate(sizes)]
+    return [W.steady_channel_uniform(x, y, seed=d, n_fwd=4, n_adj=4)
+            for d, (x, y) in enumerate(sizes)]
+
+
+# (designs, FP32 steps per launch, FP64, FP64 thermal): each candidate of the
+# batches that fit one round of blocks, and the last one, over several rounds
+CANDIDATES = [
+    ([(64, 64)] * 2, 6, 6, 6), ([(64, 64)] * 4, 6, 6, 6), ([(64, 64)] * 6, 5, 5, 5),
+    ([(31, 31), (5, 4), (64, 40)], 6, 6, 6), ([(64, 64)] * 8, 4, 4, 4),
+    ([(100, 100)] * 2, 5, 5, 5), ([(128, 128)] * 2, 5, 5, 5), ([(48, 48)] * 8, 5, 5, 5),
+    ([(144, 144)] * 4, 6, 6, 3), ([(128, 128)] * 5, 6, 5, 3), ([(128, 128)] * 7, 5, 5, 2),
+    ([(200, 200)] * 4, 4, 4, 2), ([(200, 200)] * 5, 3, 3, 2), ([(200, 200)] * 8, 2, 3, 2)]
+
+
+@pytest.mark.parametrize("thermal", [False, True])
+@pytest.mark.parametrize("sizes,f32,f64,f64t", CANDIDATES)
+def test_small_batches_run_several_steps_per_launch(sizes, f32, f64, f64t, thermal):
+    for precision, k in (("fp32", f32), ("fp64", f64t if thermal else f64)):
+        b = lks.Batch(_designs(sizes, thermal), precision=precision, bind=False)
+        assert b.launch_plan() == ("multi", k, k), precision
+
+
+@pytest.mark.parametrize("thermal", [False, True])
+def test_batch_budget_too_small_for_the_plans_table(thermal):
+    """Four designs of 64 x 64 run 6 steps per launch on 256 tiles; the table of
+    the tile kernels holds 64, which leave 4 steps. What a batch without the
+    larger table needs is still enough."""
+    wls = _designs([(64, 64)] * 4, thermal)
+    b = lks.Batch(wls, precision="fp32", bind=False)
+    full = b.workspace_size()
+    b.set_memory_budget(full)
+    assert b.launch_plan() == ("multi", 6, 6)
+    small = lks.Batch(wls, precision="fp32", bind=False)
+    # (unsteady: of the largest plan; its smaller ones fit with either table)
+    tables = 8 * (256 - 64)
+    if thermal:
+        lo, hi = 1, full
+        while hi - lo > 256:  # the smallest budget
+            mid = (lo + hi) // 2
+            try:
+                lks.Batch(wls, precision="fp32", bind=False).set_memory_budget(mid)
+                hi = mid
+            except lks.LKSError:
+                lo = mid
+        small.set_memory_budget(hi)
+    else:
+        small.set_memory_budget(full - tables)
+    assert small.launch_plan() == ("multi", 4, 4)
+    with pytest.raises(lks.LKSError) as e:
+        b.set_memory_budget(1)
+    assert e.value.status == lks.LKS_E_NOMEM and b.launch_plan() == ("multi", 6, 6)
+    assert b.workspace_size() == full
+    b.set_tile_rows(8)
+    with pytest.raises(lks.LKSError):
+        b.set_memory_budget(1)
+    assert b.launch_plan() == ("tile", 1, 1)
