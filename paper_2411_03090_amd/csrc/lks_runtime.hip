@@ -2116,6 +2116,15 @@ void batch_multi(lks_batch* b, int most, bool use) {
   }
 }
 
+// the captured step sequence holds the addresses and launch shapes of its run
+void drop_graph(lks_batch* b) {
+  if (!b->exec) return;
+  hipGraphExecDestroy(b->exec);
+  hipGraphDestroy(b->graph);
+  b->exec = nullptr;
+  b->graph = nullptr;
+}
+
 // LKS_KERNEL_* of a batch's plan
 int batch_kernel(const lks::BatchPlan& p) {
   return p.kf == 0 ? LKS_KERNEL_TILE : (p.vf == lks::MARCH ? LKS_KERNEL_MARCH : LKS_KERNEL_MULTI);
@@ -2532,6 +2541,7 @@ lks_status lks_batch_bind_workspace(lks_batch* b, void* dev_ptr, size_t bytes) {
   if (!dev_ptr || (reinterpret_cast<uintptr_t>(dev_ptr) & 255))
     return bfail(b, LKS_E_INVALID, "workspace must be non-null and 256-byte aligned");
   if (bytes < b->total) return bfail(b, LKS_E_NOMEM, "workspace smaller than lks_batch_workspace_size");
+  drop_graph(b);
   char* base = static_cast<char*>(dev_ptr);
   for (int d = 0; d < b->n; ++d) {
     lks_status st = lks_bind_workspace(b->ctx[d], base + b->off[d], b->ctx[d]->plan.total);
@@ -2627,12 +2637,7 @@ lks_status lks_batch_run(lks_batch* b, const double* const* gamma_dev, int n_fwd
     }
   }
   if (use_graph) {
-    if (b->exec && (b->g_nf != n_fwd || b->g_na != n_adj)) {
-      hipGraphExecDestroy(b->exec);
-      hipGraphDestroy(b->graph);
-      b->exec = nullptr;
-      b->graph = nullptr;
-    }
+    if (b->g_nf != n_fwd || b->g_na != n_adj) drop_graph(b);
     if (!b->exec) {
       if (!hip_ok(nullptr, hipStreamBeginCapture(b->own, hipStreamCaptureModeThreadLocal),
                   "begin capture", &st))
@@ -2693,12 +2698,7 @@ static lks_status batch_set_tile_rows(lks_batch* b, int ty, const lks::BatchPlan
   b->multi = multi;
   batch_tiles(b);
   b->ty = ty;
-  if (b->exec) {
-    hipGraphExecDestroy(b->exec);
-    hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
-  }
+  drop_graph(b);
   lks_status st = LKS_OK;
   build_tile_map(b);
   // the upload is ordered before every later launch on the user stream;

@@ -95,3 +95,21 @@ def test_unsteady_batch_candidates(sizes, precision, thermal, mode):
     J1, b = _batch(wls, precision, None, n, n, **kw)
     assert all(abs(x - y) <= 1e-13 * max(abs(x), 1.0) for x, y in zip(J0, J1))
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def test_a_batch_bound_again_captures_its_steps_again():
+    """The captured sequence holds addresses of the workspace it was captured on."""
+    wls = [W.steady_channel_uniform(40, 24, Re=20.0, seed=d, n_fwd=9, n_adj=8) for d in range(2)]
+    b = lks.Batch(wls, precision="fp64", device=DEV)
+    gs = [T(w.gamma) for w in wls]
+    outs = [torch.empty_like(g) for g in gs]
+    J0 = b.run(gs, outs, 9, 8)
+    ref = [o.clone() for o in outs]
+    first = b.workspace  # kept: the sequence of before would still run on it
+    b.bind()
+    first.zero_()
+    for o in outs:
+        o.zero_()
+    assert b.run(gs, outs, 9, 8) == J0
+    assert all(torch.equal(o, r) for o, r in zip(outs, ref))
+    assert not first.any()
