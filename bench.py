@@ -13,8 +13,8 @@ path stays within the stated bounds (fields 1e-5, J and dJ/dgamma 1e-3,
 relative L2); the others are reported beside it.
 
 Further sections of the same JSON line (not the headline value):
-  batched_64_designs        64 independent steady designs of uneven size, one
-                            launch per step for all, HIP graph replay;
+  batched_64_designs        64 independent steady designs of uneven size in one
+                            sequence of launches, HIP graph replay;
   steady_2048x2048          the headline's recipe at 16x the nodes;
   unsteady_thermal_1024x512 the checkpointed unsteady thermal sweep;
   heat_exchanger_201x201    the steady heat exchanger (heat source);
@@ -24,10 +24,13 @@ Further sections of the same JSON line (not the headline value):
 Rooflines. Every step is a memory-bound gather, so each section reports the
 HBM roofline of its dominant kernel: algorithmic bytes per launch (bytes per
 lattice update x updates per launch) over the average launch duration measured
-with HIP events on the context's stream. The algorithmic bytes per update
+with HIP events on the context's stream, both of the kernel that runs
+(LKS.launch_plan). The algorithmic bytes per update
 read the state once and write it once, with gamma the only static field and
 an FP64 sensitivity accumulator read and written once per update where the
-sweep accumulates it (ALGO_BYTES). The library's own accounting (the adjoint
+sweep accumulates it (ALGO_BYTES). A launch of several steps passes over memory
+once for all of them, so the bytes of its updates can exceed what HBM delivers;
+one_pass_achieved counts them once per launch. The library's own accounting (the adjoint
 state kept as equilibrium coefficients, 1/(1 + alpha) and the node-class byte
 read in place of gamma) is reported beside it (LIB_BYTES), and so are the HBM
 bytes the rocprofv3 counters FETCH_SIZE and WRITE_SIZE measured for the same
@@ -50,7 +53,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 CSRC = os.path.join(ROOT, "paper_2411_03090_amd", "csrc")
-KERNEL_SOURCES = ("lks_kernels.hip", "lks_kernels3d.hip", "lks_device.h")
+KERNEL_SOURCES = ("lks_kernels.hip", "lks_multi.hip", "lks_march.hip", "lks_kernels3d.hip",
+                  "lks_node.h", "lks_device.h")
 SECTIONS = ("headline", "batch", "ubatch", "large", "unsteady", "exchanger", "sink", "duct3d")
 BOUND_FIELDS, BOUND_GRAD = 1e-5, 1e-3
 
@@ -99,9 +103,10 @@ def parse(argv=None):
     p.add_argument("--only", default="",
                    help="comma-separated sections to run (default: all): " + ",".join(SECTIONS))
     p.add_argument("--shapes", default="",
-                   help="JSON {section: {precision: [tile_rows, fwd_steps, adj_steps]}} of "
-                        "fixed launch shapes (no autotuning), e.g. from a previous line's "
-                        "launch_shape entries")
+                   help="JSON {section: {precision: [tile_rows, fwd_steps, adj_steps, "
+                        "fwd_kernel, adj_kernel]}} of fixed launch shapes (no autotuning), "
+                        "the values of a previous line's launch_shape entries; without "
+                        "the kernels, those of the tiles")
     p.add_argument("--copy-calibration", action="store_true",
                    help="only run a 256 MiB device copy (counter calibration)")
     return p.parse_args(argv)
@@ -120,10 +125,22 @@ def rel(a, b):
     return float(np.linalg.norm(a - b) / nb) if nb > 0 else float(np.linalg.norm(a))
 
 
-def kernel_name(sweep, dtype, thermal, ty, spl):
-    base = "lks_step" if sweep == "fwd" else "alks_step"
-    k = base + ("2_kernel" if spl == 2 else "_kernel")
-    return f"{k}<{dtype}, {'true' if thermal else 'false'}, {ty}>"
+def sweep_kernel(ctx, sweep, dtype, thermal):
+    """(name, steps per launch) of the kernel a context's sweep takes."""
+    kernel, steps = ctx.launch_plan()[0 if sweep == "fwd" else 1]
+    return kernel_name(sweep, dtype, thermal, kernel, steps, ctx.launch_shape()[0]), steps
+
+
+def kernel_name(sweep, dtype, thermal, kernel, steps, ty, many=""):
+    """Name of a D2Q9 step kernel; `many`: "batch" or "ubatch"."""
+    base = "lks" if sweep == "fwd" else "alks"
+    th = "true" if thermal else "false"
+    many = many and "_" + many
+    if kernel == "march":
+        return f"{base}_march{many}_kernel<{dtype}, {steps}>"
+    if kernel == "multi":  # (and its block size)
+        return f"{base}_multi{many}_kernel<{dtype}, {th}>"
+    return f"{base}_step{'2' if steps == 2 else ''}{many}_kernel<{dtype}, {th}, {ty}>"
 
 
 def sources_sha():
@@ -146,10 +163,10 @@ def traffic_per_launch(section, kernel):
     return k["fetch_kib"] * 1024 / t["fetch_factor"] + k["write_kib"] * 1024 / t["write_factor"]
 
 
-def roofline(section, kernel, key, dtype, updates_per_launch, launch_us):
+def roofline(section, kernel, key, dtype, updates_per_launch, launch_us, steps=1):
     """The HBM roofline entry of one kernel: algorithmic bytes (ALGO_BYTES)
-    per launch over the measured launch duration, the library's bytes
-    (LIB_BYTES) and the counter-measured HBM bytes beside it."""
+    per launch of `steps` steps over the measured launch duration, the library's
+    bytes (LIB_BYTES) and the counter-measured HBM bytes beside it."""
     i = 0 if dtype == "float" else 1
     algo_b = ALGO_BYTES[key][i] * updates_per_launch
     lib_b = LIB_BYTES[key][i] * updates_per_launch
@@ -161,7 +178,10 @@ def roofline(section, kernel, key, dtype, updates_per_launch, launch_us):
            "node_updates_per_launch": updates_per_launch,
            "algorithmic_bytes_per_launch": algo_b,
            "library_bytes_per_node_update": LIB_BYTES[key][i],
-           "library_achieved": lib_b / (launch_us * 1e-6) / 1e9}
+           "library_achieved": lib_b / (launch_us * 1e-6) / 1e9, "steps_per_launch": steps}
+    if steps > 1:
+        out["one_pass_achieved"] = achieved / steps
+        out["one_pass_frac"] = achieved / steps / HBM_PEAK_GBS
     if traffic is not None:
         out["hbm_measured"] = traffic / (launch_us * 1e-6) / 1e9
         out["hbm_measured_frac"] = out["hbm_measured"] / HBM_PEAK_GBS
@@ -169,24 +189,43 @@ def roofline(section, kernel, key, dtype, updates_per_launch, launch_us):
 
 
 def apply_shape(ctx, shape):
-    ty, sf, sa = shape
+    ty, sf, sa, kf, ka = (list(shape) + ["tile", "tile"])[:5]
     ctx.set_tile_rows(int(ty))
-    ctx.set_steps_per_launch(int(sf), int(sa))
+    ctx.set_steps_per_launch(int(sf) if kf == "tile" else 1, int(sa) if ka == "tile" else 1)
+    ctx.set_launch_plan(kf, ka)
 
 
-def shape_dict(s):
-    return {"tile_rows": s[0], "forward_steps_per_launch": s[1], "adjoint_steps_per_launch": s[2]}
+def apply_batch_shape(b, shape):
+    ty, _, _, kernel = (list(shape) + ["tile"])[:4]
+    b.set_tile_rows(int(ty))
+    b.set_launch_plan(kernel)
+
+
+def shape_dict(ctx):
+    """The launch shape in the order of --shapes."""
+    (kf, sf), (ka, sa) = ctx.launch_plan()
+    return {"tile_rows": ctx.launch_shape()[0], "forward_steps_per_launch": sf,
+            "adjoint_steps_per_launch": sa, "forward_kernel": kf, "adjoint_kernel": ka}
+
+
+def batch_shape_dict(b, ty):
+    kernel, sf, sa = b.launch_plan()
+    return {"tile_rows": ty, "forward_steps_per_launch": sf, "adjoint_steps_per_launch": sa,
+            "forward_kernel": kernel, "adjoint_kernel": kernel}
 
 
 def steady_launch_us(ctx, g, wl, sweep, nprobe):
     """Average launch duration of the steady forward (lks_advance) or adjoint
-    (alks_advance) kernel over nprobe back-to-back steps, measured with
-    events on the context's stream (torch's current stream)."""
+    (alks_advance) kernel over about nprobe back-to-back steps in full launches,
+    measured with events on the context's stream (torch's current stream), and
+    the steps per launch."""
     import torch
     out = torch.empty_like(g)
     ctx.forward(g, wl.n_fwd)
     ctx.backward(1.0, out, 10)
     torch.cuda.synchronize()
+    spl = ctx.launch_plan()[0 if sweep == "fwd" else 1][1]
+    nprobe = max(1, nprobe // spl) * spl
     e0 = ev()
     if sweep == "fwd":
         ctx.advance(g, nprobe)
@@ -194,8 +233,6 @@ def steady_launch_us(ctx, g, wl, sweep, nprobe):
         ctx.adjoint_advance(1.0, nprobe, None)
     e1 = ev()
     torch.cuda.synchronize()
-    ty, sf, sa = ctx.launch_shape()
-    spl = sf if sweep == "fwd" else sa
     return e0.elapsed_time(e1) * 1e3 / nprobe * spl, spl
 
 
@@ -263,7 +300,7 @@ def headline(args, dev, shapes):
               and err["dJdgamma_l2"] <= BOUND_GRAD)
         paths[prec] = {"mlups": upd / (r["ms"] * 1e-3) / 1e6, "ms_per_gradient": r["ms"],
                        "gradients_per_s": 1e3 / r["ms"], "J": r["J"],
-                       "launch_shape": shape_dict(ctxs[prec].launch_shape()),
+                       "launch_shape": shape_dict(ctxs[prec]),
                        "vs_fp64_rel_error": err, "within_stated_error": ok}
     head = min((p for p in paths if paths[p]["within_stated_error"]),
                key=lambda p: paths[p]["ms_per_gradient"])
@@ -271,26 +308,24 @@ def headline(args, dev, shapes):
     # roofline of the headline path's dominant kernel: the sweep with the
     # larger share of the gradient's time
     c = ctxs[head]
-    ty, sf, sa = c.launch_shape()
     fwd_us, spl_f = steady_launch_us(c, g, wl, "fwd", args.probe_steps)
     adj_us, spl_a = steady_launch_us(c, g, wl, "adj", args.probe_steps)
     fdt = "double" if head in ("fp64", "mixed") else "float"
     adt = "double" if head == "fp64" else "float"
     if wl.n_fwd / spl_f * fwd_us >= wl.n_adj / spl_a * adj_us:
-        rf = roofline("headline", kernel_name("fwd", fdt, False, ty, spl_f), ("2d", "fwd"), fdt,
-                      nodes * spl_f, fwd_us)
+        rf = roofline("headline", sweep_kernel(c, "fwd", fdt, False)[0], ("2d", "fwd"), fdt,
+                      nodes * spl_f, fwd_us, spl_f)
     else:
-        rf = roofline("headline", kernel_name("adj", adt, False, ty, spl_a), ("2d", "adj_steady"),
-                      adt, nodes * spl_a, adj_us)
+        rf = roofline("headline", sweep_kernel(c, "adj", adt, False)[0], ("2d", "adj_steady"),
+                      adt, nodes * spl_a, adj_us, spl_a)
     other = {"forward_launch_us": fwd_us, "adjoint_launch_us": adj_us}
     # the FP32 adjoint kernel (the FP32 and mixed paths share it)
     if head != "fp32":
         c32 = ctxs["fp32"]
-        ty32, _, _ = c32.launch_shape()
         a32_us, spl32 = steady_launch_us(c32, g, wl, "adj", args.probe_steps)
         other["fp32_adjoint_roofline"] = roofline(
-            "headline", kernel_name("adj", "float", False, ty32, spl32), ("2d", "adj_steady"),
-            "float", nodes * spl32, a32_us)
+            "headline", sweep_kernel(c32, "adj", "float", False)[0], ("2d", "adj_steady"),
+            "float", nodes * spl32, a32_us, spl32)
     del ctxs, c
     torch.cuda.empty_cache()
     return {"wl": wl, "head": head, "paths": paths, "roofline": rf, "roofline_detail": other}
@@ -301,8 +336,8 @@ def headline(args, dev, shapes):
 # ---------------------------------------------------------------------------
 def batched_bench(args, dev, shapes):
     """64 independent steady designs, edge lengths from {128,...,512} and
-    Re in [10, 200], forward + adjoint of all designs with one launch per
-    step, replayed as a HIP graph (FP32 state, FP64 J and dJ/dgamma)."""
+    Re in [10, 200], forward + adjoint of all designs in one sequence of
+    launches, replayed as a HIP graph (FP32 state, FP64 J and dJ/dgamma)."""
     import torch
     from paper_2411_03090_amd import lks, workloads as W
     n = args.batch_steps
@@ -313,7 +348,7 @@ def batched_bench(args, dev, shapes):
     outs = [torch.empty_like(x) for x in gs]
     if "fp32" in shapes.get("batch", {}):
         ty = int(shapes["batch"]["fp32"][0])
-        b.set_tile_rows(ty)
+        apply_batch_shape(b, shapes["batch"]["fp32"])
     else:
         ty = b.autotune(gs, outs, 50)
     b.run(gs, outs, n, n)                                   # warm-up, builds the graph
@@ -340,13 +375,16 @@ def batched_bench(args, dev, shapes):
     e1 = ev()
     torch.cuda.synchronize()
     fwd_us = (e0.elapsed_time(e1) * 1e3 - adj_us) / n
+    kernel, sf, sa = b.launch_plan()
     return {"designs": 64, "nodes": nodes, "n_fwd": n, "n_adj": n, "ms_per_batch": ms,
             "mlups": nodes * 2 * n / (ms * 1e-3) / 1e6,
-            "gradients_per_s": 64 * 1e3 / ms, "launch_shape": shape_dict((ty, 1, 1)),
-            "roofline": roofline("batch", f"alks_step_batch_kernel<float, false, {ty}>",
-                                 ("2d", "adj_steady"), "float", nodes, adj_us),
-            "forward_roofline": roofline("batch", f"lks_step_batch_kernel<float, false, {ty}>",
-                                         ("2d", "fwd"), "float", nodes, fwd_us)}
+            "gradients_per_s": 64 * 1e3 / ms, "launch_shape": batch_shape_dict(b, ty),
+            "roofline": roofline(
+                "batch", kernel_name("adj", "float", False, kernel, sa, ty, "batch"),
+                ("2d", "adj_steady"), "float", nodes * sa, adj_us * sa, sa),
+            "forward_roofline": roofline(
+                "batch", kernel_name("fwd", "float", False, kernel, sf, ty, "batch"), ("2d", "fwd"),
+                "float", nodes * sf, fwd_us * sf, sf)}
 
 
 def ubatch_bench(args, dev, shapes):
@@ -354,7 +392,7 @@ def ubatch_bench(args, dev, shapes):
     {128,...,512}, Re in [10, 200], Pr = 6, oscillating inflow, time-averaged
     enthalpy flux through the last interior column) over one horizon of n
     steps: the forward sweep and the checkpointed adjoint sweep of all
-    designs, one launch per step for all of them, replayed as a HIP graph;
+    designs in one sequence of launches, replayed as a HIP graph;
     one checkpoint interval for the batch from its memory budget (16 GiB
     FP32, 32 GiB FP64).
 
@@ -368,9 +406,10 @@ def ubatch_bench(args, dev, shapes):
     nodes = sum(w.nx * w.ny for w in wls)
     gs = [torch.tensor(w.gamma.reshape(-1), dtype=torch.float64, device=dev) for w in wls]
 
-    def timed(prec, budget, ty, reps=2, steps=False):
+    def timed(prec, budget, shape, reps=2, steps=False):
         b = lks.Batch(wls, precision=prec, device=dev, mem_budget=budget)
-        b.set_tile_rows(ty)
+        if shape is not None:                           # None: the kernels of its default
+            apply_batch_shape(b, shape)
         outs = [torch.empty_like(x) for x in gs]
         Js = b.run(gs, outs, n, n)                      # warm-up, builds the graph
         torch.cuda.synchronize()
@@ -382,7 +421,8 @@ def ubatch_bench(args, dev, shapes):
         K, rep, ws = b.checkpoint_info()
         out = {"ms_per_batch": ms, "mlups": nodes * 2 * n / (ms * 1e-3) / 1e6,
                "gradients_per_s": 64 * 1e3 / ms, "K": K, "replay_steps": rep,
-               "workspace_GiB": ws / 2 ** 30, "budget_GiB": budget / 2 ** 30, "tile_rows": ty}
+               "workspace_GiB": ws / 2 ** 30, "budget_GiB": budget / 2 ** 30,
+               "launch_shape": batch_shape_dict(b, shape[0] if shape else 8)}
         sens = np.concatenate([o.cpu().numpy() for o in outs])
         if steps:
             b.run(gs, outs, n, 0)                       # forward-only graph
@@ -403,26 +443,27 @@ def ubatch_bench(args, dev, shapes):
 
     res = {"designs": 64, "nodes": nodes, "steps": n}
     sh = shapes.get("ubatch", {})
-    ty32 = int(sh["fp32"][0]) if "fp32" in sh else None
-    if ty32 is None:                                    # the faster tile height
-        tries = {ty: timed("fp32", 16 * 2 ** 30, ty, reps=1)[0]["ms_per_batch"] for ty in (4, 8)}
-        ty32 = min(tries, key=tries.get)
-    a, J32, s32 = timed("fp32", 16 * 2 ** 30, ty32, steps=True)
-    ty64 = int(sh["fp64"][0]) if "fp64" in sh else 8
-    c, J64, s64 = timed("fp64", 32 * 2 ** 30, ty64)
+    s32 = sh.get("fp32")
+    if s32 is None:                                     # the faster of the shapes
+        tries = [(timed("fp32", 16 * 2 ** 30, x, reps=1)[0]["ms_per_batch"], i, x)
+                 for i, x in enumerate((None, [4, 1, 1], [8, 1, 1]))]
+        s32 = min(tries)[2]
+    a, J32, d32 = timed("fp32", 16 * 2 ** 30, s32, steps=True)
+    c, J64, d64 = timed("fp64", 32 * 2 ** 30, sh.get("fp64"))
     res.update({"fp32": a, "fp64": c,
                 "speedup_fp32_vs_fp64": c["ms_per_batch"] / a["ms_per_batch"],
                 "fp32_vs_fp64_rel_error": {
                     "J_max": float(np.max(np.abs(J32 - J64) / np.abs(J64))),
-                    "dJdgamma_l2": rel(s32, s64)}})
-    res["roofline"] = roofline("ubatch", f"alks_step_ubatch_kernel<float, true, {ty32}>",
-                               ("2d_thermal", "adj_unsteady"), "float", nodes,
-                               a["adjoint_step_us"])
+                    "dJdgamma_l2": rel(d32, d64)}})
+    ty, sf, sa, kernel, _ = a["launch_shape"].values()
+    res["roofline"] = roofline(
+        "ubatch", kernel_name("adj", "float", True, kernel, sa, ty, "ubatch"),
+        ("2d_thermal", "adj_unsteady"), "float", nodes * sa, a["adjoint_step_us"] * sa, sa)
     res["roofline"]["note"] = ("step duration: the full run less its forward and replayed "
                                "steps at the forward-only run's step time")
-    res["forward_roofline"] = roofline("ubatch", f"lks_step_ubatch_kernel<float, true, {ty32}>",
-                                       ("2d_thermal", "fwd"), "float", nodes,
-                                       a["forward_step_us"])
+    res["forward_roofline"] = roofline(
+        "ubatch", kernel_name("fwd", "float", True, kernel, sf, ty, "ubatch"),
+        ("2d_thermal", "fwd"), "float", nodes * sf, a["forward_step_us"] * sf, sf)
     return res
 
 
@@ -441,7 +482,6 @@ def large_bench(args, dev, shapes):
         apply_shape(c, shapes["large"]["fp32"])
     else:
         c.autotune(g, 50)
-    ty, sf, sa = c.launch_shape()
     out = torch.empty_like(g)
     torch.cuda.synchronize()
     e0 = ev()
@@ -451,14 +491,14 @@ def large_bench(args, dev, shapes):
     e1 = ev()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
-    fwd_us, _ = steady_launch_us(c, g, wl, "fwd", min(args.probe_steps, 1000))
-    adj_us, _ = steady_launch_us(c, g, wl, "adj", min(args.probe_steps, 1000))
+    fwd_us, sf = steady_launch_us(c, g, wl, "fwd", min(args.probe_steps, 1000))
+    adj_us, sa = steady_launch_us(c, g, wl, "adj", min(args.probe_steps, 1000))
     res = {"mlups": nodes * 2 * n / (ms * 1e-3) / 1e6, "ms_per_gradient": ms,
-           "n_fwd": n, "n_adj": n, "nodes": nodes, "launch_shape": shape_dict((ty, sf, sa)),
-           "roofline": roofline("large", kernel_name("adj", "float", False, ty, sa),
-                                ("2d", "adj_steady"), "float", nodes * sa, adj_us),
-           "forward_roofline": roofline("large", kernel_name("fwd", "float", False, ty, sf),
-                                        ("2d", "fwd"), "float", nodes * sf, fwd_us)}
+           "n_fwd": n, "n_adj": n, "nodes": nodes, "launch_shape": shape_dict(c),
+           "roofline": roofline("large", sweep_kernel(c, "adj", "float", False)[0],
+                                ("2d", "adj_steady"), "float", nodes * sa, adj_us, sa),
+           "forward_roofline": roofline("large", sweep_kernel(c, "fwd", "float", False)[0],
+                                        ("2d", "fwd"), "float", nodes * sf, fwd_us, sf)}
     del c
     torch.cuda.empty_cache()
     return res
@@ -522,12 +562,10 @@ def unsteady_bench(args, dev, shapes):
             c.autotune(g, 100)
     nodes = wl.nx * wl.ny
     res, _ = _checkpointed(c32, c64, g, nodes, n)
-    ty = c32.launch_shape()[0]
-    res["launch_shape"] = {"fp32": shape_dict(c32.launch_shape()),
-                           "fp64": shape_dict(c64.launch_shape())}
-    res["roofline"] = roofline("unsteady", kernel_name("adj", "float", True, ty, 1),
-                               ("2d_thermal", "adj_unsteady"), "float", nodes,
-                               res["fp32"]["adjoint_step_us"])
+    res["launch_shape"] = {"fp32": shape_dict(c32), "fp64": shape_dict(c64)}
+    kernel, sa = sweep_kernel(c32, "adj", "float", True)
+    res["roofline"] = roofline("unsteady", kernel, ("2d_thermal", "adj_unsteady"), "float",
+                               nodes * sa, res["fp32"]["adjoint_step_us"] * sa, sa)
     res["roofline"]["note"] = "launch duration estimated from the backward call less its replay"
     res.update({"nodes": nodes, "steps": n, "budget_GiB": {"fp32": 4, "fp64": 8}})
     del c32, c64
@@ -564,7 +602,7 @@ def exchanger_bench(args, dev, shapes):
         ms = e0.elapsed_time(e1)
         res[prec] = {"ms_per_gradient": ms, "mlups": nodes * 2 * n / (ms * 1e-3) / 1e6,
                      "gradients_per_s": 1e3 / ms, "J": J,
-                     "launch_shape": shape_dict(c.launch_shape())}
+                     "launch_shape": shape_dict(c)}
         outs[prec] = out.cpu().numpy()
         del c
     J64 = res["fp64"]["J"]
@@ -613,7 +651,7 @@ def sink_bench(args, dev, shapes):
         o = out.cpu().numpy()
         res[key] = {"ms_per_gradient": ms, "mlups": nodes * 2 * n / (ms * 1e-3) / 1e6,
                     "gradients_per_s": 1e3 / ms, "J": J,
-                    "launch_shape": shape_dict(c.launch_shape()),
+                    "launch_shape": shape_dict(c),
                     "dJdgamma_finite": bool(np.isfinite(o).all()),
                     "dJdgamma_max_abs": float(np.abs(o).max()) if np.isfinite(o).all() else None}
         outs[key] = o
