@@ -1600,7 +1600,6 @@ __global__ __launch_bounds__(ZT, sizeof(R) == 4 ? 3 : 1) void alks3f_kernel(Geo3
   }
   unsigned i0 = unsigned(n0.lds - SX - 1), i1 = unsigned(n1.lds - SX - 1);
   unsigned e0 = unsigned(n0.ci), e1 = unsigned(n1.ci);
-  auto has = [&](int q) { return pz || (q >= 0 && q < g.nz); };
   // first node of plane q (of the nearest one that exists)
   auto plane = [&](int q) {
     if (pz) {
