@@ -820,6 +820,24 @@ void multi_batch_tiles(const Geo& g, int tile, int* ntx, int* nty) {
 // kernels, FP64 30 x 30 and 3 steps 46.9, 48.4 against 65.9, 79.3; 16 thermal
 // ones, 1.46M nodes, FP32 33.9, 38.0 against 39.5, 41.6, FP64 24 x 24 and 2 steps
 // 61.9, 71.5 against 82.8, 92.5.
+// What several rounds cost grows with the rounds, whatever the tiles hold, and
+// the tile kernels' time with their blocks, so designs a few tiles wide or tall
+// and, in FP32 without temperature, whole rounds of it are left to those. us per
+// step, tile kernels -> R rounds instead of B blocks: FP32 5 designs of 256 x 256 8.6
+// -> 7.9 (R = 2, B = 640), 24 of 200 x 200 18.3 -> 16.7 (4, 2400), but one of 1000 x 1000
+// 13.7 -> 14.8 (4, 2000) and 30 of 300 x 40 9.6 -> 11.4 (3, 750); FP64 100 of 64 x 64
+// 17.4 -> 14.8 (4, 800), 16 of 1000 x 10 8.7 -> 9.5 (3, 512); thermal FP32 5 of 256 x 256
+// 16.0 -> 13.8 (2, 1280), 20 of 700 x 5 11.1 -> 12.8 (2, 440); thermal FP64 16 of 1000 x 10
+// 18.1 -> 17.8 (3, 768), 20 of 700 x 5 11.9 -> 16.5 (3, 440).
+bool worth_rounds(const Geo* const* g, int n, int rsz, bool th, long long tiles) {
+  const long long R = (tiles + 255) / 256;
+  long long B = 0;
+  for (int d = 0; d < n; ++d)
+    B += (long long)tiles_along(g[d]->nx, TX) * tiles_along(g[d]->ny, th ? 4 : 8);
+  if (th) return B >= (rsz == 4 ? 500 : 250) * R;
+  return R <= 2 || B >= (rsz == 4 ? 850 * R - 1050 : 180 * R);
+}
+
 // The first candidate that `holds`: from the smallest tiles of one round of
 // blocks on to the largest ones.
 BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th,
@@ -845,7 +863,8 @@ BatchPlan multi_batch_plan(const Geo* const* g, int n, int rsz, bool th,
       multi_batch_tiles(*g[d], p.tile, &x, &y);
       tiles += (long long)x * y;
     }
-    if ((tiles <= 256 || i == nc - 1) && holds(p)) return p;
+    if ((tiles <= 256 || (i == nc - 1 && worth_rounds(g, n, rsz, th, tiles))) && holds(p))
+      return p;
   }
   return BatchPlan();
 }

@@ -156,3 +156,18 @@ def test_batch_budget_too_small_for_the_plans_table(thermal):
     with pytest.raises(lks.LKSError):
         b.set_memory_budget(1)
     assert b.launch_plan() == ("tile", 1, 1)
+
+
+@pytest.mark.parametrize("sizes,thermal,f32,f64", [
+    ([(256, 256)] * 5, False, "multi", "multi"), ([(200, 200)] * 24, False, "multi", "multi"),
+    ([(1000, 1000)], False, "tile", "multi"), ([(300, 40)] * 30, False, "tile", "multi"),
+    ([(1000, 10)] * 16, False, "multi", "tile"), ([(64, 64)] * 100, False, "multi", "multi"),
+    ([(256, 256)] * 5, True, "multi", "multi"), ([(1000, 1000)], True, "multi", "multi"),
+    ([(700, 5)] * 20, True, "tile", "tile"), ([(1000, 10)] * 16, True, "tile", "multi"),
+    ([(5, 700)] * 20, True, "multi", "multi")])
+def test_batches_of_several_rounds_take_the_faster_kernels(sizes, thermal, f32, f64):
+    """Where several rounds of blocks were measured slower than the tile kernels,
+    the tile kernels stay."""
+    for precision, kernel in (("fp32", f32), ("fp64", f64)):
+        b = lks.Batch(_designs(sizes, thermal), precision=precision, bind=False)
+        assert b.launch_plan()[0] == kernel, precision
