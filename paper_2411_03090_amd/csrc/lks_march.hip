@@ -203,7 +203,8 @@ __device__ __forceinline__ void fwd_push(const FwdMarch<R, K>& w, FwdLevel<R>* L
         v0 = l.v[2];
       }
       fwd_post(w.A, d0, u0, v0, lane_dx<MODE>(c, u0), row_dy<MODE>(l.u[0], l.u[1], l.u[2], e),
-               lane_dx<MODE>(c, v0), row_dy<MODE>(l.v[0], l.v[1], l.v[2], e), f);
+               lane_dx<MODE>(c, v0), row_dy<MODE>(l.v[0], l.v[1], l.v[2], e),
+               [&](int q, R x) { f[q] = x; });
       s4 = f[4];
       s7 = lane<RIGHT>(f[7]);
       s8 = lane<LEFT>(f[8]);
@@ -223,8 +224,10 @@ __device__ __forceinline__ void fwd_push(const FwdMarch<R, K>& w, FwdLevel<R>* L
           const R p3 = o == 0 ? q[6] : (o == 2 ? q[7] : q[5]);
           const R p4 = o == 0 ? q[7] : (o == 3 ? q[6] : q[8]);
           const R Sp = p2 + p3 + p4;
-          fwd_ring<R, false>(w.g, S0, Sp, R(0), R(0), o, l.m, l.bx, l.by,
-                             (l.m & 3) == FLOW_VELOCITY ? w.fac[LV] : 0.0, R(0), dn, un, vn, Tn);
+          const double fac = (l.m & 3) == FLOW_VELOCITY ? w.fac[LV] : 0.0;
+          fwd_ring<R, false>(
+              w.g, S0, Sp, R(0), R(0), o, l.m, [&](int x) { return x ? l.by : l.bx; },
+              [&]() { return fac; }, [&]() { return R(0); }, dn, un, vn, Tn);
           if (ye && c.ex) {
             un = vn = R(0);
             dn = l.last;  // (of row 0: taken from row 1 later)

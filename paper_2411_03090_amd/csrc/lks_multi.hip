@@ -207,7 +207,8 @@ __device__ __forceinline__ void multi_fwd(const Geo& g, const FwdArgs<R>& a, con
         auto dx = [&](int f) { return end_d(L[f], p, 1, RING ? n[e].ex() : 0); };
         auto dy = [&](int f) { return end_d(L[f], p, W, RING ? n[e].ey() : 0); };
         R f[9];
-        fwd_post(A, d[e], u[e], v[e], dx(LU), dy(LU), dx(LV), dy(LV), f);
+        fwd_post(A, d[e], u[e], v[e], dx(LU), dy(LU), dx(LV), dy(LV),
+                 [&](int q, R x) { f[q] = x; });
         f0[e] = f[0];
 #pragma unroll
         for (int q = 1; q < 9; ++q) L[LF + q - 1][p] = f[q];
@@ -254,8 +255,10 @@ __device__ __forceinline__ void multi_fwd(const Geo& g, const FwdArgs<R>& a, con
         const R S0 = f[0] + x[0] + x[1], Sp = x[2] + x[3] + x[4];
         const R S0g = gg[0] + y[0] + y[1], Spg = y[2] + y[3] + y[4];
         const bool vel = (m[e] & 3) == FLOW_VELOCITY;
-        fwd_ring<R, TH>(g, S0, Sp, S0g, Spg, o, m[e], ubx[e], uby[e], vel ? a.ufac[level] : 0.0,
-                        Tb[e], dn, un, vn, Tn);
+        const double fac = vel ? a.ufac[level] : 0.0;
+        fwd_ring<R, TH>(
+            g, S0, Sp, S0g, Spg, o, m[e], [&](int c) { return c ? uby[e] : ubx[e]; },
+            [&]() { return fac; }, [&]() { return Tb[e]; }, dn, un, vn, Tn);
         for (int top = 0; top < 2; ++top) {
           if (!n[e].feeds(top)) continue;
           const int pc = p + (top ? W : -W), kc = k + (top ? g.nx : -g.nx);
