@@ -283,20 +283,21 @@ lks_status lks_write_field(lks_ctx *ctx, int which, const double *dev_in);
  * on this context's stream, keeps the fastest and reports its tile height in
  * *tile_rows (lks_launch_shape gives the whole shape; each sweep direction
  * that is faster with those kernels keeps them). Synchronises; the forward and
- * adjoint states are discarded (run lks_forward afterwards). D2Q9 only (LKS_E_UNSUPPORTED for D3Q19,
- * whose node-parallel kernels have no tile shape). */
+ * adjoint states are discarded (run lks_forward afterwards). D2Q9 only
+ * (LKS_E_UNSUPPORTED for D3Q19, whose kernels have no tile shape). */
 lks_status lks_autotune(lks_ctx *ctx, const double *gamma_dev, int steps, int *tile_rows);
 
 /* Set the tile height (4 or 8 rows of 64 nodes, or 16 for FP32 non-thermal
- * problems) explicitly; results do not depend on it. Discards the forward and
- * adjoint states. D2Q9 only. Two steps per launch apply to heights 4 and 8;
- * with 16 every launch runs one step. */
+ * problems) explicitly, and take the tiled kernels; results do not depend on
+ * it. Discards the forward and adjoint states. D2Q9 only. Two steps per launch
+ * apply to heights 4 and 8; with 16 every launch runs one step. A MIXED context
+ * takes heights 4 and 8. */
 lks_status lks_set_tile_rows(lks_ctx *ctx, int tile_rows);
 
-/* Time steps per kernel launch, forward (lks_advance, lks_forward, and the
- * checkpoint replays of an unsteady alks_backward) and adjoint (steady
- * alks_backward, alks_advance; an unsteady adjoint sweep runs one step per
- * launch): 1, or 2 for FP32 D2Q9 problems and for the forward sweep of FP64
+/* Time steps per launch of the tiled kernels, which both sweeps take from here
+ * on: forward (lks_advance, lks_forward, and the checkpoint replays of an
+ * unsteady alks_backward) and adjoint (steady alks_backward, alks_advance; an
+ * unsteady adjoint sweep on tiles runs one step per launch): 1, or 2 for FP32 D2Q9 problems and for the forward sweep of FP64
  * non-thermal D2Q9 problems (LKS_E_UNSUPPORTED otherwise; a MIXED context
  * applies forward_steps to its FP64 forward and adjoint_steps to its FP32
  * adjoint). With 2, each launch loads its tile with a 4-node halo and runs
@@ -446,7 +447,8 @@ lks_status lks_batch_run(lks_batch *b, const double *const *gamma_dev, int n_fwd
                          double J_seed, double *const *dJdgamma_dev, double *J_host,
                          int use_graph);
 /* Tile autotuner of a steady batch: runs the batch eagerly for `steps`
- * forward and adjoint steps per tile height and keeps the fastest.
+ * forward and adjoint steps with its several-steps or marching kernels, if any,
+ * and per tile height, and keeps the fastest.
  * scratch_dev[d] receives a throw-away sensitivity. Synchronises. Unsteady
  * batches: LKS_E_UNSUPPORTED. */
 lks_status lks_batch_autotune(lks_batch *b, const double *const *gamma_dev, int steps,

@@ -103,11 +103,14 @@ struct RingFillT {
   T ka[4], ke[4];
   T A0, A1, A2, Hc, H1;
 };
-// bytes of the workspace the operators of a D2Q9 context are given; what the
-// operators leave of it holds RING_ACC objective accumulators
-constexpr size_t RING_OPS_BYTES = 4 * 1264;
+// Bytes of the workspace the operators of a D2Q9 context are given, and behind
+// them RING_ACC objective accumulators: at least two for each of the 256 tiles
+// of a one-round launch of the several-steps kernels. (5056, the former size of
+// the slice, so that a workspace of a stored size still fits.)
+constexpr size_t RING_OPS_BYTES = 5056;
 constexpr int RING_ACC = int((RING_OPS_BYTES - 512) / sizeof(double));
 static_assert(sizeof(RingFillT<double>) <= 512, "operators leave room for the accumulators");
+static_assert(RING_ACC >= 512, "accumulators of two rounds of tiles");
 
 // element-wise conversion of operator tables (host)
 template <typename D, typename S>
@@ -332,8 +335,10 @@ inline FaceFillT<R> face_fill_as(const FaceFillT<double>& s) {
   conv_op(d.A2, s.A2); conv_op(d.Hc, s.Hc); conv_op(d.H1, s.H1);
   return d;
 }
-// bytes of the workspace the face operators of a D3Q19 context are given
-constexpr size_t FACE_OPS_BYTES = 6 * 4056;
+// Bytes of the workspace the face operators of a D3Q19 context are given: more
+// than they need, but the former size of the slice, so that a workspace of a
+// stored size still fits.
+constexpr size_t FACE_OPS_BYTES = 24336;
 static_assert(sizeof(FaceFillT<double>) <= FACE_OPS_BYTES, "face operators fit their slice");
 void build_face_fill(double A, double Bf, FaceFillT<double>& fill);
 

@@ -494,7 +494,8 @@ template <typename R, bool TH, int TY>
 // (8 waves per SIMD in FP32 without temperature: a ninth group of SGPRs, to which
 // the compiler would go, leaves 7 and so three blocks of 8 waves per CU instead of
 // four; 2048 x 1024 on 64 x 4 tiles 27.3 us instead of 25.9)
-__global__ __launch_bounds__((NT1<R, TH, TY>), sizeof(R) == 4 && !TH ? 8 : 1) void lks_step_kernel(Geo g, FwdArgs<R> a) {
+__global__ __launch_bounds__((NT1<R, TH, TY>), sizeof(R) == 4 && !TH ? 8 : 1)
+void lks_step_kernel(Geo g, FwdArgs<R> a) {
   __shared__ FwdLds<R, TH, TY> L;
   int x0, x1, y0, y1, tile;
   if (!block_tile(g, &x0, &x1, &y0, &y1, &tile)) return;

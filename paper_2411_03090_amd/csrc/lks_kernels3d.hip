@@ -341,8 +341,8 @@ __device__ inline void zregion(const Geo3& g, const ZTile& t, int off[SRL]) {
 // Bound by instructions. Forming all 19 values at the source and sending each
 // behind a test of its target, with a branch for each difference, took 135 us
 // on 256 x 128 x 128 in FP32 and 74 us on 97 x 61 x 53 in FP64; this way it is
-// 75 and 41 us, and 29 us in whole rounds of blocks (172 MB of FP32 traffic, 28 us
-// at the rate of a copy).
+// 75 and 41 us, the second 29 us in whole rounds of blocks. In the first 260 MB pass
+// below the L2, 3.5 TB/s; a copy of that size reaches 5.3.
 template <typename R>
 struct alignas(2 * sizeof(R)) V2 {
   R x, y;
@@ -1553,8 +1553,8 @@ __global__ __launch_bounds__(ZT) void alks3e_kernel(Geo3 g, Adj3Args<R> a) {
 // alks3e<ENDS> updates afterwards.
 // Bound by instructions. Reading the 19 values of a node from three planes of
 // LDS took 157 us on 256 x 128 x 128 in FP32 and 58 us on 97 x 61 x 53 in FP64;
-// this way it is 121 and 41 us (108 with packed x-face moments), 523 MB passing below the L2 in the first (4.3
-// TB/s, a copy reaches 6.2).
+// this way it is 121 and 41 us, the first 106 us with packed x-face moments (417 MB
+// pass below the L2 then, 3.9 TB/s; a copy of that size reaches 5.3).
 template <typename R>
 struct AdjFLds {
   V4<R> p[NSR];  // rho~, V of plane s

@@ -557,7 +557,7 @@ __global__ __launch_bounds__(256) void alks_march_batch_kernel(const BatchAdj<R>
   march_adj<R, K>(g, a, tmap[2 * t + 1], batch_shape(g, k, rows));
 }
 
-// Waves of a launch: one per SIMD in FP64 and two in FP32, what the registers of
+// Waves of a launch: one per SIMD (of 1024) in FP64 and two in FP32, what the registers of
 // three and two steps allow. A second round of waves costs more than it hides
 // (2048 x 2048 FP32 adjoint, 8 % over one round: 31 instead of 19 us).
 constexpr int round_waves(int rsz) { return (rsz == 8 ? 1024 : 2048) - 8; }

@@ -763,7 +763,7 @@ void tiles_for(const Geo& g, int most, int* ntx, int* nty) {
 
 MultiPlan multi_plan(const Geo& g, int rsz, bool adj, int max_tiles) {
   const bool th = g.thermal;
-  // rounds of one block per CU. FP32 without temperature: the tile kernels'
+  // rounds of one block per CU of the 256. FP32 without temperature: the tile kernels'
   // 64 x 8 and 64 x 16 blocks overlap their loads with each other's work and
   // need no halo of 2k nodes, and are ahead from 1024 x 768 on (8.8 against
   // 9.5 us per forward step; 1024 x 512: 6.7 against 6.4). FP32 thermal: 1536 x

@@ -1,6 +1,7 @@
 // Device functions of the D2Q9 LKS and ALKS steps that act on one node, shared
-// by the tile kernels (lks_kernels.hip) and the several-steps kernels of small
-// grids (lks_multi.hip). They take values rather than positions and contract
+// by the tile kernels (lks_kernels.hip), the several-steps kernels of small
+// grids (lks_multi.hip) and the marching kernels of large ones (lks_march.hip).
+// They take values rather than positions and contract
 // multiply-adds only within a source expression, so that every kernel built on
 // them gives the same bits.
 #pragma once
@@ -438,8 +439,7 @@ struct AdjNode {
 // coupling, implicit Brinkman), then V and Theta of the new level from the
 // node's moments, div s~ = (dsx, dsy) and dq = div q~ (paper) or div (B q~)
 // (exact). pair is the Brinkman pairing of the sensitivity, adj_T the T~ or
-// Theta that pairs with the heat source. Accessors dq() and the like are
-// only called where the term exists.
+// Theta that pairs with the heat source.
 template <typename R, bool TH>
 __device__ inline void adj_node(const Geo& g, const AdjArgs<R>& a, const AdjNode<R>& n,
                                 const R mom[9], R dsx, R dsy, R dq, R& r_out, R& Vx, R& Vy, R& Th,

@@ -1989,7 +1989,7 @@ void lks_destroy(lks_ctx* c) {
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// batches: many independent steady designs, one launch per step
+// batches: many independent designs in one sequence of launches
 // ---------------------------------------------------------------------------
 struct lks_batch {
   int n = 0;
